@@ -74,6 +74,7 @@ struct fps_sim {
     int32_t n_door, door_rate;
     uint64_t door_seed;
     bool numeric_fault;
+    bool counts;               // evacuee counts were set since creation or the last clearing: they may be non-zero
 };
 
 struct Engine {
@@ -89,13 +90,14 @@ struct Engine {
     int* chunk_off_d = nullptr;
     std::vector<Scn> scn_h;
     std::vector<int> tile_off_h, agent_off_h, chunk_off_h;
-    int total_tiles = 0, total_agents = 0, total_chunks = 0, fv_blocks = 0;
+    int total_tiles = 0, total_agents = 0, total_chunks = 0, red_chunks = 0, fv_blocks = 0;
     int64_t max_cells = 0;
     int fin_lds_bytes = 0;
     bool any_big = false;
     bool any_doors = false;          // some scenario runs the pre-flood door flow
     bool dirty = true;
     int graph_chunk = 16;
+    bool people = false;             // some scenario may have non-zero evacuee counts
     int hll = 0;                     // face flux of every scenario: HLL instead of HLLC
     int order2 = 0;                  // second-order (MUSCL, two-stage) variant for every scenario
     hipGraphExec_t exec = nullptr;
@@ -263,7 +265,6 @@ fps_sim* new_member(Engine* e, int idx, const fps_grid_desc* d, const fps_ped_pa
     s->doors = at<int32_t>(base, L.doors);
     s->csum = at<int32_t>(base, L.csum);
     s->line_cap = L.line_cap;
-    s->H = fv_rows_per_wave(d->nx, d->ny);
     s->bsx = std::max(1, (int)std::ceil(P.r_cut / d->dx - 1e-9));
     s->bsy = std::max(1, (int)std::ceil(P.r_cut / d->dy - 1e-9));
     s->nbx = (d->nx + s->bsx - 1) / s->bsx;
@@ -404,12 +405,17 @@ int upload(Engine* e)
     e->max_cells = 0;
     e->any_big = false;
     e->any_doors = false;
+    e->people = false;
+    e->red_chunks = 0;
     e->fin_lds_bytes = 0;
     for (int k = 0; k < e->S; ++k) {
         fps_sim* s = e->m[k];
         fill_scn(s, e->scn_h[k]);
         e->tile_off_h[k + 1] = e->tile_off_h[k] + e->scn_h[k].fv.ntiles;
         e->agent_off_h[k + 1] = e->agent_off_h[k] + (s->na + kPedBlock - 1) / kPedBlock * kPedBlock;
+        e->people = e->people || s->counts;
+        const int nt = e->scn_h[k].fv.ntiles;
+        if (nt > kRedMin) e->red_chunks = std::max(e->red_chunks, (nt + kRedTiles - 1) / kRedTiles);
         e->max_cells = std::max(e->max_cells, (int64_t)s->G.nx * s->G.ny);
         e->chunk_off_h[k + 1] = e->chunk_off_h[k] + e->scn_h[k].bins.nchunk;
         e->any_big = e->any_big || (s->na > 0 && !e->scn_h[k].inline_place);
@@ -451,6 +457,8 @@ Batch batch_of(const Engine* e, int s_only = -1)
     b.s_only = s_only;
     b.hll = e->hll;
     b.order2 = e->order2;
+    b.people = e->people;
+    b.red_chunks = e->red_chunks;
     if (s_only >= 0) b.fv_blocks = fv_blocks_for_tiles(e->scn_h[s_only].fv.ntiles);
     if (e->S == 1) b.one = e->scn_h[0];
     return b;
@@ -467,6 +475,7 @@ int prime(fps_sim* s)
     if (rc != FPS_OK) return fail(s, rc, "%s", e->err);
     Batch b = batch_of(e);
     HIPCHK(s, launch_fv_scan(b, s->idx, e->scn_h[s->idx].fv.ntiles, e->stream));
+    HIPCHK(s, launch_fv_reduce(b, s->idx, 1, e->stream));
     HIPCHK(s, launch_finalize(b, 1, s->idx, 1, e->stream));
     return FPS_OK;
 }
@@ -516,6 +525,7 @@ int step_launches(Engine* e, hipStream_t st, KernelEvents* K)
         rec(1, 1);
     }
     rec(2, 0);
+    HIPCHK_E(e, launch_fv_reduce(b, 0, e->S, st));
     if (e->total_chunks > 0) HIPCHK_E(e, launch_bin_chunk_sum(b, st));
     HIPCHK_E(e, launch_finalize(b, 0, 0, e->S, st));
     if (e->total_chunks > 0) HIPCHK_E(e, launch_bin_chunk_scan(b, st));
@@ -849,6 +859,7 @@ int build_engine(Engine* e, int32_t S, const fps_grid_desc* descs, const fps_ped
     o += align256(sizeof(int) * (S + 1));
     e->chunk_off_d = at<int>(ws, o);
     o += align256(sizeof(int) * (S + 1));
+    const int rows = fv_rows_per_wave(descs, S);
     for (int k = 0; k < S; ++k) {
         fps_ped_params P;
         if (peds) P = peds[k];
@@ -858,6 +869,7 @@ int build_engine(Engine* e, int32_t S, const fps_grid_desc* descs, const fps_ped
         if (!s) return efail(e, FPS_E_DEVICE, "out of host memory");
         e->m.push_back(s);
         o += member_layout(&descs[k], ma).total;
+        s->H = rows;
         int rc = init_member_device(s);
         if (rc != FPS_OK) return efail(e, rc, "%s", s->err);
     }
@@ -1300,6 +1312,7 @@ int fps_bind_agents(fps_sim* s, int32_t n, float* x, float* y, float* vx, float*
             return fail(s, FPS_E_INVALID, "fps_bind_agents: %d agents with invalid role/state/dest", bad[1]);
     }
     s->na = n;
+    s->counts = s->counts || n > 0;
     s->body_h = s->body_m = nullptr;      // bodies follow the agents: set them again
     s->x = x; s->y = y; s->vx = vx; s->vy = vy; s->vbase = v_base;
     s->role = role; s->state = state; s->cls = hr_class; s->dest = dest; s->timer = timer;
@@ -1461,6 +1474,11 @@ int fps_set_occupancy(fps_sim* s, const int32_t* counts)
     const size_t nc = (size_t)s->G.nx * s->G.ny;
     if (counts) HIPCHK(s, hipMemcpyAsync(s->np, counts, sizeof(int32_t) * nc, hipMemcpyDeviceToDevice, st));
     else HIPCHK(s, launch_fill_i32(s->np, 0, (int64_t)nc, st));
+    // whether the flood update reads the counts at all follows from here
+    if (s->counts != (counts != nullptr)) {
+        s->counts = counts != nullptr;
+        mark_dirty(s);
+    }
     return FPS_OK;
 }
 

@@ -26,6 +26,8 @@
 // ensemble; each wave finds its scenario and reads its parameters.
 #include "fps_device.h"
 
+#include <type_traits>
+
 namespace fps {
 namespace {
 
@@ -86,15 +88,6 @@ __device__ __forceinline__ Cell load_raw(const Src& src, const FvParams& p, int 
     c.qy = ld(src.qy, k);
     c.z = ld(src.z, k);
     return c;
-}
-
-__device__ __forceinline__ void derive(const FvParams& p, Cell& c, bool mirror_x, int j)
-{
-    if (mirror_x) c.qx = -c.qx;
-    if ((j < 0 && p.bc[2] == FPS_BC_WALL) || (j >= p.ny && p.bc[3] == FPS_BC_WALL)) c.qy = -c.qy;
-    float r = c.h > p.eps ? rcp(c.h) : 0.0f;
-    c.u = c.qx * r;
-    c.v = c.qy * r;
 }
 
 // Hydrostatic pressure 1/2 g h^2 of a reconstructed depth.  Never contracted
@@ -168,6 +161,60 @@ __device__ __forceinline__ void face_flux(const FvParams& p, float hL, float unL
     F2 = (none || wall) ? 0.0f : H2;
 }
 
+// The same face for the first-order march, with every fused multiply-add
+// written out (each instantiation and each row rounds alike) and what the
+// general form spends on selections left out:
+//  - z_f - z_L and z_f - z_R are the positive and the negative part of the
+//    bed step;
+//  - a face dry on both sides has zero depths, discharges and pressures, so
+//    only its denominator needs a guard, not its fluxes;
+//  - the contact speed has the sign of the HLL mass flux, whose numerator is
+//    sR hL (uL - sL) - sL hR (uR - sR), so F0 selects the tangential velocity.
+// GL / GR: the normal momentum flux less the pressure of the reconstructed
+// depth on that side (what the cell on that side receives).  kProd: the right
+// side's normal velocity is the product rR * qR, which enters the sums with
+// it unrounded.
+template <bool kHll, bool kProd>
+__device__ __forceinline__ void face_march(const FvParams& p, float hL, float unL, float utL, float zL, float hR,
+                                           float unR, float utR, float zR, float rR, float qR, bool wall,
+                                           float& F0, float& GL, float& GR, float& F2)
+{
+#pragma clang fp contract(off)
+    const float dz = zR - zL;
+    float hl = hL - fmaxf(dz, 0.0f);
+    float hr = hR + fminf(dz, 0.0f);
+    const bool wetL = hl > p.eps, wetR = hr > p.eps;
+    hl = wetL ? hl : 0.0f;
+    hr = wetR ? hr : 0.0f;
+    const float pL = p.half_g * hl * hl, pR = p.half_g * hr * hr;
+    const float cL = sqrt_fast(p.g * hl), cR = sqrt_fast(p.g * hr);
+    const float sum = kProd ? fmaf(rR, qR, unL) : unL + unR;
+    const float dif = kProd ? fmaf(-rR, qR, unL) : unL - unR;
+    const float us = fmaf(0.5f, sum, cL) - cR;
+    const float cs = fmaf(0.25f, dif, 0.5f * (cL + cR));
+    const float lo = unL - cL, hi = kProd ? fmaf(rR, qR, cR) : unR + cR;
+    // dry-bed wave speeds, then both clamped to either side of zero
+    float sL = wetR ? fminf(lo, us - cs) : lo;
+    float sR = wetR ? fmaxf(hi, us + cs) : fmaf(2.0f, cL, unL);
+    sL = fminf(wetL ? sL : fmaf(-2.0f, cR, unR), 0.0f);
+    sR = fmaxf(wetL ? sR : hi, 0.0f);
+    const float qL = hl * unL, qr = hr * unR;
+    const float ML = fmaf(qL, unL, pL), MR = fmaf(qr, unR, pR);
+    const float inv = rcp(fmaxf(sR - sL, 1e-30f));
+    const float H0 = fmaf(inv, sL * fmaf(hr - hl, sR, fmaf(-hr, unR, qL)), qL);
+    const float F1 = fmaf(inv, sL * fmaf(fmaf(hr, unR, -qL), sR, ML - MR), ML);
+    F0 = wall ? 0.0f : H0;
+    GL = F1 - pL;
+    GR = F1 - pR;
+    if (kHll) {
+        const float tL = qL * utL;
+        const float H2 = fmaf(inv, sL * fmaf(fmaf(utR, hr, -(utL * hl)), sR, fmaf(-utR, qr, tL)), tL);
+        F2 = wall ? 0.0f : H2;
+    } else {
+        F2 = F0 * (F0 >= 0.0f ? utL : utR);
+    }
+}
+
 // Wave reductions by DPP lane moves (VALU only, no LDS round trips): pairs,
 // quads (quad permutes), eight and sixteen lanes (half-row and row mirrors)
 // leave every lane of a row with the row's total; the row broadcasts of lanes
@@ -234,7 +281,18 @@ __device__ __forceinline__ int xcd_tile_block(int b, int nblocks)
     return (b & 7) * per + (b >> 3);
 }
 
-template <bool kOne, bool kHll>
+// What bounds it: VALU issue while it takes more than about 200 instructions a
+// row of 62 cells, HBM below that.  With 266 a row (22 of them copies of the
+// rows in flight and the carried face, 20 more for volumes that only edge
+// cells have) the counters showed the VALU busy for all of the launch: 8192^2
+// wet cells, 499 us at 16 rows a wave.  Written with four rows a turn (no
+// copies), rare work behind uniform branches and the leaner face, 212 a row:
+// 423 us, 28 B a cell at 4.45 TB/s (a 1 GiB copy on the card: 4.95 TB/s), with
+// the same bits.  1531 x 977: 17.7 -> 16.5 us; 6 x 2048^2 with people: 204 ->
+// 184 us.  Loads run four rows ahead, so a wave keeps 16 of them in flight.
+// kPeople: some scenario has evacuee counts (they raise the friction); without
+// any the counts are not read (4 of 32 B a cell).
+template <bool kOne, bool kHll, bool kPeople>
 __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -299,116 +357,155 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
         const int ii = min(max(i, 0), p.nx - 1);
         const int j0 = sy * p.H, j1 = min(j0 + p.H, p.ny);
         const bool out_lane = lane >= 1 && lane <= kStrip && i < p.nx;
+        // what only the strips on the west and east sides do (wave-uniform)
+        const bool first_strip = sx == 0, last_strip = sx == p.nsx - 1;
+        const bool side_strip = first_strip || last_strip;
         const bool mirror_x = (i < 0 && p.bc[0] == FPS_BC_WALL) || (i >= p.nx && p.bc[1] == FPS_BC_WALL);
         const bool xwall = (i == -1 && p.bc[0] == FPS_BC_WALL) ||
                            (i + 1 == p.nx && p.bc[1] == FPS_BC_WALL);
-        bool inflow_col = false;
-        if (p.inflow_side == FPS_SIDE_S || p.inflow_side == FPS_SIDE_N)
-            inflow_col = i >= p.c0 && i < p.c1;
+        const bool inflow_x = (p.inflow_side == FPS_SIDE_W && first_strip) || (p.inflow_side == FPS_SIDE_E && last_strip);
+        const int in_row = p.inflow_side == FPS_SIDE_S ? 0 : p.inflow_side == FPS_SIDE_N ? p.ny - 1 : -1;
+        const int in_col = p.inflow_side == FPS_SIDE_W ? 0 : p.nx - 1;
+        const bool out_w = first_strip && p.bc[0] == FPS_BC_TRANSMISSIVE, out_e = last_strip && p.bc[1] == FPS_BC_TRANSMISSIVE;
+        const int out_s = p.bc[2] == FPS_BC_TRANSMISSIVE ? 0 : -1, out_n = p.bc[3] == FPS_BC_TRANSMISSIVE ? p.ny - 1 : -1;
+        const float kn0 = p.n_base * (p.g * p.n_base);        // g n^2 of a cell with no evacuees
+        // largest |u| + c and |v| + c of the lane's cells, as bits (they order
+        // as the non-negative values do, and a NaN comes through)
+        unsigned umax = 0, vmax = 0;
 
-        // Row j0-1 now, rows j0 .. j0+2 in flight (rows past j1 are never needed).  The first pass of the loop
-        // (j = j0-1) only forms the face below row j0, so every y face goes
-        // through the same code (same rounding) whatever the tile height.
-        Cell c = load_raw(src, p, ii, j0 - 1);
-        Cell pf0 = load_raw(src, p, ii, j0);
-        Cell pf1 = {}, pf2 = {};
-        if (j0 + 1 <= j1) pf1 = load_raw(src, p, ii, j0 + 1);
-        if (j0 + 2 <= j1) pf2 = load_raw(src, p, ii, j0 + 2);
-        derive(p, c, mirror_x, j0 - 1);
-        float Fs0 = 0.0f, Fs1 = 0.0f, Fs2 = 0.0f, pS = 0.0f;
-        for (int j = j0 - 1; j < j1; ++j) {
-            Cell nb = pf0;
-            pf0 = pf1;
-            pf1 = pf2;
-            if (j + 4 <= j1) pf2 = load_raw(src, p, ii, j + 4);   // rows above the tile's last need stay unread
-            derive(p, nb, mirror_x, j + 1);
-            // north face (y normal: pass v as normal, u as tangential)
-            float Fn0, Fn1, Fn2, pN, pS_next;
-            face_flux<kHll>(p, c.h, c.v, c.u, c.z, nb.h, nb.v, nb.u, nb.z,
-                      (j + 1 == 0 && p.bc[2] == FPS_BC_WALL) || (j + 1 == p.ny && p.bc[3] == FPS_BC_WALL),
-                      Fn0, Fn1, Fn2, pN, pS_next);
-            if (j < j0) {
-                Fs0 = Fn0;
-                Fs1 = Fn1;
-                Fs2 = Fn2;
-                pS = pS_next;
-                c = nb;
-                continue;
-            }
-            const uint32_t k = (uint32_t)j * (uint32_t)p.nx + (uint32_t)i;
+        // the derived velocities of a raw row (ghost rows and columns mirrored at
+        // walls) and the reciprocal depth
+        auto prim = [&](const Cell& raw, int j, float& r) {
+            Cell c = raw;
+            r = c.h > p.eps ? rcp(c.h) : 0.0f;
+            if (side_strip && mirror_x) c.qx = -c.qx;
+            if ((j < 0 && p.bc[2] == FPS_BC_WALL) || (j >= p.ny && p.bc[3] == FPS_BC_WALL)) c.qy = -c.qy;
+            c.u = c.qx * r;
+            c.v = c.qy * r;
+            return c;
+        };
+        struct Flux {
+            float F0, G, F2;       // mass, normal momentum less the upper cell's pressure, tangential momentum
+        };
+        // row j with its cells c, the face below it s and the raw row above it
+        // (held in ring, which then takes the row four further up): the face
+        // above goes to n, the cells above to nb
+        auto row = [&](const Cell& c, Cell& nb, Cell& ring, int j, const Flux& s, Flux& n, auto fetch) {
+            const uint32_t k = (uint32_t)j * (uint32_t)p.nx + (uint32_t)ii;     // ii: in the grid on every lane
             int npc = 0;
-            if (out_lane) npc = ld(npp, k);
-            // east face with the neighbour lane's cell
-            float eh = lane_from_above(c.h), eu = lane_from_above(c.u);
-            float ev = lane_from_above(c.v), ez = lane_from_above(c.z);
-            float Fe0, Fe1, Fe2, pE, pW_east;
-            face_flux<kHll>(p, c.h, c.u, c.v, c.z, eh, eu, ev, ez, xwall, Fe0, Fe1, Fe2, pE, pW_east);
-            // west face = east face of the lane below
-            float Fw0 = lane_from_below(Fe0), Fw1 = lane_from_below(Fe1);
-            float Fw2 = lane_from_below(Fe2), pW = lane_from_below(pW_east);
+            if (kPeople) npc = ld(npp, k);
+            float rn;
+            nb = prim(ring, j + 1, rn);
+            // a row past the tile's last need is replaced by that row (cached):
+            // a load under a condition would make the compiler copy the ring,
+            // and so wait for its loads, at every row
+            if constexpr (decltype(fetch)::value) ring = load_raw(src, p, ii, min(j + 5, j1));
+            // north face (y normal: v normal, u tangential)
+            float Gn;
+            face_march<kHll, true>(p, c.h, c.v, c.u, c.z, nb.h, nb.v, nb.u, nb.z, rn, nb.qy,
+                                   j + 1 == p.ny && p.bc[3] == FPS_BC_WALL, n.F0, Gn, n.G, n.F2);
+            // east face with the neighbour lane's cell; the west face is the east face of the lane below
+            const float eh = lane_from_above(c.h), eu = lane_from_above(c.u);
+            const float ev = lane_from_above(c.v), ez = lane_from_above(c.z);
+            float Fe0, Ge, Gw_next, Fe2;
+            face_march<kHll, false>(p, c.h, c.u, c.v, c.z, eh, eu, ev, ez, 0.0f, 0.0f, xwall, Fe0, Ge, Gw_next, Fe2);
+            const float Fw0 = lane_from_below(Fe0), Gw = lane_from_below(Gw_next), Fw2 = lane_from_below(Fe2);
             if (out_lane) {
-                float hn = c.h - (lx * (Fe0 - Fw0) + ly * (Fn0 - Fs0));
-                float qxn = c.qx - (lx * ((Fe1 - pE) - (Fw1 - pW)) + ly * (Fn2 - Fs2));
-                float qyn = c.qy - (ly * ((Fn1 - pN) - (Fs1 - pS)) + lx * (Fe2 - Fw2));
+#pragma clang fp contract(off)
+                float hn = c.h - fmaf(ly, n.F0 - s.F0, lx * (Fe0 - Fw0));
+                float qxn = c.qx - fmaf(ly, n.F2 - s.F2, lx * (Ge - Gw));
+                float qyn = c.qy - fmaf(ly, Gn - s.G, lx * (Fe2 - Fw2));
                 // inflow line source (sec. 3.1)
-                bool inflow = false;
-                if (p.inflow_side == FPS_SIDE_S) inflow = inflow_col && j == 0;
-                else if (p.inflow_side == FPS_SIDE_N) inflow = inflow_col && j == p.ny - 1;
-                else if (p.inflow_side == FPS_SIDE_W) inflow = i == 0 && j >= p.c0 && j < p.c1;
-                else if (p.inflow_side == FPS_SIDE_E) inflow = i == p.nx - 1 && j >= p.c0 && j < p.c1;
-                if (inflow) hn += inc;
+                if (j == in_row) {
+                    if (i >= p.c0 && i < p.c1) hn += inc;
+                } else if (inflow_x && j >= p.c0 && j < p.c1) {
+                    if (i == in_col) hn += inc;
+                }
                 // non-negative depth, no discharge on dry cells
                 if (hn < 0.0f) {
+                    asm volatile("");      // a branch (rare), not a sum selected afterwards
                     vclip_acc += (double)(-hn);
                     hn = 0.0f;
                 }
-                if (!(hn > p.eps)) {
+                if (hn > p.eps) {
+                    // Manning friction, splitting point-implicit (still water: the
+                    // guard keeps a finite, and nothing is taken off)
+                    const float r = rcp(hn);
+                    float u = qxn * r, v = qyn * r;
+                    const float uu = u * u, vv = v * v;
+                    const float speed = sqrt_fast(fmaxf(fmaf(u, u, vv), 1e-36f));
+                    float kn = kn0;
+                    if (kPeople) {
+                        const float n_ = fmaf(p.n_base, (float)min(npc, p.np_cap), p.n_base);
+                        kn = n_ * (p.g * n_);
+                    }
+                    const float Cf = kn * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(hn) * (-1.0f / 3.0f));
+                    const float Sx = u * -Cf * speed, Sy = v * -Cf * speed;
+                    const float a = dt * Cf * r * rcp(speed);
+                    const float Dx = fmaf(fmaf(u, u + u, vv), a, 1.0f), Dy = fmaf(fmaf(v, v + v, uu), a, 1.0f);
+                    float dqx = dt * Sx * rcp(Dx), dqy = dt * Sy * rcp(Dy);
+                    if (fabsf(dqx) > fabsf(qxn)) dqx = -qxn;
+                    if (fabsf(dqy) > fabsf(qyn)) dqy = -qyn;
+                    qxn += dqx;
+                    qyn += dqy;
+                    u = qxn * r;
+                    v = qyn * r;
+                    const float cel = sqrt_fast(p.g * hn);
+                    umax = max(umax, __builtin_bit_cast(unsigned, fabsf(u) + cel));
+                    vmax = max(vmax, __builtin_bit_cast(unsigned, fabsf(v) + cel));
+                } else {
                     qxn = 0.0f;
                     qyn = 0.0f;
                 }
-                if (hn > p.eps) {
-                    float r = rcp(hn);
-                    float u = qxn * r, v = qyn * r;
-                    float V2 = u * u + v * v;
-                    if (V2 > 0.0f) {
-                        // Manning friction, splitting point-implicit
-                        float n = p.n_base + (float)min(npc, p.np_cap) * p.n_base;
-                        float speed = sqrt_fast(V2);
-                        float hm13 = __builtin_amdgcn_exp2f(-__builtin_amdgcn_logf(hn) * (1.0f / 3.0f));
-                        float Cf = p.g * n * n * hm13;
-                        float Sx = -Cf * u * speed, Sy = -Cf * v * speed;
-                        float a = dt * Cf * r * rcp(speed);
-                        float Dx = 1.0f + a * (2.0f * u * u + v * v);
-                        float Dy = 1.0f + a * (2.0f * v * v + u * u);
-                        float dqx = dt * Sx * rcp(Dx), dqy = dt * Sy * rcp(Dy);
-                        if (fabsf(dqx) > fabsf(qxn)) dqx = -qxn;
-                        if (fabsf(dqy) > fabsf(qyn)) dqy = -qyn;
-                        qxn += dqx;
-                        qyn += dqy;
-                        u = qxn * r;
-                        v = qyn * r;
-                    }
-                    float cel = sqrt_fast(p.g * hn);
-                    smax = fmaxf(smax, fmaxf((fabsf(u) + cel) * p.inv_dx, (fabsf(v) + cel) * p.inv_dy));
-                }
                 m_acc += (double)hn;
                 // outflow through transmissive sides
-                if (i == 0 || i == p.nx - 1 || j == 0 || j == p.ny - 1) {    // rare: skipped by most waves
-                    if (i == 0 && p.bc[0] == FPS_BC_TRANSMISSIVE) vout_acc -= (double)Fw0 * dt * p.dy;
-                    if (i == p.nx - 1 && p.bc[1] == FPS_BC_TRANSMISSIVE) vout_acc += (double)Fe0 * dt * p.dy;
-                    if (j == 0 && p.bc[2] == FPS_BC_TRANSMISSIVE) vout_acc -= (double)Fs0 * dt * p.dx;
-                    if (j == p.ny - 1 && p.bc[3] == FPS_BC_TRANSMISSIVE) vout_acc += (double)Fn0 * dt * p.dx;
+                if (out_w || out_e || j == out_s || j == out_n) {
+                    asm volatile("");      // skipped by most waves
+                    if (out_w && i == 0) vout_acc -= (double)Fw0 * dt * p.dy;
+                    if (out_e && i == p.nx - 1) vout_acc += (double)Fe0 * dt * p.dy;
+                    if (j == out_s) vout_acc -= (double)s.F0 * dt * p.dx;
+                    if (j == out_n) vout_acc += (double)n.F0 * dt * p.dx;
                 }
                 st_at(ho, k, hn);
                 st_at(qxo, k, qxn);
                 st_at(qyo, k, qyn);
             }
-            Fs0 = Fn0;
-            Fs1 = Fn1;
-            Fs2 = Fn2;
-            pS = pS_next;
-            c = nb;
+        };
+
+        // The rows j0 - 1 and j0 form the face below the tile; then the march,
+        // four rows a turn, so that the cells, the carried face and the four
+        // rows in flight stay where they are instead of being moved along.
+        // Every row runs the same code (same rounding) whatever the tile height.
+        Cell A = load_raw(src, p, ii, j0 - 1);
+        Cell R0 = load_raw(src, p, ii, j0), R1 = {}, R2 = {}, R3 = {}, Bc;
+        if (j0 + 1 <= j1) R1 = load_raw(src, p, ii, j0 + 1);
+        if (j0 + 2 <= j1) R2 = load_raw(src, p, ii, j0 + 2);
+        if (j0 + 3 <= j1) R3 = load_raw(src, p, ii, j0 + 3);
+        Flux Fa, Fb;
+        {
+            float ra, rb, unused;
+            A = prim(A, j0 - 1, ra);
+            Bc = prim(R0, j0, rb);
+            if (j0 + 4 <= j1) R0 = load_raw(src, p, ii, j0 + 4);
+            face_march<kHll, true>(p, A.h, A.v, A.u, A.z, Bc.h, Bc.v, Bc.u, Bc.z, rb, Bc.qy,
+                                   j0 == 0 && p.bc[2] == FPS_BC_WALL, Fa.F0, unused, Fa.G, Fa.F2);
         }
+        const std::true_type fetch{};
+        const std::false_type last{};
+        int j = j0;
+        for (; j + 4 <= j1; j += 4) {
+            row(Bc, A, R1, j, Fa, Fb, fetch);
+            row(A, Bc, R2, j + 1, Fb, Fa, fetch);
+            row(Bc, A, R3, j + 2, Fa, Fb, fetch);
+            row(A, Bc, R0, j + 3, Fb, Fa, fetch);
+        }
+        if (j < j1) {
+            row(Bc, A, R1, j, Fa, Fb, last);
+            if (j + 1 < j1) row(A, Bc, R2, j + 1, Fb, Fa, last);
+            if (j + 2 < j1) row(Bc, A, R3, j + 2, Fa, Fb, last);
+        }
+        const float su = __builtin_bit_cast(float, umax) * p.inv_dx, sv = __builtin_bit_cast(float, vmax) * p.inv_dy;
+        smax = __builtin_bit_cast(float, max(__builtin_bit_cast(unsigned, su), __builtin_bit_cast(unsigned, sv)));
     }
     // wave partials, fixed reduction order; reduced by the finalize kernel.
     // Outflow and clipped volumes are zero in almost every wave (outflow only
@@ -774,6 +871,60 @@ __global__ __launch_bounds__(kFvBlock) void fv_scan_kernel(Batch B, int sc)
     }
 }
 
+// First level of the reduction of a large grid's partials (more than
+// kRedMin tiles): block c adds the partials of tiles [c kRedTiles, (c + 1)
+// kRedTiles) in a fixed order into the first of them, which the end-of-step
+// block then reads.  One block reading them all is a chain of dependent loads
+// (8192^2 at 16 rows a wave: 68,096 partials).
+__global__ __launch_bounds__(kFvBlock) void fv_reduce_kernel(Batch B, int s_first)
+{
+    const FvParams& p = B.scn[s_first + blockIdx.y].fv;
+    const int ntiles = p.ntiles, t0 = blockIdx.x * kRedTiles;
+    if (ntiles <= kRedMin || t0 >= ntiles) return;
+    constexpr int kPer = kRedTiles / kFvBlock;
+    double2* P2 = reinterpret_cast<double2*>(p.partials);
+    double2 a[kPer], c[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int b = min(t0 + (int)threadIdx.x + u * kFvBlock, ntiles - 1);
+        a[u] = P2[2 * b];
+        c[u] = P2[2 * b + 1];
+    }
+    double m = 0.0, vo = 0.0, vc = 0.0, sm = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        if (t0 + (int)threadIdx.x + u * kFvBlock < ntiles) {
+            m += a[u].x;
+            vo += a[u].y;
+            vc += c[u].x;
+            sm = fmax(sm, c[u].y);
+        }
+    }
+    __shared__ double red[kFvBlock / kWave][4];
+    m = wave_sum(m);
+    vo = wave_sum(vo);
+    vc = wave_sum(vc);
+    sm = (double)wave_max((float)sm);
+    if ((threadIdx.x & (kWave - 1)) == 0) {
+        const int w = threadIdx.x >> 6;
+        red[w][0] = m;
+        red[w][1] = vo;
+        red[w][2] = vc;
+        red[w][3] = sm;
+    }
+    __syncthreads();      // every partial of the block has been read
+    if (threadIdx.x == 0) {
+        for (int w = 1; w < kFvBlock / kWave; ++w) {
+            m += red[w][0];
+            vo += red[w][1];
+            vc += red[w][2];
+            sm = fmax(sm, red[w][3]);
+        }
+        P2[2 * t0] = make_double2(m, vo);
+        P2[2 * t0 + 1] = make_double2(vc, sm);
+    }
+}
+
 // Exact integral over [a, b] of the piecewise-linear hydrograph (sec. 3.1),
 // on one wave whose lane k holds knot k (tk, qk) for k < nh: lane k takes the
 // part of [a, b] in [t_k, t_k+1] by the trapezoid rule (exact on a linear
@@ -828,7 +979,9 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     DevState* gst = p.st;
     const double* partials = p.partials;
     int32_t* wet = p.wet;
-    const int ntiles = p.ntiles, n_inflow = p.n_inflow, inflow_side = p.inflow_side;
+    // partials of a large grid were added by chunks into every kRedTiles-th one
+    const int every = p.ntiles > kRedMin ? kRedTiles : 1;
+    const int ntiles = (p.ntiles + every - 1) / every, n_inflow = p.n_inflow, inflow_side = p.inflow_side;
     const double dxdy = p.dxdy;
     const float cfl = p.cfl, dt_max = p.dt_max, dn = inflow_side <= 1 ? p.dx : p.dy;
     const bool jmask = p.jmask != nullptr;
@@ -866,7 +1019,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
         double2 a[kPU], c[kPU];
 #pragma unroll
         for (int u = 0; u < kPU; ++u) {
-            const int b = threadIdx.x + u * kScanThreads, bc = b < ntiles ? b : 0;
+            const int b = threadIdx.x + u * kScanThreads, bc = (b < ntiles ? b : 0) * every;
             a[u] = P2[2 * bc];
             c[u] = P2[2 * bc + 1];
         }
@@ -881,10 +1034,11 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
             }
         }
         for (int b = threadIdx.x + kPU * kScanThreads; b < ntiles; b += kScanThreads) {
-            m += partials[4 * b + 0];
-            vo += partials[4 * b + 1];
-            vc += partials[4 * b + 2];
-            sm = fmax(sm, partials[4 * b + 3]);
+            const double* q = partials + 4 * (size_t)b * every;
+            m += q[0];
+            vo += q[1];
+            vc += q[2];
+            sm = fmax(sm, q[3]);
         }
     }
     __syncthreads();
@@ -1062,16 +1216,6 @@ hipError_t launch_stream_probe(float* buf, int64_t n, int64_t stride, int n_in, 
     return hipGetLastError();
 }
 
-int fv_rows_per_wave(int nx, int ny)
-{
-    // long marches on large grids (halo rows amortised), short ones on small
-    // grids so that there are enough waves to spread over the 1024 SIMDs
-    const int64_t nsx = (nx + kStrip - 1) / kStrip;
-    int H = 64;
-    while (H > 4 && nsx * ((ny + H - 1) / H) < 4096) H >>= 1;
-    return H;
-}
-
 int fv_tiles2(int nx, int ny, int H)
 {
     const int64_t nsx = (nx + kStrip2 - 1) / kStrip2;
@@ -1117,12 +1261,20 @@ hipError_t launch_fv(const Batch& b, hipStream_t s)
     }
     if (b.fv_blocks > 0) {
         const dim3 grid(b.fv_blocks), block(kFvBlock);
+        const auto go = [&](auto one, auto hll, auto people) {
+            hipLaunchKernelGGL((fv_step_kernel<decltype(one)::value, decltype(hll)::value, decltype(people)::value>),
+                               grid, block, 0, s, b);
+        };
+        const auto with_people = [&](auto one, auto hll) {
+            if (b.people) go(one, hll, std::true_type{});
+            else go(one, hll, std::false_type{});
+        };
         if (b.S == 1) {
-            if (b.hll) hipLaunchKernelGGL((fv_step_kernel<true, true>), grid, block, 0, s, b);
-            else hipLaunchKernelGGL((fv_step_kernel<true, false>), grid, block, 0, s, b);
+            if (b.hll) with_people(std::true_type{}, std::true_type{});
+            else with_people(std::true_type{}, std::false_type{});
         } else {
-            if (b.hll) hipLaunchKernelGGL((fv_step_kernel<false, true>), grid, block, 0, s, b);
-            else hipLaunchKernelGGL((fv_step_kernel<false, false>), grid, block, 0, s, b);
+            if (b.hll) with_people(std::false_type{}, std::true_type{});
+            else with_people(std::false_type{}, std::false_type{});
         }
     }
     return hipGetLastError();
@@ -1132,6 +1284,34 @@ hipError_t launch_fv_scan(const Batch& b, int scenario, int ntiles, hipStream_t 
 {
     hipLaunchKernelGGL(fv_scan_kernel, dim3(ntiles), dim3(kFvBlock), 0, s, b, scenario);
     return hipGetLastError();
+}
+
+hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t s)
+{
+    if (b.red_chunks > 0)
+        hipLaunchKernelGGL(fv_reduce_kernel, dim3(b.red_chunks, count), dim3(kFvBlock), 0, s, b, s_first);
+    return hipGetLastError();
+}
+
+// Rows per wave before any tuning: the longest march (fewest halo rows) that
+// still gives the chip kMinWaves waves, at most 16 rows.  Measured flood
+// launches (us) at 1, 2, 4, 8, 16, 32 rows:
+//   128^2 x 2     3.9   4.5   5.6   7.7  12.2   21
+//   512^2         6.1   6.1   6.9   8.2  12.6   22
+//   1531 x 977   19.1  16.0  15.4  17.7  19.0   24
+//   2048^2         43    33    30    31    33   39
+//   6 x 2048^2    365   273   223   200   193  201
+//   8192^2        663   509   480   423   417  442
+// (before: 16 rows at 2048^2, 64 at 8192^2, never fewer than 4).
+int fv_rows_per_wave(const fps_grid_desc* d, int S)
+{
+    constexpr int64_t kMinWaves = 6000;     // about the waves that fit the chip at 7 per SIMD
+    for (int H = 16; H > 1; H >>= 1) {
+        int64_t tiles = 0;
+        for (int k = 0; k < S; ++k) tiles += fv_tiles(d[k].nx, d[k].ny, H);
+        if (tiles >= kMinWaves) return H;
+    }
+    return 1;
 }
 
 hipError_t prepare_finalize(int lds_bytes)

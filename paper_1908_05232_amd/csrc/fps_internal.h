@@ -34,6 +34,8 @@ constexpr int kWetStride = 32;         // ints between flags (one 128-byte line 
 constexpr int kMaxDoor = 16;           // entrance doors of the pre-flood flow
 constexpr int kCodeDest = 16;          // destinations whose direction codes are kept (more: read the distances)
 constexpr int kChunkBins = 4096;       // bins per block of the multi-block bin scan (256 threads x 16)
+constexpr int kRedMin = 8192;          // flood partials the end-of-step block reads in one round (8 a thread)
+constexpr int kRedTiles = 2048;        // partials of a larger grid added by one block first
 constexpr int kMbScanBins = 32768;     // scenarios with more bins scan them with many blocks
 
 // Scalars that live in device memory so that n steps run without the host.
@@ -180,12 +182,14 @@ struct Batch {
     const int* chunk_off;  // [S+1] prefix of multi-block bin-scan chunks per scenario
     int S;
     int total_tiles, total_agents, total_chunks;
+    int red_chunks;        // chunks of partials of the largest scenario that reduces them in two levels (0: none)
     int fv_blocks;         // launched flood blocks: a multiple of 8 covering total_tiles
     int fin_lds_bytes;     // dynamic LDS of the finalize launch (LDS binning)
     int s_only;            // >= 0: restrict the flood launch to one scenario (tuning)
     Scn one;               // S == 1: the scenario itself, read from the kernel arguments
     int hll;               // face flux: HLL (1) or HLLC (0), the same for every scenario
     int order2;            // the second-order (MUSCL, two-stage) variant for every scenario
+    int people;            // some scenario has (or had) evacuee counts; else they are all zero
 };
 
 // launchers (stream-ordered, no synchronisation)
@@ -193,9 +197,10 @@ int fv_blocks_for_tiles(int64_t tiles);
 int fv_tiles(int nx, int ny, int H);
 int fv_tiles2(int nx, int ny, int H);    // tiles of the second-order march (narrower strips)
 int fv_strip(bool order2);               // output columns of one wave of the march
-int fv_rows_per_wave(int nx, int ny);
+int fv_rows_per_wave(const fps_grid_desc* d, int S);   // d: the grids of a launch
 hipError_t launch_fv(const Batch& b, hipStream_t s);
 hipError_t launch_fv_scan(const Batch& b, int scenario, int ntiles, hipStream_t s);
+hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t s);   // after an update or scan: chunks of a large grid's partials
 hipError_t launch_finalize(const Batch& b, int mode, int s_first, int count, hipStream_t s);
 hipError_t prepare_finalize(int lds_bytes);   // host, outside any capture: allow that much dynamic LDS
 hipError_t launch_sync_back(const Batch& b, int64_t max_cells, hipStream_t s);
