@@ -36,6 +36,13 @@ struct Cell {
 };
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// A value used on a path that few waves take: what is computed from it stays
+// on that path (the compiler would otherwise compute it always, and select).
+__device__ __forceinline__ float rare(float x)
+{
+    asm volatile("" : "+v"(x));
+    return x;
+}
 __device__ __forceinline__ float sqrt_fast(float x) { return __builtin_amdgcn_sqrtf(x); }
 
 // Whole-wave DPP shifts (a VALU move, no LDS traffic): lane i receives lane
@@ -90,90 +97,27 @@ __device__ __forceinline__ Cell load_raw(const Src& src, const FvParams& p, int 
     return c;
 }
 
-// Hydrostatic pressure 1/2 g h^2 of a reconstructed depth.  Never contracted
-// into a neighbouring add: the flux and the bed-slope correction must use the
-// identical rounded value for still water to stay exactly at rest.
-__device__ __forceinline__ float pressure(float half_g, float h)
-{
-#pragma clang fp contract(off)
-    return half_g * h * h;
-}
-
 // One face: reconstruction, then the HLLC flux.  (un, ut) are the normal and
-// tangential velocities of each side; F0 mass, F1 normal momentum, F2
-// tangential momentum; pL / pR the pressures 1/2 g h*^2 of the reconstructed
-// depth each side sees (the bed-slope correction of the two cells).
-// Written without divergent branches: every case is evaluated and selected.
-// kHll: the tangential momentum by the HLL average of the two outer waves, in
-// the same left-anchored form as mass and normal momentum, instead of from the
-// side of the contact wave.
-template <bool kHll>
-__device__ __forceinline__ void face_flux(const FvParams& p, float hL, float unL, float utL,
-                                          float zL, float hR, float unR, float utR, float zR,
-                                          bool wall, float& F0, float& F1, float& F2,
-                                          float& pL, float& pR)
-{
-    // max(zL, zR) by compare and select: fmaxf would first quieten the two
-    // raw loaded values (bed elevations are finite, and the result is one of
-    // them either way)
-    float zf = zL > zR ? zL : zR;
-    float hl = hL - (zf - zL);
-    float hr = hR - (zf - zR);
-    hl = hl > p.eps ? hl : 0.0f;
-    hr = hr > p.eps ? hr : 0.0f;
-    pL = pressure(p.half_g, hl);
-    pR = pressure(p.half_g, hr);
-    const bool wetL = hl > 0.0f, wetR = hr > 0.0f;
-    float cL = sqrt_fast(p.g * hl), cR = sqrt_fast(p.g * hr);
-    float us = 0.5f * (unL + unR) + cL - cR;
-    float cs = 0.5f * (cL + cR) + 0.25f * (unL - unR);
-    float sL = fminf(unL - cL, us - cs);
-    float sR = fmaxf(unR + cR, us + cs);
-    // dry-bed wave speeds
-    sL = wetL ? (wetR ? sL : unL - cL) : unR - 2.0f * cR;
-    sR = wetL ? (wetR ? sR : unL + 2.0f * cL) : unR + cR;
-    float qL = hl * unL, qR = hr * unR;
-    float FL0 = qL, FL1 = qL * unL + pL, FL2 = qL * utL;
-    float FR0 = qR, FR1 = qR * unR + pR, FR2 = qR * utR;
-    // HLL written from the left flux with the wave speeds clamped to either
-    // side of zero: the one formula is the left flux exactly when sL >= 0
-    // (the clamped sL is 0), the right flux up to rounding when sR <= 0, and
-    // the star-region flux between, with no selection of the case; identical
-    // states give F exactly.  Only a face dry on both sides has a zero
-    // denominator, and its flux is set to zero below.
-    const float sLc = fminf(sL, 0.0f), sRc = fmaxf(sR, 0.0f);
-    float inv = rcp(sRc - sLc);
-    float H0 = FL0 + sLc * ((FL0 - FR0) + sRc * (hr - hl)) * inv;
-    float H1 = FL1 + sLc * ((FL1 - FR1) + sRc * (qR - qL)) * inv;
-    float H2;
-    if (kHll) {
-        H2 = FL2 + sLc * ((FL2 - FR2) + sRc * (hr * utR - hl * utL)) * inv;
-    } else {
-        // tangential momentum from the side of the contact wave: s_M = num /
-        // den with den < 0 here, so s_M >= 0 iff num <= 0 (the left state for
-        // sL >= 0, the right one for sR <= 0)
-        float num = sL * hr * (unR - sR) - sR * hl * (unL - sL);
-        H2 = H0 * (num <= 0.0f ? utL : utR);
-    }
-    const bool none = !(wetL || wetR);
-    F0 = (none || wall) ? 0.0f : H0;
-    F1 = none ? 0.0f : H1;
-    F2 = (none || wall) ? 0.0f : H2;
-}
-
-// The same face for the first-order march, with every fused multiply-add
-// written out (each instantiation and each row rounds alike) and what the
-// general form spends on selections left out:
+// tangential velocities of each side; F0 mass, F2 tangential momentum; GL / GR
+// the normal momentum flux less the pressure 1/2 g h*^2 of the reconstructed
+// depth on that side (what the cell on that side receives, with the bed-slope
+// correction).  Written without divergent branches: every case is evaluated
+// and selected, and every fused multiply-add is written out, so that each
+// instantiation rounds alike.  HLL is written from the left flux with the wave
+// speeds clamped to either side of zero: the one formula is the left flux
+// exactly when sL >= 0, the right flux up to rounding when sR <= 0, and the
+// star-region flux between; identical states give F exactly, and still water
+// F1 = pL = pR.  What a straightforward form would spend on selections is left
+// out:
 //  - z_f - z_L and z_f - z_R are the positive and the negative part of the
 //    bed step;
 //  - a face dry on both sides has zero depths, discharges and pressures, so
 //    only its denominator needs a guard, not its fluxes;
 //  - the contact speed has the sign of the HLL mass flux, whose numerator is
-//    sR hL (uL - sL) - sL hR (uR - sR), so F0 selects the tangential velocity.
-// GL / GR: the normal momentum flux less the pressure of the reconstructed
-// depth on that side (what the cell on that side receives).  kProd: the right
-// side's normal velocity is the product rR * qR, which enters the sums with
-// it unrounded.
+//    sR hL (uL - sL) - sL hR (uR - sR), so F0 selects the tangential velocity
+//    (kHll: the tangential momentum by the HLL average instead).
+// kProd: the right side's normal velocity is the product rR * qR, which
+// enters the sums with it unrounded.
 template <bool kHll, bool kProd>
 __device__ __forceinline__ void face_march(const FvParams& p, float hL, float unL, float utL, float zL, float hR,
                                            float unR, float utR, float zR, float rR, float qR, bool wall,
@@ -213,6 +157,84 @@ __device__ __forceinline__ void face_march(const FvParams& p, float hL, float un
     } else {
         F2 = F0 * (F0 >= 0.0f ? utL : utR);
     }
+}
+
+// The face of the second-order march in fewer instructions still:
+//  - with the Riemann invariants a = uL + 2 cL and b = uR - 2 cR the two-
+//    rarefaction wave speeds u* -+ c* are b + (a - b) / 4 and a - (a - b) / 4;
+//  - a dry side takes the velocity of the front that the wet side sends into
+//    it (a, or b), and the wet formulas then give the dry-bed speeds (its
+//    depth, celerity and discharge are zero, so it enters nothing else).
+// About 50 instructions against 66; the rounding is another (the first-order
+// march keeps the form whose results its runs have always had).
+template <bool kHll>
+__device__ __forceinline__ void face_lean(const FvParams& p, float hL, float unL, float utL, float zL, float hR,
+                                          float unR, float utR, float zR, bool wall, float& F0, float& GL,
+                                          float& GR, float& F2)
+{
+#pragma clang fp contract(off)
+    const float dz = zR - zL;
+    float hl = hL - fmaxf(dz, 0.0f);
+    float hr = hR + fminf(dz, 0.0f);
+    const bool wetL = hl > p.eps, wetR = hr > p.eps;
+    hl = wetL ? hl : 0.0f;
+    hr = wetR ? hr : 0.0f;
+    const float pL = p.half_g * hl * hl, pR = p.half_g * hr * hr;
+    const float cL = sqrt_fast(p.g * hl), cR = sqrt_fast(p.g * hr);
+    const float uL = wetL ? unL : fmaf(-2.0f, cR, unR);
+    const float uR = wetR ? unR : fmaf(2.0f, cL, unL);
+    const float a = fmaf(2.0f, cL, uL), b = fmaf(-2.0f, cR, uR);
+    const float d = a - b;
+    const float sL = fminf(fminf(uL - cL, fmaf(0.25f, d, b)), 0.0f);
+    const float sR = fmaxf(fmaxf(uR + cR, fmaf(-0.25f, d, a)), 0.0f);
+    const float qL = hl * uL, qR = hr * uR;
+    const float ML = fmaf(qL, uL, pL), MR = fmaf(qR, uR, pR);
+    const float k = sL * rcp(fmaxf(sR - sL, 1e-30f));
+    const float H0 = fmaf(k, fmaf(sR, hr - hl, qL - qR), qL);
+    const float F1 = fmaf(k, fmaf(sR, qR - qL, ML - MR), ML);
+    F0 = wall ? 0.0f : H0;
+    GL = F1 - pL;
+    GR = F1 - pR;
+    if (kHll) {
+        const float tL = qL * utL, tR = qR * utR;
+        const float H2 = fmaf(k, fmaf(sR, hr * utR - hl * utL, tL - tR), tL);
+        F2 = wall ? 0.0f : H2;
+    } else {
+        F2 = F0 * (F0 >= 0.0f ? utL : utR);
+    }
+}
+
+// g n^2 of a cell with npc evacuees
+__device__ __forceinline__ float counted_friction(const FvParams& p, int npc)
+{
+#pragma clang fp contract(off)
+    const float n = fmaf(p.n_base, (float)min(npc, p.np_cap), p.n_base);
+    return n * (p.g * n);
+}
+
+// Manning friction of a wet cell (kn = g n^2), splitting point-implicit with a
+// no-reversal limiter, on the discharges; u, v become the new velocities.
+// Still water: the guard keeps every factor finite, and nothing is taken off.
+__device__ __forceinline__ void friction(const FvParams& p, float dt, float kn, float hn, float& qx, float& qy,
+                                         float& u, float& v)
+{
+#pragma clang fp contract(off)
+    const float r = rcp(hn);
+    u = qx * r;
+    v = qy * r;
+    const float uu = u * u, vv = v * v;
+    const float speed = sqrt_fast(fmaxf(fmaf(u, u, vv), 1e-36f));
+    const float Cf = kn * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(hn) * (-1.0f / 3.0f));
+    const float Sx = u * -Cf * speed, Sy = v * -Cf * speed;
+    const float a = dt * Cf * r * rcp(speed);
+    const float Dx = fmaf(fmaf(u, u + u, vv), a, 1.0f), Dy = fmaf(fmaf(v, v + v, uu), a, 1.0f);
+    float dqx = dt * Sx * rcp(Dx), dqy = dt * Sy * rcp(Dy);
+    if (fabsf(dqx) > fabsf(qx)) dqx = -qx;
+    if (fabsf(dqy) > fabsf(qy)) dqy = -qy;
+    qx += dqx;
+    qy += dqy;
+    u = qx * r;
+    v = qy * r;
 }
 
 // Wave reductions by DPP lane moves (VALU only, no LDS round trips): pairs,
@@ -327,7 +349,8 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
     FPS_GLOBAL float* __restrict__ qxo = gmem(cur ? p.qx[0] : p.qx[1]);
     FPS_GLOBAL float* __restrict__ qyo = gmem(cur ? p.qy[0] : p.qy[1]);
     const FPS_GLOBAL int32_t* __restrict__ npp = gmem(p.np);
-    double m_acc = 0.0, vout_acc = 0.0, vclip_acc = 0.0;
+    // mass, boundary fluxes through the x and y sides, clipped depth
+    double m_acc = 0.0, vx_acc = 0.0, vy_acc = 0.0, vclip_acc = 0.0;
     float smax = 0.0f;
     const float dt = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->dt)));
     const float inc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->inc)));
@@ -423,33 +446,12 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
                 }
                 // non-negative depth, no discharge on dry cells
                 if (hn < 0.0f) {
-                    asm volatile("");      // a branch (rare), not a sum selected afterwards
-                    vclip_acc += (double)(-hn);
+                    vclip_acc -= (double)rare(hn);
                     hn = 0.0f;
                 }
                 if (hn > p.eps) {
-                    // Manning friction, splitting point-implicit (still water: the
-                    // guard keeps a finite, and nothing is taken off)
-                    const float r = rcp(hn);
-                    float u = qxn * r, v = qyn * r;
-                    const float uu = u * u, vv = v * v;
-                    const float speed = sqrt_fast(fmaxf(fmaf(u, u, vv), 1e-36f));
-                    float kn = kn0;
-                    if (kPeople) {
-                        const float n_ = fmaf(p.n_base, (float)min(npc, p.np_cap), p.n_base);
-                        kn = n_ * (p.g * n_);
-                    }
-                    const float Cf = kn * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(hn) * (-1.0f / 3.0f));
-                    const float Sx = u * -Cf * speed, Sy = v * -Cf * speed;
-                    const float a = dt * Cf * r * rcp(speed);
-                    const float Dx = fmaf(fmaf(u, u + u, vv), a, 1.0f), Dy = fmaf(fmaf(v, v + v, uu), a, 1.0f);
-                    float dqx = dt * Sx * rcp(Dx), dqy = dt * Sy * rcp(Dy);
-                    if (fabsf(dqx) > fabsf(qxn)) dqx = -qxn;
-                    if (fabsf(dqy) > fabsf(qyn)) dqy = -qyn;
-                    qxn += dqx;
-                    qyn += dqy;
-                    u = qxn * r;
-                    v = qyn * r;
+                    float u, v;
+                    friction(p, dt, kPeople ? counted_friction(p, npc) : kn0, hn, qxn, qyn, u, v);
                     const float cel = sqrt_fast(p.g * hn);
                     umax = max(umax, __builtin_bit_cast(unsigned, fabsf(u) + cel));
                     vmax = max(vmax, __builtin_bit_cast(unsigned, fabsf(v) + cel));
@@ -460,11 +462,10 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
                 m_acc += (double)hn;
                 // outflow through transmissive sides
                 if (out_w || out_e || j == out_s || j == out_n) {
-                    asm volatile("");      // skipped by most waves
-                    if (out_w && i == 0) vout_acc -= (double)Fw0 * dt * p.dy;
-                    if (out_e && i == p.nx - 1) vout_acc += (double)Fe0 * dt * p.dy;
-                    if (j == out_s) vout_acc -= (double)s.F0 * dt * p.dx;
-                    if (j == out_n) vout_acc += (double)n.F0 * dt * p.dx;
+                    if (out_w && i == 0) vx_acc -= (double)rare(Fw0);
+                    if (out_e && i == p.nx - 1) vx_acc += (double)rare(Fe0);
+                    if (j == out_s) vy_acc -= (double)rare(s.F0);
+                    if (j == out_n) vy_acc += (double)rare(n.F0);
                 }
                 st_at(ho, k, hn);
                 st_at(qxo, k, qxn);
@@ -512,6 +513,7 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
     // on transmissive sides, clipping only where a depth went negative): their
     // sums are skipped when no lane holds a non-zero value.
     m_acc = wave_sum(m_acc);
+    double vout_acc = (double)dt * (vx_acc * p.dy + vy_acc * p.dx);
     if (__ballot(vout_acc != 0.0)) vout_acc = wave_sum(vout_acc);
     else vout_acc = 0.0;
     if (__ballot(vclip_acc != 0.0)) vclip_acc = wave_sum(vclip_acc);
@@ -558,65 +560,25 @@ struct V4 {
     float h, eta, u, v;     // depth, surface elevation, velocities (0 where h <= h_dry)
 };
 
-__device__ __forceinline__ float minmod(float a, float b)
+// minmod: the median of the two differences and zero
+__device__ __forceinline__ float minmod(float a, float b) { return __builtin_amdgcn_fmed3f(a, b, 0.0f); }
+
+__device__ __forceinline__ V4 operator-(const V4& a, const V4& b)
 {
-    return a * b > 0.0f ? (fabsf(a) <= fabsf(b) ? a : b) : 0.0f;
+    return V4{a.h - b.h, a.eta - b.eta, a.u - b.u, a.v - b.v};
 }
 
-// the velocities and surface of a raw cell (a ghost mirrors the adjacent
-// interior cell: the normal velocity negated at a wall)
-__device__ __forceinline__ V4 v4_of(const FvParams& p, const Cell& c, bool mirror_x, int j)
+// cell c reconstructed at its two faces in one direction from the differences
+// f (to the next cell) and g (from the cell before); half: 1/2, or 0 for a
+// ghost or next to a dry cell (no slope).  Returns the change of the surface
+// across the cell.  A face value lies between the cell's and its mean with a
+// neighbour, so a face is dry only where the cell is, and its velocity is then 0.
+__device__ __forceinline__ float recon(const V4& c, const V4& f, const V4& g, float half, V4& lo, V4& hi)
 {
-    V4 v;
-    v.h = c.h;
-    v.eta = c.h + c.z;
-    const float r = c.h > p.eps ? rcp(c.h) : 0.0f;
-    v.u = c.qx * r;
-    v.v = c.qy * r;
-    if (mirror_x) v.u = -v.u;
-    if ((j < 0 && p.bc[2] == FPS_BC_WALL) || (j >= p.ny && p.bc[3] == FPS_BC_WALL)) v.v = -v.v;
-    return v;
-}
-
-// cell b reconstructed at its two faces in one direction, from its
-// neighbours a (before) and c (after): lo at the face towards a, hi at the
-// face towards c; no slope for a ghost or next to a dry cell
-__device__ __forceinline__ void recon(const FvParams& p, const V4& a, const V4& b, const V4& c, bool ghost,
-                                      V4& lo, V4& hi)
-{
-    lo = b;
-    hi = b;
-    if (ghost || !(a.h > p.eps) || !(b.h > p.eps) || !(c.h > p.eps)) return;
-    const float mh = minmod(c.h - b.h, b.h - a.h), me = minmod(c.eta - b.eta, b.eta - a.eta);
-    const float mu = minmod(c.u - b.u, b.u - a.u), mv = minmod(c.v - b.v, b.v - a.v);
-    hi.h += 0.5f * mh;
-    hi.eta += 0.5f * me;
-    hi.u += 0.5f * mu;
-    hi.v += 0.5f * mv;
-    lo.h += -0.5f * mh;
-    lo.eta += -0.5f * me;
-    lo.u += -0.5f * mu;
-    lo.v += -0.5f * mv;
-}
-
-// one face between reconstructed states L and R in the face's normal
-// direction (un, ut: normal and tangential velocity): flux and, per side, the
-// hydrostatic depth
-template <bool kHll>
-__device__ __forceinline__ void face2(const FvParams& p, float hL, float etaL, float unL, float utL, float hR,
-                                      float etaR, float unR, float utR, bool wall, float& F0, float& F1,
-                                      float& F2, float& hsL, float& hsR)
-{
-    const float zL = etaL - hL, zR = etaR - hR;
-    const bool wL = hL > p.eps, wR = hR > p.eps;
-    float pL, pR;
-    face_flux<kHll>(p, hL, wL ? unL : 0.0f, wL ? utL : 0.0f, zL, hR, wR ? unR : 0.0f, wR ? utR : 0.0f, zR, wall,
-                    F0, F1, F2, pL, pR);
-    // the hydrostatic depths themselves (the pressures are their squares)
-    const float zf = zL > zR ? zL : zR;
-    const float hl = hL - (zf - zL), hr = hR - (zf - zR);
-    hsL = hl > p.eps ? hl : 0.0f;
-    hsR = hr > p.eps ? hr : 0.0f;
+    const V4 m{minmod(f.h, g.h), minmod(f.eta, g.eta), minmod(f.u, g.u), minmod(f.v, g.v)};
+    lo = V4{fmaf(-half, m.h, c.h), fmaf(-half, m.eta, c.eta), fmaf(-half, m.u, c.u), fmaf(-half, m.v, c.v)};
+    hi = V4{fmaf(half, m.h, c.h), fmaf(half, m.eta, c.eta), fmaf(half, m.u, c.u), fmaf(half, m.v, c.v)};
+    return (half + half) * m.eta;
 }
 
 // One Runge-Kutta stage of the second-order variant over one tile (kStage 1:
@@ -624,7 +586,21 @@ __device__ __forceinline__ void face2(const FvParams& p, float hL, float etaL, f
 // / 2 into the other ping-pong buffer, then inflow, friction, volumes and the
 // wave speed).  The outflow and clipped volumes of stage 1 are left in the
 // tile's partial slots for stage 2 to add to (each stage counts half).
-template <bool kOne, bool kHll, int kStage>
+//
+// The bed slope: a face gives its cell G + 1/2 g h_f^2 (G the momentum flux
+// less 1/2 g h*^2), the centred term 1/2 g (h_w + h_e)(z_e - z_w); the squares
+// and that term are together 1/2 g (h_w + h_e)(eta_e - eta_w), and h_w + h_e is
+// twice the cell's depth, so a cell receives G_e - G_w + g h (eta_e - eta_w):
+// one multiply-add, and nothing where the surface is level.
+//
+// What bounds it: VALU issue up to a few million cells, HBM (72 B a cell over
+// the two stages) beyond.  Before this form (general faces and limiter, window
+// and carried faces moved along every row, one row of U^n loaded where it is
+// used) both stages took 122 us at 2048^2 and 16 rows a wave; now 70 us at 8
+// rows, and 943 us at 8192^2 (5.1 TB/s).  It holds 96 VGPRs in stage 1 and 115
+// in stage 2 (5 and 4 waves per SIMD); the scheduling barriers keep the two
+// faces of a row from being interleaved, which would take 123.
+template <bool kOne, bool kHll, bool kPeople, int kStage>
 __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
 {
     const int lane = threadIdx.x & (kWave - 1);
@@ -651,6 +627,10 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
                  gmem<const float>(cur ? p.qy[1] : p.qy[0]), gmem(p.z)};
     const Src s1{gmem<const float>(p.h1), gmem<const float>(p.qx1), gmem<const float>(p.qy1), gmem(p.z)};
     const Src& src = kStage == 1 ? s0 : s1;        // the state the residual is taken of
+    FPS_GLOBAL float* __restrict__ ho = gmem(kStage == 1 ? p.h1 : cur ? p.h[0] : p.h[1]);
+    FPS_GLOBAL float* __restrict__ qxo = gmem(kStage == 1 ? p.qx1 : cur ? p.qx[0] : p.qx[1]);
+    FPS_GLOBAL float* __restrict__ qyo = gmem(kStage == 1 ? p.qy1 : cur ? p.qy[0] : p.qy[1]);
+    const FPS_GLOBAL int32_t* __restrict__ npp = gmem(p.np);
     const float dt = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->dt)));
     const float inc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->inc)));
     const float lx = dt * p.inv_dx, ly = dt * p.inv_dy;
@@ -663,150 +643,205 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
     const bool mirror_x = (i < 0 && p.bc[0] == FPS_BC_WALL) || (i >= p.nx && p.bc[1] == FPS_BC_WALL);
     // the west face of this lane's column is a wall face
     const bool xwall = (i == 0 && p.bc[0] == FPS_BC_WALL) || (i == p.nx && p.bc[1] == FPS_BC_WALL);
-    double m_acc = 0.0, vout_acc = 0.0, vclip_acc = 0.0;
-    float smax = 0.0f;
+    // what only the strips on the west and east sides do (wave-uniform); the
+    // last strip may hold only the ghosts of the east side, so it is the one
+    // whose lanes reach it
+    const bool first_strip = sx == 0, last_strip = sx * kStrip2 + kStrip2 >= p.nx;
+    const bool out_w = first_strip && p.bc[0] == FPS_BC_TRANSMISSIVE, out_e = last_strip && p.bc[1] == FPS_BC_TRANSMISSIVE;
+    const int out_s = p.bc[2] == FPS_BC_TRANSMISSIVE ? 0 : -1, out_n = p.bc[3] == FPS_BC_TRANSMISSIVE ? p.ny - 1 : -1;
+    const bool inflow_x = (p.inflow_side == FPS_SIDE_W && first_strip) || (p.inflow_side == FPS_SIDE_E && last_strip);
+    const int in_row = p.inflow_side == FPS_SIDE_S ? 0 : p.inflow_side == FPS_SIDE_N ? p.ny - 1 : -1;
+    const int in_col = p.inflow_side == FPS_SIDE_W ? 0 : p.nx - 1;
+    const float kn0 = p.n_base * (p.g * p.n_base);
+    // mass, boundary fluxes through the x and y sides, clipped depth
+    double m_acc = 0.0, vx_acc = 0.0, vy_acc = 0.0, vclip_acc = 0.0;
+    unsigned umax = 0, vmax = 0;     // largest |u| + c and |v| + c of the lane's cells, as bits
     FPS_GLOBAL double* part = gmem(&p.partials[4 * tile]);
 
-    // window: rows r - 1, r, r + 1 (raw and derived), two rows in flight
-    Cell cm = load_raw(src, p, ii, j0 - 2), c0 = load_raw(src, p, ii, j0 - 1), cp = load_raw(src, p, ii, j0);
-    Cell pf0 = load_raw(src, p, ii, j0 + 1), pf1 = load_raw(src, p, ii, j0 + 2);
-    V4 vm = v4_of(p, cm, mirror_x, j0 - 2), v0 = v4_of(p, c0, mirror_x, j0 - 1), vp = v4_of(p, cp, mirror_x, j0);
-    // carried from row r - 1: its north state, and its residual but the north face
-    V4 nprev = {};
-    Cell crow = {};                                // raw values of row r - 1 (the stage's base)
-    float Fs0 = 0.0f, Fs1 = 0.0f, Fs2 = 0.0f, hsS = 0.0f, hS = 0.0f, zS = 0.0f, hN = 0.0f, zN = 0.0f;
-    float ex0 = 0.0f, ex1 = 0.0f, ex2 = 0.0f, cx = 0.0f;
-    double rate_x = 0.0;                           // outflow rate through the row's x boundary faces
-    for (int r = j0 - 1; r <= j1; ++r) {
-        // y reconstruction of row r from the window (rows r - 1, r, r + 1)
-        V4 sr, nr;
-        recon(p, vm, v0, vp, r < 0 || r >= p.ny, sr, nr);
-        if (r >= j0) {
-            // the face below row r: north state of row r - 1 against the south state of row r
-            float F0, F1, F2, hsl, hsr;
-            face2<kHll>(p, nprev.h, nprev.eta, nprev.v, nprev.u, sr.h, sr.eta, sr.v, sr.u,
-                        (r == 0 && p.bc[2] == FPS_BC_WALL) || (r == p.ny && p.bc[3] == FPS_BC_WALL), F0, F1,
-                        F2, hsl, hsr);
-            if (r > j0) {
-                // row r - 1 is complete: its north face is this one
-                const int jr = r - 1;
-                const float cy = p.half_g * (hN * hN - hsl * hsl) - p.half_g * (hS * hS - hsS * hsS) +
-                                 p.half_g * (hS + hN) * (zN - zS);
-                const float dh = -(lx * ex0 + ly * (F0 - Fs0));
-                const float dqx = -(lx * (ex1 + cx) + ly * (F2 - Fs2));
-                const float dqy = -(ly * ((F1 - Fs1) + cy) + lx * ex2);
-                if (out_lane) {
-                    const uint32_t k = (uint32_t)jr * (uint32_t)p.nx + (uint32_t)i;
-                    double rate = rate_x;
-                    if (jr == 0 && p.bc[2] == FPS_BC_TRANSMISSIVE) rate -= (double)Fs0 * p.dx;
-                    if (jr == p.ny - 1 && p.bc[3] == FPS_BC_TRANSMISSIVE) rate += (double)F0 * p.dx;
-                    vout_acc += 0.5 * rate * (double)dt;
-                    float h = crow.h + dh, qx = crow.qx + dqx, qy = crow.qy + dqy;
-                    if (h < 0.0f) {
-                        vclip_acc += 0.5 * (double)(-h);
-                        h = 0.0f;
+    // a row of cells: surface and velocities, the raw discharges, and which lanes are wet
+    struct Row {
+        V4 v;
+        float qx, qy;
+        unsigned long long wet;
+    };
+    auto derive = [&](const Cell& raw, int j) {
+        Row c;
+        const bool wet = raw.h > p.eps;
+        const float r = wet ? rcp(raw.h) : 0.0f;
+        c.qx = raw.qx;
+        c.qy = raw.qy;
+        c.v.h = raw.h;
+        c.v.eta = raw.h + raw.z;
+        c.v.u = raw.qx * r;
+        c.v.v = raw.qy * r;
+        if (mirror_x) c.v.u = -c.v.u;
+        if ((j < 0 && p.bc[2] == FPS_BC_WALL) || (j >= p.ny && p.bc[3] == FPS_BC_WALL)) c.v.v = -c.v.v;
+        c.wet = __ballot(wet);
+        return c;
+    };
+    // what a row hands to the one above: its north face state, and its cells'
+    // change but the north face's part with the values it applies to
+    struct Up {
+        V4 n;
+        float ih, iqx, iqy, h, qx, qy;
+        float bh, bqx, bqy;      // stage 2: the state at the start of the step
+    };
+
+    // Row r (c; the row above it nb), the differences gy from the row below
+    // and its wetness wb; lower: what row r - 1 hands up.  Forms the face below
+    // row r (first: none below the tile's halo row), completes row r - 1
+    // (done) and starts row r (start), leaving up and the differences fy.
+    auto row = [&](const Row& c, const Row& nb, const V4& gy, unsigned long long wb, int r, const Up& lower, Up& up,
+                   V4& fy, auto face_, auto done_, auto start_) {
+#pragma clang fp contract(off)
+        constexpr bool face = decltype(face_)::value, done = decltype(done_)::value, start = decltype(start_)::value;
+        fy = nb.v - c.v;
+        const bool inside = r >= 0 && r < p.ny;      // a ghost row has no slope
+        const unsigned long long wy = inside ? wb & c.wet & nb.wet : 0ull;
+        V4 sr;
+        const float ey = recon(c.v, fy, gy, __builtin_amdgcn_inverse_ballot_w64(wy) ? 0.5f : 0.0f, sr, up.n);
+        float F0 = 0.0f, GL = 0.0f, GR = 0.0f, F2 = 0.0f;
+        if (face)
+            face_lean<kHll>(p, lower.n.h, lower.n.v, lower.n.u, lower.n.eta - lower.n.h, sr.h, sr.v, sr.u,
+                            sr.eta - sr.h, (r == 0 && p.bc[2] == FPS_BC_WALL) || (r == p.ny && p.bc[3] == FPS_BC_WALL),
+                            F0, GL, GR, F2);
+        __builtin_amdgcn_sched_barrier(0);
+        if (done) {
+            // row r - 1 is complete: its north face is this one
+            const int jr = r - 1;
+            if (out_lane) {
+                const uint32_t k = (uint32_t)jr * (uint32_t)p.nx + (uint32_t)i;
+                if (jr == out_n) vy_acc += (double)rare(F0);
+                float h = lower.h - fmaf(ly, F0, lower.ih), qx = lower.qx - fmaf(ly, F2, lower.iqx),
+                      qy = lower.qy - fmaf(ly, GL, lower.iqy);
+                if (h < 0.0f) {
+                    vclip_acc -= (double)rare(h);
+                    h = 0.0f;
+                }
+                if (!(h > p.eps)) {
+                    qx = 0.0f;
+                    qy = 0.0f;
+                }
+                if (kStage == 2) {
+                    h = 0.5f * (lower.bh + h);
+                    qx = 0.5f * (lower.bqx + qx);
+                    qy = 0.5f * (lower.bqy + qy);
+                    if (jr == in_row) {
+                        if (i >= p.c0 && i < p.c1) h += inc;
+                    } else if (inflow_x && jr >= p.c0 && jr < p.c1) {
+                        if (i == in_col) h += inc;
                     }
-                    if (!(h > p.eps)) {
+                    if (h > p.eps) {
+                        float u, v;
+                        friction(p, dt, kPeople ? counted_friction(p, ld(npp, k)) : kn0, h, qx, qy, u, v);
+                        const float cel = sqrt_fast(p.g * h);
+                        umax = max(umax, __builtin_bit_cast(unsigned, fabsf(u) + cel));
+                        vmax = max(vmax, __builtin_bit_cast(unsigned, fabsf(v) + cel));
+                    } else {
                         qx = 0.0f;
                         qy = 0.0f;
                     }
-                    if (kStage == 1) {
-                        st_at(gmem(p.h1), k, h);
-                        st_at(gmem(p.qx1), k, qx);
-                        st_at(gmem(p.qy1), k, qy);
-                    } else {
-                        float hn = 0.5f * (ld(s0.h, k) + h), qxn = 0.5f * (ld(s0.qx, k) + qx),
-                              qyn = 0.5f * (ld(s0.qy, k) + qy);
-                        bool inflow = false;
-                        if (p.inflow_side == FPS_SIDE_S) inflow = jr == 0 && i >= p.c0 && i < p.c1;
-                        else if (p.inflow_side == FPS_SIDE_N) inflow = jr == p.ny - 1 && i >= p.c0 && i < p.c1;
-                        else if (p.inflow_side == FPS_SIDE_W) inflow = i == 0 && jr >= p.c0 && jr < p.c1;
-                        else if (p.inflow_side == FPS_SIDE_E) inflow = i == p.nx - 1 && jr >= p.c0 && jr < p.c1;
-                        if (inflow) hn += inc;
-                        if (!(hn > p.eps)) {
-                            qxn = 0.0f;
-                            qyn = 0.0f;
-                        }
-                        if (hn > p.eps) {
-                            const float rr = rcp(hn);
-                            float u = qxn * rr, v = qyn * rr;
-                            const float V2 = u * u + v * v;
-                            if (V2 > 0.0f) {
-                                // Manning friction, splitting point-implicit (as in the first-order update)
-                                const int npc = ld(gmem<const int32_t>(p.np), k);
-                                const float n = p.n_base + (float)min(npc, p.np_cap) * p.n_base;
-                                const float speed = sqrt_fast(V2);
-                                const float hm13 = __builtin_amdgcn_exp2f(-__builtin_amdgcn_logf(hn) * (1.0f / 3.0f));
-                                const float Cf = p.g * n * n * hm13;
-                                const float Sx = -Cf * u * speed, Sy = -Cf * v * speed;
-                                const float a = dt * Cf * rr * rcp(speed);
-                                const float Dx = 1.0f + a * (2.0f * u * u + v * v);
-                                const float Dy = 1.0f + a * (2.0f * v * v + u * u);
-                                float dfx = dt * Sx * rcp(Dx), dfy = dt * Sy * rcp(Dy);
-                                if (fabsf(dfx) > fabsf(qxn)) dfx = -qxn;
-                                if (fabsf(dfy) > fabsf(qyn)) dfy = -qyn;
-                                qxn += dfx;
-                                qyn += dfy;
-                                u = qxn * rr;
-                                v = qyn * rr;
-                            }
-                            const float cel = sqrt_fast(p.g * hn);
-                            smax = fmaxf(smax, fmaxf((fabsf(u) + cel) * p.inv_dx, (fabsf(v) + cel) * p.inv_dy));
-                        }
-                        m_acc += (double)hn;
-                        st_at(gmem(cur ? p.h[0] : p.h[1]), k, hn);
-                        st_at(gmem(cur ? p.qx[0] : p.qx[1]), k, qxn);
-                        st_at(gmem(cur ? p.qy[0] : p.qy[1]), k, qyn);
-                    }
+                    m_acc += (double)h;
                 }
+                st_at(ho, k, h);
+                st_at(qxo, k, qx);
+                st_at(qyo, k, qy);
             }
-            Fs0 = F0;
-            Fs1 = F1;
-            Fs2 = F2;
-            hsS = hsr;
         }
-        if (r >= j0 && r < j1) {
-            // x reconstruction of row r from the neighbour lanes, its west face,
-            // and its east face from the lane above
-            const V4 w{lane_from_below(v0.h), lane_from_below(v0.eta), lane_from_below(v0.u), lane_from_below(v0.v)};
-            const V4 e{lane_from_above(v0.h), lane_from_above(v0.eta), lane_from_above(v0.u), lane_from_above(v0.v)};
+        __builtin_amdgcn_sched_barrier(0);
+        if (start) {
+            if (kStage == 2) {
+                // the state at the start of the step, used when the row is complete
+                const uint32_t k = (uint32_t)r * (uint32_t)p.nx + (uint32_t)ii;
+                up.bh = ld(s0.h, k);
+                up.bqx = ld(s0.qx, k);
+                up.bqy = ld(s0.qy, k);
+            }
+            // x reconstruction from the neighbour lanes, the west face, and the
+            // east face from the lane above
+            const V4 fx{lane_from_above(c.v.h) - c.v.h, lane_from_above(c.v.eta) - c.v.eta,
+                        lane_from_above(c.v.u) - c.v.u, lane_from_above(c.v.v) - c.v.v};
+            const V4 gw{lane_from_below(fx.h), lane_from_below(fx.eta), lane_from_below(fx.u), lane_from_below(fx.v)};
+            const unsigned long long wx = c.wet & (c.wet >> 1) & (c.wet << 1);
             V4 wr, er;
-            recon(p, w, v0, e, gx, wr, er);
+            const float ex = recon(c.v, fx, gw, __builtin_amdgcn_inverse_ballot_w64(wx) && !gx ? 0.5f : 0.0f, wr, er);
             const V4 el{lane_from_below(er.h), lane_from_below(er.eta), lane_from_below(er.u), lane_from_below(er.v)};
-            float Fw0, Fw1, Fw2, hsw_l, hsw_r;
-            face2<kHll>(p, el.h, el.eta, el.u, el.v, wr.h, wr.eta, wr.u, wr.v, xwall, Fw0, Fw1, Fw2, hsw_l, hsw_r);
-            const float Fe0 = lane_from_above(Fw0), Fe1 = lane_from_above(Fw1), Fe2 = lane_from_above(Fw2);
-            const float hsE = lane_from_above(hsw_l);
-            const float zW = wr.eta - wr.h, zE = er.eta - er.h;
-            cx = p.half_g * (er.h * er.h - hsE * hsE) - p.half_g * (wr.h * wr.h - hsw_r * hsw_r) +
-                 p.half_g * (wr.h + er.h) * (zE - zW);
-            ex0 = Fe0 - Fw0;
-            ex1 = Fe1 - Fw1;
-            ex2 = Fe2 - Fw2;
-            rate_x = 0.0;
-            if (i == 0 && p.bc[0] == FPS_BC_TRANSMISSIVE) rate_x -= (double)Fw0 * p.dy;
-            if (i == p.nx - 1 && p.bc[1] == FPS_BC_TRANSMISSIVE) rate_x += (double)Fe0 * p.dy;
-            hS = sr.h;
-            zS = sr.eta - sr.h;
-            hN = nr.h;
-            zN = nr.eta - nr.h;
-            crow = c0;
+            float Fw0, GwL, GwR, Fw2;
+            face_lean<kHll>(p, el.h, el.u, el.v, el.eta - el.h, wr.h, wr.u, wr.v, wr.eta - wr.h, xwall, Fw0, GwL, GwR,
+                            Fw2);
+            const float Fe0 = lane_from_above(Fw0), Ge = lane_from_above(GwL), Fe2 = lane_from_above(Fw2);
+            const float gh = p.g * c.v.h;
+            up.ih = fmaf(-ly, F0, lx * (Fe0 - Fw0));
+            up.iqx = fmaf(-ly, F2, lx * fmaf(gh, ex, Ge - GwR));
+            up.iqy = fmaf(ly, fmaf(gh, ey, -GR), lx * (Fe2 - Fw2));
+            up.h = c.v.h;
+            up.qx = c.qx;
+            up.qy = c.qy;
+            // outflow of the row through the west, east and south sides
+            if (out_lane) {
+                if (r == out_s) vy_acc -= (double)rare(F0);
+                if (out_w && i == 0) vx_acc -= (double)rare(Fw0);
+                if (out_e && i == p.nx - 1) vx_acc += (double)rare(Fe0);
+            }
         }
-        nprev = nr;
-        // advance the window
-        cm = c0;
-        c0 = cp;
-        cp = pf0;
-        pf0 = pf1;
-        if (r + 4 <= j1 + 1) pf1 = load_raw(src, p, ii, r + 4);     // rows past the last one needed stay unread
-        vm = v0;
-        v0 = vp;
-        vp = v4_of(p, cp, mirror_x, r + 2);
+    };
+    const std::true_type yes{};
+    const std::false_type no{};
+
+    // Rows j0 - 1 to j1 + 1 with a ring of rows in flight (rows past the last
+    // one needed are replaced by it); two rows a turn, so that the window stays
+    // where it is.
+    auto fetch = [&](int j) { return load_raw(src, p, ii, min(j, j1 + 1)); };
+    Row A, Bc;
+    Up Ua, Ub;
+    V4 fa, fb;
+    unsigned long long wl;
+    {
+        const Cell r0 = load_raw(src, p, ii, j0 - 2), r1 = load_raw(src, p, ii, j0 - 1), r2 = load_raw(src, p, ii, j0);
+        A = derive(r0, j0 - 2);
+        Bc = derive(r1, j0 - 1);
+        fb = Bc.v - A.v;
+        wl = A.wet;
+        A = derive(r2, j0);
     }
-    // the two stages' volumes in the tile's partials (stage 1 leaves its
-    // outflow and clipped volumes there for stage 2)
-    vout_acc = wave_sum(vout_acc);
-    vclip_acc = wave_sum(vclip_acc);
+    Cell R0 = fetch(j0 + 1), R1 = fetch(j0 + 2);
+    // row j0 - 1: its north state only
+    row(Bc, A, fb, wl, j0 - 1, Ub, Ua, fa, no, no, no);
+    wl = Bc.wet;
+    Bc = derive(R0, j0 + 1);
+    R0 = fetch(j0 + 3);
+    // row j0: its faces, no row below to complete
+    row(A, Bc, fa, wl, j0, Ua, Ub, fb, yes, no, yes);
+    wl = A.wet;
+    A = derive(R1, j0 + 2);
+    R1 = fetch(j0 + 4);
+    int r = j0 + 1;
+    for (; r + 2 <= j1; r += 2) {
+        row(Bc, A, fb, wl, r, Ub, Ua, fa, yes, yes, yes);
+        wl = Bc.wet;
+        Bc = derive(R0, r + 2);
+        R0 = fetch(r + 4);
+        row(A, Bc, fa, wl, r + 1, Ua, Ub, fb, yes, yes, yes);
+        wl = A.wet;
+        A = derive(R1, r + 3);
+        R1 = fetch(r + 5);
+    }
+    if (r < j1) {
+        row(Bc, A, fb, wl, r, Ub, Ua, fa, yes, yes, yes);
+        wl = Bc.wet;
+        Bc = derive(R0, r + 2);
+        row(A, Bc, fa, wl, r + 1, Ua, Ub, fb, yes, yes, no);
+    } else {
+        row(Bc, A, fb, wl, r, Ub, Ua, fa, yes, yes, no);
+    }
+    // the two stages' volumes in the tile's partials, each stage for half
+    // (stage 1 leaves its outflow and clipped volumes there for stage 2)
+    double vout_acc = 0.5 * (double)dt * (vx_acc * p.dy + vy_acc * p.dx);
+    vclip_acc *= 0.5;
+    if (__ballot(vout_acc != 0.0)) vout_acc = wave_sum(vout_acc);
+    else vout_acc = 0.0;
+    if (__ballot(vclip_acc != 0.0)) vclip_acc = wave_sum(vclip_acc);
+    else vclip_acc = 0.0;
     if (kStage == 1) {
         if (lane == 0) {
             part[1] = vout_acc;
@@ -815,7 +850,9 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
         return;
     }
     m_acc = wave_sum(m_acc);
-    smax = wave_max(smax);
+    const float su = __builtin_bit_cast(float, umax) * p.inv_dx, sv = __builtin_bit_cast(float, vmax) * p.inv_dy;
+    const float smax = wave_max(__builtin_bit_cast(
+        float, max(__builtin_bit_cast(unsigned, su), __builtin_bit_cast(unsigned, sv))));
     if (lane == 0) {
         const double vo1 = part[1], vc1 = part[2];
         part[0] = m_acc;
@@ -1240,22 +1277,18 @@ hipError_t launch_fv(const Batch& b, hipStream_t s)
 {
     if (b.fv_blocks > 0 && b.order2) {
         const dim3 grid(b.fv_blocks), block(kFvBlock);
+        const auto go = [&](auto one, auto hll) {
+            constexpr bool kOne = decltype(one)::value, kHll = decltype(hll)::value;
+            hipLaunchKernelGGL((fv2_stage_kernel<kOne, kHll, false, 1>), grid, block, 0, s, b);
+            if (b.people) hipLaunchKernelGGL((fv2_stage_kernel<kOne, kHll, true, 2>), grid, block, 0, s, b);
+            else hipLaunchKernelGGL((fv2_stage_kernel<kOne, kHll, false, 2>), grid, block, 0, s, b);
+        };
         if (b.S == 1) {
-            if (b.hll) {
-                hipLaunchKernelGGL((fv2_stage_kernel<true, true, 1>), grid, block, 0, s, b);
-                hipLaunchKernelGGL((fv2_stage_kernel<true, true, 2>), grid, block, 0, s, b);
-            } else {
-                hipLaunchKernelGGL((fv2_stage_kernel<true, false, 1>), grid, block, 0, s, b);
-                hipLaunchKernelGGL((fv2_stage_kernel<true, false, 2>), grid, block, 0, s, b);
-            }
+            if (b.hll) go(std::true_type{}, std::true_type{});
+            else go(std::true_type{}, std::false_type{});
         } else {
-            if (b.hll) {
-                hipLaunchKernelGGL((fv2_stage_kernel<false, true, 1>), grid, block, 0, s, b);
-                hipLaunchKernelGGL((fv2_stage_kernel<false, true, 2>), grid, block, 0, s, b);
-            } else {
-                hipLaunchKernelGGL((fv2_stage_kernel<false, false, 1>), grid, block, 0, s, b);
-                hipLaunchKernelGGL((fv2_stage_kernel<false, false, 2>), grid, block, 0, s, b);
-            }
+            if (b.hll) go(std::false_type{}, std::true_type{});
+            else go(std::false_type{}, std::false_type{});
         }
         return hipGetLastError();
     }
