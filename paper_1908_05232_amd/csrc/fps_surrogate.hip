@@ -9,12 +9,12 @@
 // channels (13 zero) so every layer is a whole number of 16x16x32 MFMA tiles.
 //
 // Kernels
-//   conv_kernel<CIN, COUT, MODE>: implicit GEMM, M = pixels, N = COUT,
+//   conv_kernel<CIN, COUT, MODE>: implicit GEMM, M = COUT, N = pixels,
 //     K = 9 * CIN, for the 16-channel input of the first layer (and the input
 //     gradient through the last).  A persistent block computes 16 x 32 pixel
 //     tiles; the input tile with its one-pixel halo and the whole weight
 //     matrix are staged in LDS; each of the 8 waves owns two image rows (four
-//     16-pixel M tiles) and all COUT channels, issuing
+//     16-pixel tiles) and all COUT channels, issuing
 //     v_mfma_f32_16x16x32_bf16.  Forward and input-gradient passes use the
 //     same kernel (the latter with flipped, transposed weights).
 //   conv64_kernel<COUT, MODE>: the same for 64 input channels, with compute
@@ -43,6 +43,7 @@ namespace fps_sur_impl {
 typedef __bf16 bf16;
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef short s16x8 __attribute__((ext_vector_type(8)));
 
 constexpr int TW = 32;            // columns of the output tile of one convolution block
 constexpr int CTH = 16;            // rows of the output tile of one convolution block (x TW columns)
@@ -62,6 +63,120 @@ __host__ __device__ constexpr int kp_of(int cin) { return (9 * cin + 31) / 32 * 
 
 __device__ __forceinline__ bf16 to_bf16(float f) { return (bf16)f; }
 __device__ __forceinline__ float to_f32(bf16 b) { return (float)b; }
+
+// The tile of a convolution's turn t (t = block + k * blocks).  Blocks go to
+// the 8 XCDs round-robin, each XCD has its own L2, and a tile shares its halo
+// (a sixth of its input) with its neighbours: the 32 turns that one XCD takes
+// together are given a patch of 4 x 8 tiles where the tiles of the image
+// divide into such patches, or else 32 consecutive tiles.  Turns past the last
+// full round of 256 blocks keep their order.
+struct TileAt {
+    int n, ty, tx;
+};
+__device__ __forceinline__ TileAt tile_at(int t, int ntiles, int tiles_x, int tiles_y, int blocks)
+{
+    constexpr int PY = 4, PX = 8, P = PY * PX, XCDS = 8;
+    int k = t;
+    if (blocks == XCDS * P && t < ntiles / blocks * blocks) {
+        const int turn = t / blocks, b = t % blocks;
+        k = (turn * XCDS + (b & (XCDS - 1))) * P + (b >> 3);
+    }
+    const int per = tiles_x * tiles_y;
+    const int n = k / per, r = k % per;
+    if (tiles_x % PX || tiles_y % PY) return TileAt{n, r / tiles_x, r % tiles_x};
+    const int patch = r / P, w = r % P, ppx = tiles_x / PX;
+    return TileAt{n, patch / ppx * PY + w / PX, patch % ppx * PX + w % PX};
+}
+
+// Output tiles of the convolutions.  The weights are the A operand (M = output
+// channels) and the pixels the B operand (N), so a lane's four values of a D
+// tile are four channels of one pixel, D row 4 * kgrp + r.  For 64 output
+// channels the rows of the four M tiles are assigned so that the tiles 2 h and
+// 2 h + 1 hold channels 32 h + 8 kgrp + 0..3 and + 4..7: a lane then holds
+// eight consecutive channels of a pixel and stores them (and reads the ReLU
+// mask) as 16 bytes.  out_channel: the channel of weight row `row` in LDS.
+// With the pixels as M a lane held one channel of four pixels and stored two
+// bytes at a time: 128 stores a lane and tile against 16.
+template <int COUT>
+__device__ __forceinline__ int out_channel(int row)
+{
+    if (COUT != 64) return row;
+    const int nt = row >> 4, m = row & 15;
+    return 32 * (nt >> 1) + 8 * (m >> 2) + 4 * (nt & 1) + (m & 3);
+}
+
+// The weights [COUT][KP] into LDS (row stride WST), by `threads` threads, thread
+// t: every load of a thread goes out before the first wait (a load, wait and
+// store at a time cost the 64 -> 64 layer about 6 us a launch).
+template <int COUT, int KP, int WST, int THREADS>
+__device__ __forceinline__ void stage_weights(const bf16* __restrict__ Wt, bf16* wl, int t)
+{
+    constexpr int CHUNKS = COUT * (KP / 8), PER = (CHUNKS + THREADS - 1) / THREADS;
+    bf16x8 v[PER];
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int q = min(t + u * THREADS, CHUNKS - 1);
+        v[u] = *reinterpret_cast<const bf16x8*>(Wt + (size_t)out_channel<COUT>(q / (KP / 8)) * KP + q % (KP / 8) * 8);
+    }
+#pragma unroll
+    for (int u = 0; u < PER; ++u) {
+        const int q = t + u * THREADS;
+        if (q < CHUNKS) *reinterpret_cast<bf16x8*>(wl + q / (KP / 8) * WST + q % (KP / 8) * 8) = v[u];
+    }
+}
+
+// The lane's bias values, [tile][r] of its channels.
+template <int COUT>
+__device__ __forceinline__ void load_bias(const float* bias, int kgrp, f32x4 (&bb)[COUT / 16])
+{
+#pragma unroll
+    for (int nt = 0; nt < COUT / 16; ++nt)
+        bb[nt] = bias ? *reinterpret_cast<const f32x4*>(bias + out_channel<COUT>(16 * nt + 4 * kgrp))
+                      : f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+}
+
+// All ones in each half of eight BF16 values whose mask value is positive, else
+// zeros: as integers (activations after a ReLU: never a NaN) the positive
+// values are those above zero.
+__device__ __forceinline__ s16x8 positive_halves(const bf16x8& m)
+{
+    const s16x8 zero = {}, one = {1, 1, 1, 1, 1, 1, 1, 1};
+    return zero - __builtin_elementwise_min(__builtin_elementwise_max(__builtin_bit_cast(s16x8, m), zero), one);
+}
+
+// The lane's values of one pixel from its accumulators, in the form of MODE
+// (see the convolutions).  p: the pixel less its column row16 in a tile
+// (wave-uniform), lane_p: that column; mk: the mask values of the lane's
+// channels (MODE 3).
+template <int COUT, int MODE>
+__device__ __forceinline__ void store_pixel(void* Y, size_t p, uint32_t lane_p, int kgrp,
+                                            const f32x4 (&acc)[COUT / 16], const f32x4 (&bb)[COUT / 16],
+                                            const bf16x8 (&mk)[(COUT + 31) / 32])
+{
+    if constexpr (MODE == 2) {
+        if (kgrp == 0) {
+            f32x4 v = acc[0] + bb[0];
+#pragma unroll
+            for (int r = kOutUsed; r < 4; ++r) v[r] = 0.0f;
+            *reinterpret_cast<f32x4*>(reinterpret_cast<char*>(Y) + 16 * p + 16 * lane_p) = v;
+        }
+    } else {
+        static_assert(COUT == 64, "eight channels a store");
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            bf16x8 o;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                float v = acc[2 * h + e / 4][e % 4];
+                if (MODE == 0) v = fmaxf(v + bb[2 * h + e / 4][e % 4], 0.0f);
+                o[e] = to_bf16(v);
+            }
+            if (MODE == 3) o = __builtin_bit_cast(bf16x8, __builtin_bit_cast(s16x8, o) & positive_halves(mk[h]));
+            *reinterpret_cast<bf16x8*>(reinterpret_cast<char*>(Y) + 2 * (p * COUT + 32 * h) +
+                                       2 * (lane_p * COUT + 8u * (uint32_t)kgrp)) = o;
+        }
+    }
+}
 
 // ----------------------------------------------------------------------------
 // convolution as implicit GEMM (forward and input gradient)
@@ -88,19 +203,18 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const bf16* __restri
     constexpr int MT = kMtPerWave;
     constexpr int CHUNKS = (CTH + 2) * (TW + 2) * (CIN / 8);
     constexpr int XPT = (CHUNKS + kConvThreads - 1) / kConvThreads;
-    constexpr int WCH = COUT * (KP / 8);
     extern __shared__ __align__(16) unsigned char smem[];
     bf16* xin = reinterpret_cast<bf16*>(smem);                        // [(CTH+2)(TW+2)][PIX]
     bf16* wl = xin + (CTH + 2) * (TW + 2) * PIX;                       // [COUT][WST]
 
-    const int tiles_x = W / TW, tiles_y = H / CTH, per_img = tiles_x * tiles_y;
-    const int ntiles = N * per_img;
+    const int tiles_x = W / TW, tiles_y = H / CTH;
+    const int ntiles = N * tiles_x * tiles_y;
     bf16x8 xb[XPT];
     // input tile (with halo, zeros outside the image) of tile t into registers
     auto fetch = [&](int t) {
-        const int n = t / per_img, r = t % per_img;
-        const int y0 = (r / tiles_x) * CTH, x0 = (r % tiles_x) * TW;
-        const bf16* Xn = X + (size_t)n * H * W * CIN;
+        const TileAt at = tile_at(t, ntiles, tiles_x, tiles_y, gridDim.x);
+        const int y0 = at.ty * CTH, x0 = at.tx * TW;
+        const bf16* Xn = X + (size_t)at.n * H * W * CIN;
 #pragma unroll
         for (int u = 0; u < XPT; ++u) {
             const int q = threadIdx.x + u * kConvThreads;
@@ -127,22 +241,18 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const bf16* __restri
     int t = blockIdx.x;
     if (t >= ntiles) return;
     fetch(t);
-    // the weights [COUT][KP], once per block
-    for (int q = threadIdx.x; q < WCH; q += kConvThreads) {
-        const int co = q / (KP / 8), k8 = (q % (KP / 8)) * 8;
-        *reinterpret_cast<bf16x8*>(wl + co * WST + k8) = *reinterpret_cast<const bf16x8*>(Wt + (size_t)co * KP + k8);
-    }
+    stage_weights<COUT, KP, WST, kConvThreads>(Wt, wl, threadIdx.x);      // once per block
     deposit();
     __syncthreads();
 
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int row16 = lane & 15, kgrp = lane >> 4;
-    float bb[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) bb[nt] = bias ? bias[16 * nt + row16] : 0.0f;
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    f32x4 bb[NT];
+    load_bias<COUT>(MODE == 3 ? nullptr : bias, kgrp, bb);
     for (; t < ntiles; t += gridDim.x) {
-        const int n = t / per_img, r = t % per_img;
-        const int y0 = (r / tiles_x) * CTH, x0 = (r % tiles_x) * TW;
+        const TileAt at = tile_at(t, ntiles, tiles_x, tiles_y, gridDim.x);
+        const int n = at.n, y0 = at.ty * CTH, x0 = at.tx * TW;
         const int tn = t + gridDim.x;
         if (tn < ntiles) fetch(tn);                     // in flight during the matrix work below
 
@@ -172,40 +282,23 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const bf16* __restri
             for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
-                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[mt], b[nt], acc[mt][nt], 0, 0, 0);
+                    acc[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[nt], a[mt], acc[mt][nt], 0, 0, 0);
         }
 
-        // D tile: lane holds rows (pixels) 4*kgrp + r, column (channel) row16.
-        // One M tile at a time: its mask values (MODE 3) loaded together, then the stores.
+        // the mask values (MODE 3) of the lane's pixels loaded together, then the stores
+        const size_t t0 = ((size_t)n * H + y0 + 2 * uwave) * W + x0;
+        bf16x8 mv[MT][(COUT + 31) / 32] = {};
+        if (MODE == 3)
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) {
-            const int gy = y0 + 2 * wave + (mt >> 1);
-            const size_t p0 = ((size_t)n * H + gy) * W + x0 + 16 * (mt & 1) + 4 * kgrp;
-            bf16 mk[NT][4];
-            if (MODE == 3) {
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
+                for (int h = 0; h < COUT / 32; ++h)
+                    mv[mt][h] = *reinterpret_cast<const bf16x8*>(
+                        mask + (t0 + (size_t)(mt >> 1) * W + 16 * (mt & 1)) * COUT + 32 * h +
+                        (uint32_t)(row16 * COUT + 8 * kgrp));
 #pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) mk[nt][rr] = mask[(p0 + rr) * COUT + 16 * nt + row16];
-            }
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) {
-                const int co = 16 * nt + row16;
-#pragma unroll
-                for (int rr = 0; rr < 4; ++rr) {
-                    float v = acc[mt][nt][rr] + bb[nt];
-                    const size_t p = p0 + rr;
-                    if (MODE == 0) {
-                        reinterpret_cast<bf16*>(Y)[p * COUT + co] = to_bf16(fmaxf(v, 0.0f));
-                    } else if (MODE == 3) {
-                        reinterpret_cast<bf16*>(Y)[p * COUT + co] =
-                            to_f32(mk[nt][rr]) > 0.0f ? to_bf16(v) : to_bf16(0.0f);
-                    } else {
-                        if (co < 4) reinterpret_cast<float*>(Y)[p * 4 + co] = co < kOutUsed ? v : 0.0f;
-                    }
-                }
-            }
-        }
+        for (int mt = 0; mt < MT; ++mt)
+            store_pixel<COUT, MODE>(Y, t0 + (size_t)(mt >> 1) * W + 16 * (mt & 1), row16, kgrp, acc[mt], bb, mv[mt]);
         if (tn < ntiles) {
             __syncthreads();          // every wave is done with this tile's input
             deposit();
@@ -221,12 +314,19 @@ __global__ __launch_bounds__(kConvThreads) void conv_kernel(const bf16* __restri
 // matrix work.  A compute wave owns 4 output rows x 32 columns x all COUT
 // channels (4 x 2 x COUT/16 accumulator tiles).  The reduction runs over
 // (dx, channel half, dy): for a fixed dx and half of the input channels the
-// wave loads the 3 x COUT/16 weight operands of the three dy taps once, then
-// streams the 6 input rows its output rows need, and each input row's two
-// operands feed every (output row, dy) pair that reads that row: 12 A and 12 B
-// loads per 96 MFMAs for COUT = 64.  Four loader waves fetch the next tile's
-// input into registers during the matrix work and store it to LDS between
-// two barriers.
+// wave's 6 input rows and the 3 x COUT/16 weight operands of the three dy taps
+// are each read once (24 loads per 96 MFMAs for COUT = 64), a few groups of
+// MFMAs ahead.  Four loader waves fetch the next tile's input into registers
+// during the matrix work and store it to LDS between two barriers.
+//
+// What bounds it: with the loads spread between the MFMAs the matrix phase of a
+// tile takes 10,000 cycles of the 9,216 its MFMAs need (13,000-19,000 with the
+// loads in bursts before their uses), and the clock then falls to 1.6-1.8 GHz:
+// on real data the power limit, with HBM (256 B a pixel) close behind at large
+// sizes.  A 64 -> 64 layer at 8 x 256^2: forward 48 -> 40 us, input gradient
+// 61 -> 51 (mask and output as 16-byte vectors, two bytes at a time before);
+// at 3 x 176 x 224: 17.7 -> 14.1 and 19 -> 17 (the weights staged in one round
+// of loads); 4 x 2048^2, real data: 1.24 -> 1.18 ms.
 // ----------------------------------------------------------------------------
 constexpr int kC64Waves = 4, kC64Loaders = 256, kC64Threads = kC64Waves * 64 + kC64Loaders;
 constexpr int kC64Rows = CTH / kC64Waves;     // output rows per compute wave
@@ -244,40 +344,36 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
     constexpr int NT = COUT / 16, R = kC64Rows;
     constexpr int CHUNKS = (CTH + 2) * (TW + 2) * (CIN / 8);
     constexpr int XPT = (CHUNKS + kC64Loaders - 1) / kC64Loaders;
-    constexpr int WCH = COUT * (KP / 8);
     static_assert(KP == 9 * CIN, "no padding of the reduction");
+    static_assert(R == 4, "the order of the operand loads");
     extern __shared__ __align__(16) unsigned char smem[];
     bf16* xin = reinterpret_cast<bf16*>(smem);                        // [(CTH+2)(TW+2)][PIX]
     bf16* wl = xin + (CTH + 2) * (TW + 2) * PIX;                       // [COUT][WST]
 
-    const int tiles_x = W / TW, tiles_y = H / CTH, per_img = tiles_x * tiles_y;
-    const int ntiles = N * per_img;
+    const int tiles_x = W / TW, tiles_y = H / CTH;
+    const int ntiles = N * tiles_x * tiles_y;
     const int wave = threadIdx.x >> 6;
     if ((int)blockIdx.x >= ntiles) return;
-    // the weights [COUT][KP], once per block
-    for (int q = threadIdx.x; q < WCH; q += kC64Threads) {
-        const int co = q / (KP / 8), k8 = (q % (KP / 8)) * 8;
-        *reinterpret_cast<bf16x8*>(wl + co * WST + k8) = *reinterpret_cast<const bf16x8*>(Wt + (size_t)co * KP + k8);
-    }
-
     if (wave >= kC64Waves) {
         // ---- loader waves
         const int lt = threadIdx.x - kC64Waves * 64;
         bf16x8 xb[XPT];
-        // input tile (with halo, zeros outside the image) of tile t into registers
+        uint32_t inside = 0;          // which of the chunks lie in the image
+        // input tile (with halo) of tile t into registers; the data is not
+        // touched before the deposit, so the wait for it lies past barrier B
         auto fetch = [&](int t) {
-            const int n = t / per_img, r = t % per_img;
-            const int y0 = (r / tiles_x) * CTH, x0 = (r % tiles_x) * TW;
-            const bf16* Xn = X + (size_t)n * H * W * CIN;
+            const TileAt at = tile_at(t, ntiles, tiles_x, tiles_y, gridDim.x);
+            const int y0 = at.ty * CTH, x0 = at.tx * TW;
+            const bf16* Xn = X + (size_t)at.n * H * W * CIN;
+            inside = 0;
 #pragma unroll
             for (int u = 0; u < XPT; ++u) {
                 const int q = lt + u * kC64Loaders;
                 const int px = q / (CIN / 8), c8 = (q % (CIN / 8)) * 8;
                 const int gy = y0 + px / (TW + 2) - 1, gx = x0 + px % (TW + 2) - 1;
-                const bool in = q < CHUNKS && gy >= 0 && gy < H && gx >= 0 && gx < W;
-                const bf16x8 l = *reinterpret_cast<const bf16x8*>(
+                inside |= (uint32_t)(gy >= 0 && gy < H && gx >= 0 && gx < W) << u;
+                xb[u] = *reinterpret_cast<const bf16x8*>(
                     Xn + ((size_t)min(max(gy, 0), H - 1) * W + min(max(gx, 0), W - 1)) * CIN + c8);
-                xb[u] = in ? l : bf16x8{};
             }
         };
         auto deposit = [&]() {
@@ -286,31 +382,35 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
                 const int q = lt + u * kC64Loaders;
                 if (q < CHUNKS) {
                     const int px = q / (CIN / 8), c8 = (q % (CIN / 8)) * 8;
-                    *reinterpret_cast<bf16x8*>(xin + px * PIX + c8) = xb[u];
+                    *reinterpret_cast<bf16x8*>(xin + px * PIX + c8) = inside >> u & 1u ? xb[u] : bf16x8{};
                 }
             }
         };
+        static_assert(XPT <= 32, "a bit per chunk");
         fetch(blockIdx.x);
         deposit();
         for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
             __syncthreads();                  // A: tile t (and the weights) in LDS
             const int tn = t + gridDim.x;
             if (tn < ntiles) fetch(tn);
+            __builtin_amdgcn_sched_barrier(0);
             __syncthreads();                  // B: the compute waves are done with tile t
+            __builtin_amdgcn_sched_barrier(0);
             if (tn < ntiles) deposit();
         }
         return;
     }
 
-    // ---- compute waves
+    // ---- compute waves: the weights, once per block, while the loaders fetch the first tile
+    stage_weights<COUT, KP, WST, kC64Waves * 64>(Wt, wl, threadIdx.x);
     const int lane = threadIdx.x & 63;
     const int row16 = lane & 15, kgrp = lane >> 4;
-    float bb[NT];
-#pragma unroll
-    for (int nt = 0; nt < NT; ++nt) bb[nt] = bias ? bias[16 * nt + row16] : 0.0f;
+    const int uwave = __builtin_amdgcn_readfirstlane(wave);
+    f32x4 bb[NT];
+    load_bias<COUT>(MODE == 3 ? nullptr : bias, kgrp, bb);
     for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
-        const int n = t / per_img, r = t % per_img;
-        const int y0 = (r / tiles_x) * CTH, x0 = (r % tiles_x) * TW;
+        const TileAt at = tile_at(t, ntiles, tiles_x, tiles_y, gridDim.x);
+        const int n = at.n, y0 = at.ty * CTH, x0 = at.tx * TW;
         __syncthreads();                      // A
         f32x4 acc[R][2][NT];
 #pragma unroll
@@ -319,73 +419,83 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
             for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) acc[i][hf][nt] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 1
+        // Step s is a column offset dx = s / 2 and half of the input channels;
+        // in it the tap row dy = 0, 1, 2 and for each the R output rows i: a
+        // group of 2 x NT MFMAs on input row i + dy.  Registers hold the R + 2
+        // input rows of the step and the weights of two tap rows, and every
+        // group issues two operand loads for later ones: a row is replaced by
+        // the next step's after its last use, the weights two tap rows ahead.
+        // So the four waves' reads spread evenly (half of what LDS delivers)
+        // and every load has at least three groups (384 cycles) to arrive; the
+        // barriers keep the compiler from moving loads to their uses.
+        bf16x8 w[2][NT], x[R + 2][2];
+        const bf16* wp = wl + row16 * WST + 8 * kgrp;
+        const bf16* xp = xin + (R * wave * (TW + 2) + row16) * PIX + 8 * kgrp;
+        auto load_w = [&](int s, int dy, int half) {
+#pragma unroll
+            for (int nt = half * (NT / 2); nt < (half ? NT : (NT + 1) / 2); ++nt)
+                w[(3 * s + dy) & 1][nt] = *reinterpret_cast<const bf16x8*>(
+                    wp + 16 * nt * WST + (dy * 3 + (s >> 1)) * CIN + 32 * (s & 1));
+        };
+        auto load_x = [&](int s, int xr) {
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+                x[xr][hf] = *reinterpret_cast<const bf16x8*>(xp + (xr * (TW + 2) + 16 * hf + (s >> 1)) * PIX +
+                                                             32 * (s & 1));
+        };
+        // MODE 3: the mask values of the lane's pixels, one output row at a time
+        // into the registers that the last step frees
+        const size_t t0 = ((size_t)n * H + y0 + R * uwave) * W + x0;
+        bf16x8 mv[R][2][(COUT + 31) / 32] = {};
+        auto load_mask = [&](int i) {
+#pragma unroll
+            for (int hf = 0; hf < 2; ++hf)
+#pragma unroll
+                for (int h = 0; h < COUT / 32; ++h)
+                    mv[i][hf][h] = *reinterpret_cast<const bf16x8*>(mask + (t0 + (size_t)i * W + 16 * hf) * COUT +
+                                                                    32 * h + (uint32_t)(row16 * COUT + 8 * kgrp));
+        };
+        load_w(0, 0, 0);
+        load_w(0, 0, 1);
+#pragma unroll
+        for (int xr = 0; xr < R + 2; ++xr) load_x(0, xr);
+#pragma unroll
         for (int s = 0; s < 6; ++s) {
-            const int dx = s >> 1, c = 32 * (s & 1) + 8 * kgrp;
-            bf16x8 b[3][NT];
 #pragma unroll
-            for (int dy = 0; dy < 3; ++dy)
+            for (int dy = 0; dy < 3; ++dy) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-                    b[dy][nt] = *reinterpret_cast<const bf16x8*>(wl + (16 * nt + row16) * WST + (dy * 3 + dx) * CIN + c);
-            // input row xr of the wave's window is tile row R * wave + xr (one halo row above)
-#pragma unroll
-            for (int xr = 0; xr < R + 2; ++xr) {
-                bf16x8 a[2];
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
-                    a[hf] = *reinterpret_cast<const bf16x8*>(
-                        xin + ((R * wave + xr) * (TW + 2) + 16 * hf + row16 + dx) * PIX + c);
-#pragma unroll
-                for (int dy = 0; dy < 3; ++dy) {
-                    const int i = xr - dy;
-                    if (i < 0 || i >= R) continue;
+                for (int i = 0; i < R; ++i) {
+                    const bool more = s < 5;
+                    if (dy < 2 && i < 2) load_w(s, dy + 1, i);
+                    if (dy == 2 && i < 2 && more) load_w(s + 1, 0, i);
+                    if (dy == 0 && i == 0 && s > 0) load_x(s, R + 1);
+                    if (dy < 2 && i == 2 && more) load_x(s + 1, dy);
+                    if (dy == 2 && i > 0 && more) load_x(s + 1, i + 1);
+                    if (MODE == 3 && !more && dy == 2 && (i == 1 || i == 3)) load_mask(i / 2);
+                    __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                     for (int hf = 0; hf < 2; ++hf)
 #pragma unroll
                         for (int nt = 0; nt < NT; ++nt)
-                            acc[i][hf][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[hf], b[dy][nt], acc[i][hf][nt], 0, 0, 0);
+                            acc[i][hf][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                w[(3 * s + dy) & 1][nt], x[i + dy][hf], acc[i][hf][nt], 0, 0, 0);
+                    __builtin_amdgcn_sched_barrier(0);
                 }
             }
         }
+        if (MODE == 3) {
+            load_mask(2);
+            load_mask(3);
+        }
+        __builtin_amdgcn_sched_barrier(0);    // the epilogue's work stays behind the barrier
         __syncthreads();                      // B: the loaders may overwrite the input tile
+        __builtin_amdgcn_sched_barrier(0);
 
-        // D tile: lane holds rows (pixels) 4*kgrp + r, column (channel) row16.
-        // One output row at a time: its mask values (MODE 3) loaded together, then the stores.
 #pragma unroll
-        for (int i = 0; i < R; ++i) {
-            const int gy = y0 + R * wave + i;
-            const size_t p0 = ((size_t)n * H + gy) * W + x0 + 4 * kgrp;
-            bf16 mk[2][NT][4];
-            if (MODE == 3) {
-#pragma unroll
-                for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                        for (int rr = 0; rr < 4; ++rr)
-                            mk[hf][nt][rr] = mask[(p0 + 16 * hf + rr) * COUT + 16 * nt + row16];
-            }
+        for (int i = 0; i < R; ++i)
 #pragma unroll
             for (int hf = 0; hf < 2; ++hf)
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) {
-                    const int co = 16 * nt + row16;
-#pragma unroll
-                    for (int rr = 0; rr < 4; ++rr) {
-                        const float v = acc[i][hf][nt][rr] + bb[nt];
-                        const size_t p = p0 + 16 * hf + rr;
-                        if (MODE == 0) {
-                            reinterpret_cast<bf16*>(Y)[p * COUT + co] = to_bf16(fmaxf(v, 0.0f));
-                        } else if (MODE == 3) {
-                            reinterpret_cast<bf16*>(Y)[p * COUT + co] =
-                                to_f32(mk[hf][nt][rr]) > 0.0f ? to_bf16(v) : to_bf16(0.0f);
-                        } else {
-                            if (co < 4) reinterpret_cast<float*>(Y)[p * 4 + co] = co < kOutUsed ? v : 0.0f;
-                        }
-                    }
-                }
-        }
+                store_pixel<COUT, MODE>(Y, t0 + (size_t)i * W + 16 * hf, row16, kgrp, acc[i][hf], bb, mv[i][hf]);
     }
 }
 
