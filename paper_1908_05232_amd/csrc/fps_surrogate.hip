@@ -29,6 +29,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 #include <utility>
 #include <cmath>
 #include <cstdarg>
@@ -504,16 +505,20 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
 //
 // The reduction runs over pixels, so each MFMA's k index needs runs of
 // consecutive pixels per channel in LDS, and the nine taps shift those runs.
-// Here the eight k values a lane supplies are the same pixel of eight images
-// (images past the batch are zero): the LDS tiles hold, per pixel position
-// and channel, one 16-byte vector of the eight images, so a tap's shift moves
-// whole vectors and one copy of the input tile serves all nine taps.  A k-slab
-// of 32 is four positions (the four rows of the tile in one column) times
-// eight images.
+// Here the eight k values a lane supplies are the same position of eight
+// bands: the batch's 4-row bands (of all images, one after the other) are cut
+// into eight runs of equal length, and slot j of a tile is band i of run j, with
+// its own halo; bands past the last are zero.  The LDS tiles hold, per
+// position and channel, one 16-byte vector of the eight slots, so a tap's
+// shift moves whole vectors and one copy of the input tile serves all nine
+// taps.  A k-slab of 32 is four positions (the four rows of the tile in one
+// column) times eight slots.  With eight images the runs are the images; any
+// other batch fills the slots as well (with a slot per image a batch of 3 left
+// 5 of 8 empty).
 //
-// Tile: 4 rows x 8 columns of positions x 8 images (256 pixels).  LDS:
-//   dzL[pos][swz(co)][8 images], pos = row * 8 + col           (32 positions)
-//   xL[pos][swz(ci)][8 images],  pos = row * 10 + col, halo of one (60 positions)
+// Tile: 4 rows x 8 columns of positions x 8 slots (256 pixels).  LDS:
+//   dzL[pos][swz(co)][8 slots], pos = row * 8 + col           (32 positions)
+//   xL[pos][swz(ci)][8 slots],  pos = row * 10 + col, halo of one (60 positions)
 // with swz(c) = c ^ ((c >> 3) & 7) and a padded position stride, so that the
 // 16-byte stores of the staging (a lane per channel group) and the 16-byte
 // operand reads (a lane per channel) fall in distinct banks.
@@ -524,9 +529,17 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
 // tiles than compute waves split the columns between waves, each writing a
 // partial of its own.  Four more waves only load: while the compute waves
 // work on a tile they fetch the next one, transpose it in registers and add
-// up its bias gradient, and between two barriers they store it to LDS.
+// up its bias gradient, and between two barriers they store it to LDS.  Every
+// load of a tile goes out before the first wait, dz first (the order x, dz
+// measured 4 us a launch more).
+// Bound by HBM for large inputs (134 MB at 64-64 channels, 8 x 256^2, 45 to
+// 48 us) and by the chain load, transpose, store where a block has few tiles.
+// Measured 64-64 / 64-16 / 16-64 channels: 8 x 256^2 45-48 / 34 / 32 us, as with a
+// slot per image; 3 x 176 x 224 19.9 / 16.6 / 15.3 us (26.8 / 23 / 19.5).
 // ----------------------------------------------------------------------------
-constexpr int WTH = 4, WTW = 8, WNG = 8;      // weight-gradient tile: rows, columns, images
+constexpr int WTH = 4, WTW = 8, WNG = 8;      // weight-gradient tile: rows, columns, slots
+// bands of each run: the tiles of the pass are wg_run bands x W / WTW columns
+__host__ __device__ constexpr int64_t wg_run(int64_t n, int H) { return (n * (H / WTH) + WNG - 1) / WNG; }
 __host__ __device__ constexpr int wg_pad(int c) { return c == 64 ? 8 : 2; }
 __host__ __device__ constexpr int wg_co_per(int cout) { return cout / 16; }
 __host__ __device__ constexpr int wg_groups(int cin, int cout) { return (cin / 16) * (cout / 16 / wg_co_per(cout)); }
@@ -549,20 +562,20 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
     constexpr int PSD = COUT + wg_pad(COUT), PSX = CIN + wg_pad(CIN);   // position strides, 16-byte units
     constexpr int XW = WTW + 2, XPOS = (WTH + 2) * XW;
     constexpr int NCO8 = COUT / 8, NCI8 = CIN / 8;
-    constexpr int DZU = WTH * WTW * NCO8, XU = XPOS * NCI8, UNITS = DZU + XU;   // staging units
-    constexpr int XPT = (UNITS + kWgLoaders - 1) / kWgLoaders;
+    constexpr int DZU = WTH * WTW * NCO8, XU = XPOS * NCI8;      // staging units: one of dz and XN of x per loader thread
+    constexpr int XN = (XU + kWgLoaders - 1) / kWgLoaders, XPT = XN + 1;
     constexpr int CO_PER = wg_co_per(COUT), NCIT = CIN / 16;
     constexpr int G = wg_groups(CIN, COUT), KS = wg_ksplit(CIN, COUT), CPW = WTW / KS;
     static_assert(G * KS == kWgWaves && WTW % KS == 0, "wave split");
-    static_assert(DZU <= kWgLoaders, "every dz unit in the first round of a fixed loader thread");
+    static_assert(DZU <= kWgLoaders && DZU % 64 == 0, "at most one dz unit a thread, in whole waves");
     static_assert(kWgLoaders % NCO8 == 0, "fixed channel group per loader thread");
     extern __shared__ __align__(16) unsigned char smem[];
     bf16x8* dzL = reinterpret_cast<bf16x8*>(smem);
     bf16x8* xL = dzL + WTH * WTW * PSD;
 
     const int wave = threadIdx.x >> 6;
-    const int tiles_x = W / WTW, tiles_y = H / WTH, per_grp = tiles_x * tiles_y;
-    const int ntiles = ((N + WNG - 1) / WNG) * per_grp;
+    const int tiles_x = W / WTW, bands_y = H / WTH, nbands = N * bands_y;
+    const int run = (int)wg_run(N, H), ntiles = run * tiles_x;
     float bsum[8] = {};
 
     if (wave >= kWgWaves) {
@@ -571,37 +584,63 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
         const int lt = threadIdx.x - kWgWaves * 64;
         typedef bf16x8 Set[XPT][8];
         Set s0;
-        // unit u: 8 images x 8 channels of one position; addresses clamped
-        // into the arrays, values outside the image or the batch zeroed
+        uint32_t kept[XPT];      // per unit, the slots whose values lie in the image and the batch
+        // unit u: 8 slots x 8 channels of one position.  A slot's band starts at
+        // a row of its own (wave-uniform), so a unit's address is that row's
+        // and a lane offset; the halo row above the first band of an image (below
+        // the last) is replaced by the row next to it, and zeroed with
+        // everything outside the image or past the last band.
+        const int lwave = __builtin_amdgcn_readfirstlane(lt >> 6);
+        const uint32_t inv_y = (uint32_t)(0x100000000ull / (uint32_t)bands_y);   // bands_y >= 4
         auto fetch = [&](Set& v, int t) {
-            const int n0 = (t / per_grp) * WNG, r = t % per_grp;
-            const int y0 = (r / tiles_x) * WTH, x0 = (r % tiles_x) * WTW;
+            const int i = t / tiles_x, x0 = t % tiles_x * WTW;
+            // the bands of the slots, and which are an image's first or last
+            // (the quotient by multiplication is at most one short)
+            int band[8];
+            bool have[8], top[8], bottom[8];
 #pragma unroll
-            for (int u = 0; u < XPT; ++u) {
-                const int q = lt + u * kWgLoaders;
-                const bool isdz = q < DZU;
-                const int qq = isdz ? q : q - DZU;
-                const int nc8 = isdz ? NCO8 : NCI8, C = isdz ? COUT : CIN;
+            for (int j = 0; j < 8; ++j) {
+                have[j] = j * run + i < nbands;
+                band[j] = min(j * run + i, nbands - 1);
+                uint32_t by = (uint32_t)band[j] - __umulhi((uint32_t)band[j], inv_y) * (uint32_t)bands_y;
+                if (by >= (uint32_t)bands_y) by -= (uint32_t)bands_y;
+                top[j] = by == 0;
+                bottom[j] = by == (uint32_t)bands_y - 1;
+            }
+            // unit u, of dz or of x (the same for all lanes of a wave)
+            auto unit = [&](auto dz_, int u, int q) {
+                constexpr bool isdz = decltype(dz_)::value;
+                constexpr int nc8 = isdz ? NCO8 : NCI8, C = isdz ? COUT : CIN, PW = isdz ? WTW : XW;
+                const int qq = isdz ? q : min(q, XU - 1);
                 const int pos = qq / nc8, cg = qq % nc8;
-                const int gy = isdz ? y0 + pos / WTW : y0 + pos / XW - 1;
-                const int gx = isdz ? x0 + pos % WTW : x0 + pos % XW - 1;
-                const bool in = q < UNITS && gy >= 0 && gy < H && gx >= 0 && gx < W;
-                const bf16* src = (isdz ? DZ : X) +
-                                  ((size_t)min(max(gy, 0), H - 1) * W + min(max(gx, 0), W - 1)) * C + 8 * cg;
-                const size_t img = (size_t)H * W * C;
+                const int rl = pos / PW - (isdz ? 0 : 1), gx = x0 + pos % PW - (isdz ? 0 : 1);
+                const bool in = (isdz || q < XU) && gx >= 0 && gx < W, above = rl < 0, below = rl >= WTH;
+                // lane offset from the row above the band (bytes: the access is a scalar base and this)
+                const uint32_t row = (uint32_t)W * (uint32_t)(2 * C);
+                const uint32_t off = (uint32_t)(rl + 1) * row + (uint32_t)min(max(gx, 0), W - 1) * (uint32_t)(2 * C) + 16u * cg;
+                const uint32_t off_t = above ? off + row : off, off_b = below ? off - row : off;
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
-                    const bf16x8 l = *reinterpret_cast<const bf16x8*>(src + (size_t)min(n0 + j, N - 1) * img);
-                    v[u][j] = in && n0 + j < N ? l : bf16x8{};
+                    const char* base = reinterpret_cast<const char*>(isdz ? DZ : X) + ((int64_t)band[j] * WTH - 1) * row;
+                    const uint32_t o = isdz ? off : top[j] ? off_t : bottom[j] ? off_b : off;
+                    v[u][j] = *reinterpret_cast<const bf16x8*>(base + o);
+                    const bool keep = in && have[j] && (isdz || (!(top[j] && above) && !(bottom[j] && below)));
+                    kept[u] = (j ? kept[u] : 0u) | (uint32_t)keep << j;
                 }
-            }
+            };
+            if (lwave * 64 < DZU) unit(std::true_type{}, 0, lt);
+#pragma unroll
+            for (int u = 1; u < XPT; ++u) unit(std::false_type{}, u, lt + (u - 1) * kWgLoaders);
+            __builtin_amdgcn_sched_barrier(0);      // every load goes out before the first wait
         };
-        // v[u][j][e] (image j, channel e) -> v[u][e][j]; dz units add to the bias sums
+        // v[u][j][e] (slot j, channel e) -> v[u][e][j]; dz units add to the bias sums
         auto transpose = [&](Set& v) {
 #pragma unroll
             for (int u = 0; u < XPT; ++u) {
-                const int q = lt + u * kWgLoaders;
-                if (u == 0 && q < DZU) {
+                if (u == 0 && lwave * 64 >= DZU) continue;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) v[u][j] = kept[u] >> j & 1u ? v[u][j] : bf16x8{};
+                if (u == 0) {
 #pragma unroll
                     for (int j = 0; j < 8; ++j)
 #pragma unroll
@@ -619,11 +658,10 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
         auto store = [&](Set& v) {
 #pragma unroll
             for (int u = 0; u < XPT; ++u) {
-                const int q = lt + u * kWgLoaders;
-                if (q >= UNITS) continue;
-                const bool isdz = q < DZU;
-                const int pos = isdz ? q / NCO8 : (q - DZU) / NCI8;
-                const int cg = isdz ? q % NCO8 : (q - DZU) % NCI8;
+                const bool isdz = u == 0;
+                const int q = isdz ? lt : lt + (u - 1) * kWgLoaders;
+                if (q >= (isdz ? DZU : XU)) continue;
+                const int pos = isdz ? q / NCO8 : q / NCI8, cg = isdz ? q % NCO8 : q % NCI8;
                 bf16x8* dst = isdz ? dzL + pos * PSD : xL + pos * PSX;
 #pragma unroll
                 for (int e = 0; e < 8; ++e) dst[wg_swz(8 * cg + e)] = v[u][e];
@@ -1159,7 +1197,7 @@ int wgrad(fps_sur* s, int n, const bf16* x, const bf16* dz, int layer)
     const size_t lds = wg_lds(CIN, COUT);
     auto k = wgrad_kernel<CIN, COUT>;
     SCHK(s, hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
-    const int tiles = (n + WNG - 1) / WNG * (s->H / WTH) * (s->W / WTW);
+    const int tiles = (int)wg_run(n, s->H) * (s->W / WTW);
     // persistent: one block per compute unit (or fewer, when capped)
     const int cap = std::min(s->cus, kWgradBlocks);
     const int blocks = std::min(tiles, s->wgrad_cap > 0 ? std::min(s->wgrad_cap, cap) : cap);

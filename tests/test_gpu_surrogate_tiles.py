@@ -1,12 +1,17 @@
 """The order in which the convolution blocks take their tiles: patches of 4 x 8
 tiles per XCD where the image divides into them, a remainder past the last full
 round of blocks, and images that do not divide.  With a cap on the blocks every
-tile is taken in plain order, and the results are the same bits."""
+tile is taken in plain order, and the results are the same bits.  And the
+weight gradient's runs of 4-row bands: with a batch that is no multiple of eight
+a run ends inside an image or past the last band."""
+import numpy as np
 import pytest
 import torch
 
+from oracle import surrogate_oracle as S
 from paper_1908_05232_amd import fps, surrogate as SG
 from tests.gpu_util import say
+from tests.test_gpu_surrogate import ELEM_TOL, cosine, make_case, rel_l2, to_dev, unpack
 
 pytestmark = pytest.mark.gpu
 
@@ -35,3 +40,27 @@ def test_tile_order_does_not_change_the_results(n, H, W):
     assert torch.isfinite(out[0][0]).all() and float(out[0][0].abs().max()) > 0
     for a, b in zip(*out):
         assert torch.equal(a, b)
+
+
+# bands of the batch: 4 (four empty slots), 8 (one each), 12 (runs of 2, two
+# slots empty), 20 (runs of 3 over image borders, the last slot 2 short of
+# full), 60 (runs of 8 in images of 12), with the bars of the other gradient tests
+@pytest.mark.parametrize("n,H,W", [(1, 16, 32), (2, 16, 32), (3, 16, 64), (5, 16, 32), (5, 48, 32)])
+def test_weight_gradient_of_ragged_batches_matches_oracle(n, H, W):
+    params, x, target = make_case(40 + n, n, H, W)
+    sur = fps.Surrogate(n, H, W)
+    p, xt, tt = to_dev(params, x, target)
+    sur.set_params(p)
+    _, g = sur.gradients(xt, tt)
+    _, gb = S.loss_and_grads(params, x, target, bf16=True)
+    gg = unpack(g.cpu().numpy().astype(np.float64), params)
+    sur.close()
+    for li in range(len(gg)):
+        (dw, db), (dwb, dbb) = gg[li], gb[li]
+        if li == 0:
+            dw, dwb = dw[..., :5], dwb[..., :5]       # zero input channels carry no gradient
+        ew = float(np.abs(dw - dwb).max() / np.abs(dwb).max())
+        eb = float(np.abs(db - dbb).max() / np.abs(dbb).max())
+        say(f"{n} x {H} x {W}, layer {li + 1}: dW max|d| / max|ref| {ew:.2e}, db {eb:.2e}")
+        assert ew <= ELEM_TOL and eb <= ELEM_TOL
+        assert cosine(dw, dwb) >= 0.9999 and rel_l2(dw, dwb) <= 1e-2
