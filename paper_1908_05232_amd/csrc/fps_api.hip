@@ -378,12 +378,10 @@ void fill_scn(const fps_sim* s, Scn& c)
     r.bags_per = s->bags_per; r.t_bag = s->t_bag; r.t_last = s->t_last;
 
     c.na = s->na;
-    // many bins: scanned by many blocks, and the agents placed by the placement kernels
-    const bool mb = s->na > 0 && s->nbins > kMbScanBins;
+    c.lds_bins = s->na > 0 && s->na <= kLdsAgents && s->nbins <= kLdsBins;
+    // many bins: scanned by many blocks
+    const bool mb = s->na > 0 && !c.lds_bins && s->nbins > kMbScanBins;
     b.nchunk = mb ? (s->nbins + kChunkBins - 1) / kChunkBins : 0;
-    c.inline_place = s->na <= kInlinePlace && !mb;
-    c.lds_bins = c.inline_place && s->na > 0 && s->nbins <= kLdsScanBins &&
-                 (int64_t)s->nbins + 1 + s->na <= kLdsBinWords;
     c.ped.need_rank = !c.lds_bins;       // the LDS binning counts the keys itself
 }
 
@@ -418,10 +416,10 @@ int upload(Engine* e)
         if (nt > kRedMin) e->red_chunks = std::max(e->red_chunks, (nt + kRedTiles - 1) / kRedTiles);
         e->max_cells = std::max(e->max_cells, (int64_t)s->G.nx * s->G.ny);
         e->chunk_off_h[k + 1] = e->chunk_off_h[k] + e->scn_h[k].bins.nchunk;
-        e->any_big = e->any_big || (s->na > 0 && !e->scn_h[k].inline_place);
+        e->any_big = e->any_big || (s->na > 0 && !e->scn_h[k].lds_bins);
         e->any_doors = e->any_doors || e->scn_h[k].ped.n_door > 0;
         if (e->scn_h[k].lds_bins)
-            e->fin_lds_bytes = std::max(e->fin_lds_bytes, (int)(sizeof(int) * (s->nbins + 1 + s->na)));
+            e->fin_lds_bytes = std::max(e->fin_lds_bytes, lds_bin_bytes(s->nbins, s->na));
     }
     HIPCHK_E(e, prepare_finalize(e->fin_lds_bytes));
     e->total_tiles = e->tile_off_h[e->S];

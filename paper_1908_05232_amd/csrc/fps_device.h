@@ -239,68 +239,34 @@ __device__ inline void sort_agent(const BinParams& b, int a)
     b.xy[f] = make_float2(b.x[a], b.y[a]);
 }
 
-// Placement and stable order of at most kInlinePlace agents by one block,
-// after its scan of the global histogram (grids with more bins than the LDS
-// binning takes).  Every global load goes out in two rounds (the agents' keys,
-// ranks and positions; then the bounds of their bins), the unordered
-// placement lives in LDS, and an agent's final slot counts the smaller ids of
-// its bin there.  Same results as place_agent followed by sort_agent.
-__device__ inline void inline_bins_place(const BinParams& b)
-{
-    constexpr int APT = kInlinePlace / kScanThreads;
-    __shared__ int lp[kInlinePlace];
-    int key[APT], rank[APT], s0[APT], s1[APT];
-    float ax[APT], ay[APT];
-#pragma unroll
-    for (int q = 0; q < APT; ++q) {
-        const int a = threadIdx.x + q * kScanThreads, ac = a < b.na ? a : 0;
-        const int k = b.key[ac];
-        rank[q] = b.rank[ac];
-        ax[q] = b.x[ac];
-        ay[q] = b.y[ac];
-        key[q] = a < b.na ? k : -1;
-    }
-#pragma unroll
-    for (int q = 0; q < APT; ++q) {
-        const int kc = key[q] >= 0 ? key[q] : 0;
-        s0[q] = b.bin_start[kc];
-        s1[q] = b.bin_start[kc + 1];
-    }
-#pragma unroll
-    for (int q = 0; q < APT; ++q)
-        if (key[q] >= 0) lp[s0[q] + rank[q]] = threadIdx.x + q * kScanThreads;
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < APT; ++q) {
-        if (key[q] < 0) continue;
-        const int a = threadIdx.x + q * kScanThreads;
-        int below = 0;
-        for (int s = s0[q]; s < s1[q]; ++s) below += lp[s] < a;
-        const int f = s0[q] + below;
-        b.slot[a] = f;
-        b.xy[f] = make_float2(ax[q], ay[q]);
-    }
-}
-
-// One-block binning in LDS for small grids (nbins <= 16 * kScanThreads, at
-// most kInlinePlace agents; dynamic shared memory of nbins + 1 + na words),
-// run by a block of its own beside the end-of-step state update.  It starts
-// from the agents' bin keys alone: a histogram by LDS atomics, the exclusive
-// scan (sixteen bins per thread, the wave by shuffles, the waves in LDS), the
-// placement by LDS atomics and the stable order by id; only the results are
+// One-block binning in LDS (at most kLdsBins bins and kLdsAgents agents), run
+// by a block of its own beside the end-of-step state update.  It starts from
+// the agents' bin keys alone: a histogram by LDS atomics, the exclusive scan,
+// the placement by LDS atomics and the stable order by id; only the results are
 // stored.  Being a function of the keys, it gives the same bins however often
 // it runs on them (a scenario that did not step keeps its bins).  Same results
 // as the global binning.
-__device__ inline void lds_bins_build(const BinParams& b)
+// A count, a start and an agent's number here are at most kLdsAgents, so bins
+// are held two to a word and agents in 16 bits: 65,536 bins (a 1024^2 grid of
+// 0.25 m cells) and 8192 agents take 144 KB.  The scan goes by tiles of sixteen
+// bins a thread (8 words), all tiles between the same two barriers.  Bound by
+// the chain keys - histogram - scan - placement - order, in one launch that the
+// state update needs anyway.  Measured, a step of one centre of 576^2 / 724^2 /
+// 1024^2 cells with 2,000 to 3,000 people: 24.8 / 32.8 / 41.7 us; with the global
+// histogram scanned and placed by one block, or beyond 32,768 bins by four
+// launches, 36.7 / 43.6 / 48.5 (about 2 of the difference are the flood march's).
+constexpr int kLdsTile = 16 * kScanThreads;
+
+template <int TILES>
+__device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
 {
-    constexpr int APT = kInlinePlace / kScanThreads;
-    extern __shared__ int4 fin_lds4[];
-    int* lb = reinterpret_cast<int*>(fin_lds4);    // [nbins + 1]: counts, then starts, then ends
-    int* lp = lb + b.nbins + 1;                    // [na]: agents by bin, unordered
-    __shared__ int wtot[kScanThreads / kWave];
+    constexpr int APT = kLdsAgents / kScanThreads;
+    extern __shared__ uint4 fin_lds4[];
+    uint32_t* lb = reinterpret_cast<uint32_t*>(fin_lds4);      // halves [nbins]: counts, then starts, then ends
+    const int nw = lds_bin_words(b.nbins);
+    uint16_t* lp = reinterpret_cast<uint16_t*>(lb + nw);       // [na]: agents by bin, unordered
+    __shared__ int wtot[TILES][kScanThreads / kWave];
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
-    const int k0 = 16 * threadIdx.x;
-    const bool full = k0 + 16 <= b.nbins;
     int key[APT];
     float ax[APT], ay[APT];
 #pragma unroll
@@ -313,81 +279,110 @@ __device__ inline void lds_bins_build(const BinParams& b)
             ay[q] = b.y[a];
         }
     }
-    if (full) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) reinterpret_cast<int4*>(lb + k0)[q] = make_int4(0, 0, 0, 0);
-    } else {
-        for (int e = k0; e < b.nbins; ++e) lb[e] = 0;
-    }
+    for (int v = threadIdx.x; v < nw / 4; v += kScanThreads) fin_lds4[v] = make_uint4(0, 0, 0, 0);
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < APT; ++q)
-        if (key[q] >= 0) atomicAdd(&lb[key[q]], 1);
+        if (key[q] >= 0) atomicAdd(&lb[key[q] >> 1], 1u << (key[q] & 1) * 16);
     __syncthreads();
-    int hist[16];
-    if (full) {
+    // sixteen bins of each tile a thread; vectors past the last bin count
+    // nothing.  The counts are read again when the starts are formed: held over
+    // the barrier they spilled.
+    auto counts = [&](int t, uint32_t (&h)[8]) {
+        const int v0 = (t * kLdsTile + 16 * (int)threadIdx.x) / 8;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const int4 w = reinterpret_cast<const int4*>(lb + k0)[q];
-            hist[4 * q] = w.x; hist[4 * q + 1] = w.y; hist[4 * q + 2] = w.z; hist[4 * q + 3] = w.w;
+        for (int q = 0; q < 2; ++q) {
+            const uint4 w = v0 + q < nw / 4 ? fin_lds4[v0 + q] : make_uint4(0, 0, 0, 0);
+            h[4 * q] = w.x; h[4 * q + 1] = w.y; h[4 * q + 2] = w.z; h[4 * q + 3] = w.w;
         }
-    } else {
+    };
+    int incl[TILES], own[TILES];
 #pragma unroll
-        for (int e = 0; e < 16; ++e) hist[e] = k0 + e < b.nbins ? lb[k0 + e] : 0;
+    for (int t = 0; t < TILES; ++t) {
+        uint32_t hist[8];
+        counts(t, hist);
+        own[t] = 0;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) own[t] += (int)(hist[e] & 0xffffu) + (int)(hist[e] >> 16);
+        incl[t] = wave_inclusive_scan(own[t]);
+        if (lane == kWave - 1) wtot[t][wid] = incl[t];
     }
-    int tsum = 0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) tsum += hist[e];
-    const int incl = wave_inclusive_scan(tsum);
-    if (lane == kWave - 1) wtot[wid] = incl;
     __syncthreads();
-    int run = incl - tsum, total = 0;
-    for (int w = 0; w < kScanThreads / kWave; ++w) {
-        run += w < wid ? wtot[w] : 0;
-        total += wtot[w];
-    }
-    if (full) {
+    int carry = 0;      // agents before the tile
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            int4 w;
-            w.x = run; run += hist[4 * q];
-            w.y = run; run += hist[4 * q + 1];
-            w.z = run; run += hist[4 * q + 2];
-            w.w = run; run += hist[4 * q + 3];
-            reinterpret_cast<int4*>(b.bin_start + k0)[q] = w;
-            reinterpret_cast<int4*>(lb + k0)[q] = w;
+    for (int t = 0; t < TILES; ++t) {
+        const int k0 = t * kLdsTile + 16 * (int)threadIdx.x;
+        int run = carry + incl[t] - own[t];
+        for (int w = 0; w < kScanThreads / kWave; ++w) {
+            const int x = wtot[t][w];
+            run += w < wid ? x : 0;
+            carry += x;
         }
-    } else {
-        for (int e = 0; e < 16 && k0 + e < b.nbins; ++e) {
-            b.bin_start[k0 + e] = run;
-            lb[k0 + e] = run;
-            run += hist[e];
+        if (k0 >= b.nbins) continue;
+        uint32_t hist[8];
+        counts(t, hist);
+        int start[16];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            start[2 * e] = run;
+            run += (int)(hist[e] & 0xffffu);
+            start[2 * e + 1] = run;
+            run += (int)(hist[e] >> 16);
+        }
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            uint4 w;
+            w.x = (uint32_t)start[8 * q] | (uint32_t)start[8 * q + 1] << 16;
+            w.y = (uint32_t)start[8 * q + 2] | (uint32_t)start[8 * q + 3] << 16;
+            w.z = (uint32_t)start[8 * q + 4] | (uint32_t)start[8 * q + 5] << 16;
+            w.w = (uint32_t)start[8 * q + 6] | (uint32_t)start[8 * q + 7] << 16;
+            if (k0 / 8 + q < nw / 4) fin_lds4[k0 / 8 + q] = w;
+        }
+        if (k0 + 16 <= b.nbins) {
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                reinterpret_cast<int4*>(b.bin_start + k0)[q] =
+                    make_int4(start[4 * q], start[4 * q + 1], start[4 * q + 2], start[4 * q + 3]);
+        } else {
+#pragma unroll
+            for (int e = 0; e < 16; ++e)
+                if (k0 + e < b.nbins) b.bin_start[k0 + e] = start[e];
         }
     }
-    if (threadIdx.x == 0) {
-        b.bin_start[b.nbins] = total;
-        lb[b.nbins] = total;
-    }
+    if (threadIdx.x == 0) b.bin_start[b.nbins] = carry;
     __syncthreads();
     // unordered placement: each agent takes the next free slot of its bin;
-    // afterwards lb[k] is the end of bin k (= start of bin k + 1)
+    // afterwards half k is the end of bin k (= start of bin k + 1)
 #pragma unroll
-    for (int q = 0; q < APT; ++q)
-        if (key[q] >= 0) lp[atomicAdd(&lb[key[q]], 1)] = threadIdx.x + q * kScanThreads;
+    for (int q = 0; q < APT; ++q) {
+        if (key[q] < 0) continue;
+        const int sh = (key[q] & 1) * 16;
+        const uint32_t was = atomicAdd(&lb[key[q] >> 1], 1u << sh);
+        lp[was >> sh & 0xffffu] = (uint16_t)(threadIdx.x + q * kScanThreads);
+    }
     __syncthreads();
     // stable order: an agent's slot counts the smaller ids of its bin
+    auto end = [&](int k) { return (int)(lb[k >> 1] >> (k & 1) * 16 & 0xffffu); };
 #pragma unroll
     for (int q = 0; q < APT; ++q) {
         const int k = key[q];
         if (k < 0) continue;
         const int a = threadIdx.x + q * kScanThreads;
-        const int s0 = k > 0 ? lb[k - 1] : 0, s1 = lb[k];
+        const int s0 = k > 0 ? end(k - 1) : 0, s1 = end(k);
         int below = 0;
         for (int s = s0; s < s1; ++s) below += lp[s] < a;
         const int f = s0 + below;
         b.slot[a] = f;
         b.xy[f] = make_float2(ax[q], ay[q]);
     }
+}
+
+__device__ inline void lds_bins_build(const BinParams& b)
+{
+    static_assert(kLdsBins == 4 * kLdsTile, "at most four tiles");
+    if (b.nbins <= kLdsTile) lds_bins_tiles<1>(b);
+    else if (b.nbins <= 2 * kLdsTile) lds_bins_tiles<2>(b);
+    else lds_bins_tiles<4>(b);
 }
 
 }  // namespace fps

@@ -998,8 +998,7 @@ __device__ double wave_hydro_integral(int nh, double tk, double qk, double a, do
 // a fixed order, advances time, sets the next CFL time step (sec. 3) and
 // inflow depth, applies the sandbag drops of the step to the barrier line
 // (sec. 2.4) and, for scenarios binned in global memory, scans the histogram
-// of the new agent bins (and, for small agent counts, places the agents in bin
-// order), or, for scenarios with many bins, the chunk counts of the
+// of the new agent bins, or, for scenarios with many bins, the chunk counts of the
 // multi-block scan.  Mode 1 only recomputes the time step and mass of the current state.
 template <bool kOne>
 __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mode, int s_first)
@@ -1022,7 +1021,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     const double dxdy = p.dxdy;
     const float cfl = p.cfl, dt_max = p.dt_max, dn = inflow_side <= 1 ? p.dx : p.dy;
     const bool jmask = p.jmask != nullptr;
-    const int na = S.na, inline_place = S.inline_place, lds_bins = S.lds_bins, nline = S.bar.nline;
+    const int na = S.na, lds_bins = S.lds_bins, nline = S.bar.nline;
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
     // The scenario's state words go through LDS: one cooperative load, the
     // serial end-of-step logic on the copy, one cooperative store.  Nothing
@@ -1195,7 +1194,6 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
             block_scan_chunks(bp);      // the chunk scans follow in a launch of their own
         } else {
             block_scan_bins(bp);
-            if (inline_place) inline_bins_place(bp);
         }
     }
 }

@@ -26,9 +26,11 @@ constexpr int kSlots = 16;             // partial sums of an agent's forces (the
 constexpr int kScanThreads = 1024;
 constexpr int kMaxHydro = 64;
 constexpr int kMaskBits = 128;         // obstacle bitmask per cell (uint4)
-constexpr int kInlinePlace = 8192;     // agent counts binned inside the one-block finalize
-constexpr int kLdsBinWords = 30 * 1024;  // LDS words for bin starts + placement in the finalize
-constexpr int kLdsScanBins = 16 * kScanThreads;   // bins the LDS binning scans in one pass
+constexpr int kLdsAgents = 8192;       // agents and bins binned in LDS by a block of the end of step
+constexpr int kLdsBins = 65536;
+// dynamic LDS of that binning: halves per bin in whole 16-byte vectors, halves per agent
+__host__ __device__ constexpr int lds_bin_words(int nbins) { return (nbins + 7) / 8 * 4; }
+__host__ __device__ constexpr int lds_bin_bytes(int nbins, int na) { return 4 * lds_bin_words(nbins) + (2 * na + 3) / 4 * 4; }
 constexpr int kWetSlots = 64;          // wetness flags of a flood update, one per group of blocks
 constexpr int kWetStride = 32;         // ints between flags (one 128-byte line each)
 constexpr int kMaxDoor = 16;           // entrance doors of the pre-flood flow
@@ -170,8 +172,7 @@ struct Scn {
     BinParams bins;
     BarrierParams bar;
     int na;
-    int inline_place;      // agents placed in their bins inside the finalize block
-    int lds_bins;          // ... with the bin starts and the placement in LDS (small grids)
+    int lds_bins;          // binned in LDS by a block of the end of step
 };
 
 // Flattened launch description of an ensemble (device arrays).

@@ -782,15 +782,15 @@ __global__ void bin_sort_kernel(BinParams b)
     if (a < b.na) sort_agent(b, a);
 }
 
-// Ensemble versions for scenarios with more agents than the finalize places
-// inline (same padded flattened index as the pedestrian step).
+// Ensemble versions for scenarios that are not binned in LDS
+// (same padded flattened index as the pedestrian step).
 __global__ __launch_bounds__(kPedBlock) void bin_place_all_kernel(Batch B)
 {
     const int g0 = blockIdx.x * kPedBlock;
     if (g0 >= B.total_agents) return;
     const int sc = find_scenario(B.agent_off, B.S, g0);
     const Scn& S = B.scn[sc];
-    if (S.inline_place) return;
+    if (S.lds_bins) return;
     const int a = g0 - B.agent_off[sc] + (int)threadIdx.x;
     if (a < S.na) {
         const BinParams b = S.bins;    // by value: not reloaded after the stores
@@ -803,7 +803,7 @@ __global__ __launch_bounds__(kPedBlock) void bin_sort_all_kernel(Batch B)
     if (g0 >= B.total_agents) return;
     const int sc = find_scenario(B.agent_off, B.S, g0);
     const Scn& S = B.scn[sc];
-    if (S.inline_place) return;
+    if (S.lds_bins) return;
     const int a = g0 - B.agent_off[sc] + (int)threadIdx.x;
     if (a < S.na) {
         const BinParams b = S.bins;
