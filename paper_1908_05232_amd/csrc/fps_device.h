@@ -252,7 +252,7 @@ __device__ inline void sort_agent(const BinParams& b, int a)
 // bins a thread (8 words), all tiles between the same two barriers.  Bound by
 // the chain keys - histogram - scan - placement - order, in one launch that the
 // state update needs anyway.  Measured, a step of one centre of 576^2 / 724^2 /
-// 1024^2 cells with 2,000 to 3,000 people: 24.8 / 32.8 / 41.7 us; with the global
+// 1024^2 cells with 2,000 to 3,000 people: 23.7 / 30.6 / 38.6 us; with the global
 // histogram scanned and placed by one block, or beyond 32,768 bins by four
 // launches, 36.7 / 43.6 / 48.5 (about 2 of the difference are the flood march's).
 constexpr int kLdsTile = 16 * kScanThreads;
@@ -312,12 +312,10 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
 #pragma unroll
     for (int t = 0; t < TILES; ++t) {
         const int k0 = t * kLdsTile + 16 * (int)threadIdx.x;
-        int run = carry + incl[t] - own[t];
-        for (int w = 0; w < kScanThreads / kWave; ++w) {
-            const int x = wtot[t][w];
-            run += w < wid ? x : 0;
-            carry += x;
-        }
+        // the waves' totals: one a lane, scanned within the row of sixteen lanes
+        const int tot = wave_inclusive_scan(wtot[t][lane & (kScanThreads / kWave - 1)]);
+        int run = carry + incl[t] - own[t] + (wid > 0 ? __builtin_amdgcn_readlane(tot, max(wid - 1, 0)) : 0);
+        carry += __builtin_amdgcn_readlane(tot, kScanThreads / kWave - 1);
         if (k0 >= b.nbins) continue;
         uint32_t hist[8];
         counts(t, hist);
@@ -338,16 +336,6 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
             w.w = (uint32_t)start[8 * q + 6] | (uint32_t)start[8 * q + 7] << 16;
             if (k0 / 8 + q < nw / 4) fin_lds4[k0 / 8 + q] = w;
         }
-        if (k0 + 16 <= b.nbins) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-                reinterpret_cast<int4*>(b.bin_start + k0)[q] =
-                    make_int4(start[4 * q], start[4 * q + 1], start[4 * q + 2], start[4 * q + 3]);
-        } else {
-#pragma unroll
-            for (int e = 0; e < 16; ++e)
-                if (k0 + e < b.nbins) b.bin_start[k0 + e] = start[e];
-        }
     }
     if (threadIdx.x == 0) b.bin_start[b.nbins] = carry;
     __syncthreads();
@@ -361,6 +349,21 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
         lp[was >> sh & 0xffffu] = (uint16_t)(threadIdx.x + q * kScanThreads);
     }
     __syncthreads();
+    // the starts, four bins a lane and whole lines a wave: stored by the thread
+    // that scanned them, every lane's sixteen bytes are a request of their own
+    // (65,536 bins: 17.2 us a launch against 13.3)
+    for (int v = threadIdx.x; v < (b.nbins + 3) / 4; v += kScanThreads) {
+        const uint32_t w0 = v > 0 ? lb[2 * v - 1] >> 16 : 0u, w1 = lb[2 * v], w2 = lb[2 * v + 1];
+        const int4 st = make_int4((int)w0, (int)(w1 & 0xffffu), (int)(w1 >> 16), (int)(w2 & 0xffffu));
+        if (4 * v + 4 <= b.nbins) {
+            reinterpret_cast<int4*>(b.bin_start)[v] = st;
+        } else {
+            const int s4[4] = {st.x, st.y, st.z, st.w};
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                if (4 * v + e < b.nbins) b.bin_start[4 * v + e] = s4[e];
+        }
+    }
     // stable order: an agent's slot counts the smaller ids of its bin
     auto end = [&](int k) { return (int)(lb[k >> 1] >> (k & 1) * 16 & 0xffffu); };
 #pragma unroll
@@ -377,7 +380,7 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
     }
 }
 
-__device__ inline void lds_bins_build(const BinParams& b)
+__device__ inline void lds_bins_build(const BinParams b)      // by value: not reloaded after the stores
 {
     static_assert(kLdsBins == 4 * kLdsTile, "at most four tiles");
     if (b.nbins <= kLdsTile) lds_bins_tiles<1>(b);

@@ -1162,7 +1162,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
                 st->drops = 0;
                 st->drops_total += D;
                 if (!st->done && nline > 0) {
-                    const BarrierParams& Bb = S.bar;     // read only while a barrier is built
+                    const BarrierParams Bb = S.bar;      // by value, read only while a barrier is built
                     int bags = st->bags + D;
                     int cell = st->active_cell, layers = st->layers_done, fin = 0;
                     while (!fin && bags >= Bb.bags_per) {

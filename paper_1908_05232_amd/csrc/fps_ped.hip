@@ -1046,12 +1046,15 @@ void launch_ped_lanes(const Batch& b, hipStream_t s)
 }  // namespace
 
 // Lanes per agent, by measurement: 16 for small crowds (latency bound: the
-// lanes share an agent's neighbour and obstacle loops), 4 up to 2^18 agents
-// (the 64-scenario sweep with 170 k agents: 58 us per step against 66 with
-// 1 lane and 88 with 16), then 1, where the agents' own work fills the chip.
+// lanes share an agent's neighbour and obstacle loops; a whole step with 4 and
+// with 16 lanes: 10,000 agents on 512^2 cells 44.8 and 40.4 us, 20,000 on
+// 1024^2 59.2 and 55.8, 45,000 there 64.4 and 64.1, but the 36 sites of 128^2
+// with 36,000 lose 1.8), 4 up to 2^18 agents (the 64-scenario sweep with 170 k
+// agents: 58 us per step against 66 with 1 lane and 88 with 16), then 1, where
+// the agents' own work fills the chip.
 int ped_lanes(int64_t total_agents)
 {
-    return total_agents <= 8192 ? 16 : total_agents <= 262144 ? 4 : 1;
+    return total_agents <= 20480 ? 16 : total_agents <= 262144 ? 4 : 1;
 }
 
 hipError_t launch_ped(const Batch& b, hipStream_t s)
