@@ -83,6 +83,7 @@ struct Engine {
     hipStream_t stream = nullptr;   // the caller's stream
     hipStream_t cap = nullptr;      // internal stream for graph capture and replay
     hipEvent_t ev_in = nullptr, ev_out = nullptr;
+    DiagRec* polled = nullptr;      // host memory the device writes, one record per member
     std::vector<fps_sim*> m;
     Scn* scn_d = nullptr;
     int* tile_off_d = nullptr;
@@ -817,6 +818,7 @@ void destroy_engine(Engine* e)
     }
     if (e->ev_in) (void)hipEventDestroy(e->ev_in);
     if (e->ev_out) (void)hipEventDestroy(e->ev_out);
+    if (e->polled) (void)hipHostFree(e->polled);
     for (fps_sim* s : e->m) delete s;
     e->m.clear();
 }
@@ -857,6 +859,8 @@ int build_engine(Engine* e, int32_t S, const fps_grid_desc* descs, const fps_ped
     o += align256(sizeof(int) * (S + 1));
     e->chunk_off_d = at<int>(ws, o);
     o += align256(sizeof(int) * (S + 1));
+    HIPCHK_E(e, hipHostMalloc(reinterpret_cast<void**>(&e->polled), sizeof(DiagRec) * (size_t)S,
+                              hipHostMallocPortable | hipHostMallocMapped));
     const int rows = fv_rows_per_wave(descs, S);
     for (int k = 0; k < S; ++k) {
         fps_ped_params P;
@@ -1563,13 +1567,11 @@ int fps_get_diag(fps_sim* s, fps_diag* out)
 {
     if (!s || !out) return fail(s, FPS_E_INVALID, "fps_get_diag: NULL argument");
     hipStream_t st = s->eng->stream;
-    HIPCHK(s, launch_fill_i32(s->stats, 0, 16, st));
-    if (s->na > 0) HIPCHK(s, launch_agent_stats(s->state, s->cls, s->na, s->stats, st));
-    DevState d;
-    int32_t stats[16];
-    HIPCHK(s, hipMemcpyAsync(&d, s->st, sizeof(d), hipMemcpyDeviceToHost, st));
-    HIPCHK(s, hipMemcpyAsync(stats, s->stats, sizeof(stats), hipMemcpyDeviceToHost, st));
+    DiagRec* const rec = s->eng->polled + s->idx;
+    HIPCHK(s, launch_diag(s->state, s->cls, s->na, s->stats, s->st, rec, st));
     HIPCHK(s, hipStreamSynchronize(st));
+    const DevState& d = rec->st;
+    const int32_t* const stats = rec->n;
     std::memset(out, 0, sizeof(*out));
     out->t = d.t;
     out->step = d.step;
@@ -1606,13 +1608,11 @@ int fps_get_time(fps_sim* s, double* t, double* dt_next)
 {
     if (!s || !t || !dt_next) return fail(s, FPS_E_INVALID, "fps_get_time: NULL argument");
     hipStream_t st = s->eng->stream;
-    double tt = 0.0;
-    float dt = 0.0f;
-    HIPCHK(s, hipMemcpyAsync(&tt, &s->st->t, sizeof(tt), hipMemcpyDeviceToHost, st));
-    HIPCHK(s, hipMemcpyAsync(&dt, &s->st->dt, sizeof(dt), hipMemcpyDeviceToHost, st));
+    DiagRec* const rec = s->eng->polled + s->idx;
+    HIPCHK(s, launch_diag(nullptr, nullptr, 0, s->stats, s->st, rec, st));
     HIPCHK(s, hipStreamSynchronize(st));
-    *t = tt;
-    *dt_next = dt;
+    *t = rec->st.t;
+    *dt_next = rec->st.dt;
     return FPS_OK;
 }
 

@@ -38,6 +38,7 @@ constexpr int kCodeDest = 16;          // destinations whose direction codes are
 constexpr int kChunkBins = 4096;       // bins per block of the multi-block bin scan (256 threads x 16)
 constexpr int kRedMin = 8192;          // flood partials the end-of-step block reads in one round (8 a thread)
 constexpr int kRedTiles = 2048;        // partials of a larger grid added by one block first
+constexpr int kDiagAgents = 16384;     // a poll counts up to this many agents by one block
 constexpr int kMbScanBins = 32768;     // scenarios with more bins scan them with many blocks
 
 // Scalars that live in device memory so that n steps run without the host.
@@ -66,6 +67,12 @@ struct DevState {
     int32_t doors_closed;  // some cell has been wet: no more entries
     int32_t n_outside;     // agents in state OUTSIDE (free slots)
     int64_t door_in, door_out;   // entries and leaves so far
+};
+
+// What a poll reads: the state and the agents per hazard class [0, 6) and state [6, 14).
+struct DiagRec {
+    DevState st;
+    int32_t n[16];
 };
 
 struct FvParams {
@@ -225,8 +232,9 @@ hipError_t launch_count(const BinParams& b, hipStream_t s);      // per-cell eva
 hipError_t launch_fill_i32(int32_t* p, int32_t v, int64_t n, hipStream_t s);
 hipError_t launch_hazard(const float* h, const float* qx, const float* qy, float* hr, int64_t n,
                          float eps, hipStream_t s);
-hipError_t launch_agent_stats(const uint8_t* state, const uint8_t* cls, int na, int32_t* out14,
-                              hipStream_t s);
+// out: host memory the device writes; counts: device scratch of 16 words
+hipError_t launch_diag(const uint8_t* state, const uint8_t* cls, int na, int32_t* counts, const DevState* st,
+                       DiagRec* out, hipStream_t s);
 hipError_t launch_wall_mask(const uint8_t* walk, uint4* mask, int nx, int ny, int Rx, int Ry,
                             hipStream_t s);
 hipError_t launch_nav_codes(const float* dist, const uint8_t* walk, int n_dest, int nx, int ny, float r_arrive,

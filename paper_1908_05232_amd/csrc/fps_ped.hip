@@ -968,6 +968,55 @@ __global__ void agent_stats_kernel(const uint8_t* state, const uint8_t* cls, int
     }
 }
 
+// The record fps_get_diag reads, written to host memory by one block: the
+// state words and the agent counts, counted here (counted NULL) or by the
+// kernel above.  A poll is bound by what the host waits for: one launch and a
+// wait take 14 us (an empty launch and its wait 12), where a fill, the counting
+// kernel and two copies took 40.  A thread's agents are read kPer at a time, all
+// loads before the first ballot; more than kDiagAgents (16 a thread, some 3 us)
+// are counted by many blocks first.
+__global__ __launch_bounds__(kScanThreads) void diag_kernel(const uint8_t* state, const uint8_t* cls, int na,
+                                                            const int32_t* counted, const DevState* st, DiagRec* out)
+{
+    constexpr int kCls = FPS_CLS_UNSTABLE + 1, kCnt = kCls + FPS_ST_OUTSIDE + 1, kPer = 4;
+    constexpr int kWords = (int)(sizeof(DevState) / sizeof(uint32_t));
+    static_assert(kWords <= kScanThreads && kCnt <= 16, "one word a thread");
+    __shared__ int cnt[16];
+    const uint32_t word = reinterpret_cast<const uint32_t*>(st)[threadIdx.x < kWords ? threadIdx.x : 0];
+    if (threadIdx.x < 16) cnt[threadIdx.x] = counted ? counted[threadIdx.x] : 0;
+    __syncthreads();
+    if (!counted) {
+        int sum[kCnt] = {};
+        for (int base = 0; base < na; base += kPer * kScanThreads) {
+            int sv[kPer], cv[kPer];
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const int a = base + u * kScanThreads + (int)threadIdx.x, ac = min(a, na - 1);
+                sv[u] = state[ac];
+                cv[u] = cls[ac];
+            }
+#pragma unroll
+            for (int u = 0; u < kPer; ++u) {
+                const bool in = base + u * kScanThreads + (int)threadIdx.x < na;
+                const int s = in ? min(sv[u], (int)FPS_ST_OUTSIDE) : -1;
+                const int c = in && s != FPS_ST_EXITED && s != FPS_ST_OUTSIDE ? min(cv[u], kCls - 1) : -1;
+#pragma unroll
+                for (int k = 0; k < kCls; ++k) sum[k] += __popcll(__ballot(c == k));
+#pragma unroll
+                for (int k = 0; k <= FPS_ST_OUTSIDE; ++k) sum[kCls + k] += __popcll(__ballot(s == k));
+            }
+        }
+        if ((threadIdx.x & (kWave - 1)) == 0) {
+#pragma unroll
+            for (int k = 0; k < kCnt; ++k)
+                if (sum[k]) atomicAdd(&cnt[k], sum[k]);
+        }
+    }
+    if (threadIdx.x < kWords) reinterpret_cast<uint32_t*>(&out->st)[threadIdx.x] = word;
+    __syncthreads();
+    if (threadIdx.x < 16) out->n[threadIdx.x] = cnt[threadIdx.x];
+}
+
 // Per cell, one bit per offset (di, dj) in [-Rx, Rx] x [-Ry, Ry], row-major
 // from (-Rx, -Ry): set where that cell lies in the grid and is not walkable.
 __global__ void wall_mask_kernel(const uint8_t* walk, uint4* mask, int nx, int ny, int Rx, int Ry)
@@ -1158,12 +1207,17 @@ hipError_t launch_hazard(const float* h, const float* qx, const float* qy, float
     hipLaunchKernelGGL(hazard_kernel, dim3(g), dim3(256), 0, s, h, qx, qy, hr, n, eps);
     return hipGetLastError();
 }
-hipError_t launch_agent_stats(const uint8_t* state, const uint8_t* cls, int na, int32_t* out14,
-                              hipStream_t s)
+hipError_t launch_diag(const uint8_t* state, const uint8_t* cls, int na, int32_t* counts, const DevState* st,
+                       DiagRec* out, hipStream_t s)
 {
-    if (na > 0)
-        hipLaunchKernelGGL(agent_stats_kernel, dim3(blocks_for(na, 256)), dim3(256), 0, s, state,
-                           cls, na, out14);
+    const int32_t* counted = nullptr;
+    if (na > kDiagAgents) {
+        hipError_t e = launch_fill_i32(counts, 0, 16, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(agent_stats_kernel, dim3(blocks_for(na, 256)), dim3(256), 0, s, state, cls, na, counts);
+        counted = counts;
+    }
+    hipLaunchKernelGGL(diag_kernel, dim3(1), dim3(kScanThreads), 0, s, state, cls, na, counted, st, out);
     return hipGetLastError();
 }
 hipError_t launch_wall_mask(const uint8_t* walk, uint4* mask, int nx, int ny, int Rx, int Ry,
