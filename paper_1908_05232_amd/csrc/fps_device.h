@@ -7,7 +7,6 @@
 // Pointers read from memory are generic (flat) to the compiler; a cast to
 // the global address space makes their loads and stores global_* ones, which
 // wait on the vector-memory counter only.
-#define FPS_GLOBAL __attribute__((address_space(1)))
 template <class T>
 __device__ __forceinline__ FPS_GLOBAL T* gmem(T* p)
 {
@@ -15,6 +14,12 @@ __device__ __forceinline__ FPS_GLOBAL T* gmem(T* p)
 }
 
 namespace fps {
+
+// 8 and 16 bytes of global memory in one access
+typedef float Float2 __attribute__((ext_vector_type(2)));
+typedef double Double2 __attribute__((ext_vector_type(2)));
+typedef int Int4 __attribute__((ext_vector_type(4)));
+typedef unsigned UInt4 __attribute__((ext_vector_type(4)));
 
 // Scenario owning flattened index g: the largest s with off[s] <= g (off has
 // S + 1 entries, non-decreasing).  Called with wave-uniform arguments.
@@ -61,7 +66,8 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
 // (fps_set_flood_frozen: the pedestrians walk on a flood state set from
 // outside).  Every kernel of the step evaluates this on the same device state
 // before the finalize changes it.
-__device__ __forceinline__ bool flood_skipped(const DevState* st)
+template <class St>      // DevState, in global memory or LDS
+__device__ __forceinline__ bool flood_skipped(const St* st)
 {
     return st->frozen || (st->settled && !st->any_wet && st->inc == 0.0f);
 }
@@ -116,7 +122,7 @@ __device__ inline void block_scan_bins(const BinParams& b)
             if (k0 + IPT <= b.nbins) {
 #pragma unroll
                 for (int q = 0; q < IPT / 4; ++q) {
-                    const int4 w = *reinterpret_cast<const int4*>(b.bin_count + k0 + 4 * q);
+                    const Int4 w = *(FPS_GLOBAL const Int4*)&b.bin_count[k0 + 4 * q];
                     v[t][4 * q] = w.x; v[t][4 * q + 1] = w.y; v[t][4 * q + 2] = w.z; v[t][4 * q + 3] = w.w;
                 }
             } else {
@@ -130,7 +136,7 @@ __device__ inline void block_scan_bins(const BinParams& b)
             if (k0 + IPT <= b.nbins) {
 #pragma unroll
                 for (int q = 0; q < IPT / 4; ++q)
-                    *reinterpret_cast<int4*>(b.bin_count + k0 + 4 * q) = make_int4(0, 0, 0, 0);
+                    *(FPS_GLOBAL Int4*)&b.bin_count[k0 + 4 * q] = Int4{0, 0, 0, 0};
             } else {
                 for (int e = 0; e < IPT; ++e)
                     if (k0 + e < b.nbins) b.bin_count[k0 + e] = 0;
@@ -156,12 +162,12 @@ __device__ inline void block_scan_bins(const BinParams& b)
             if (k0 + IPT <= b.nbins) {
 #pragma unroll
                 for (int q = 0; q < IPT / 4; ++q) {
-                    int4 w;
+                    Int4 w;
                     w.x = run; run += v[t][4 * q];
                     w.y = run; run += v[t][4 * q + 1];
                     w.z = run; run += v[t][4 * q + 2];
                     w.w = run; run += v[t][4 * q + 3];
-                    *reinterpret_cast<int4*>(b.bin_start + k0 + 4 * q) = w;
+                    *(FPS_GLOBAL Int4*)&b.bin_start[k0 + 4 * q] = w;
                 }
             } else {
                 for (int e = 0; e < IPT; ++e) {
@@ -224,7 +230,7 @@ __device__ inline void place_agent(const BinParams& b, int a)
         b.slot[a] = -1;
     } else {
         b.slot[a] = s0;
-        b.xy[s0] = make_float2(x, y);
+        *(FPS_GLOBAL Float2*)&b.xy[s0] = Float2{x, y};
     }
 }
 __device__ inline void sort_agent(const BinParams& b, int a)
@@ -236,7 +242,7 @@ __device__ inline void sort_agent(const BinParams& b, int a)
     for (int s = s0; s < s1; ++s) below += b.perm_u[s] < a;
     const int f = s0 + below;
     b.slot[a] = f;
-    b.xy[f] = make_float2(b.x[a], b.y[a]);
+    *(FPS_GLOBAL Float2*)&b.xy[f] = Float2{b.x[a], b.y[a]};
 }
 
 // One-block binning in LDS (at most kLdsBins bins and kLdsAgents agents), run
@@ -354,14 +360,13 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
     // (65,536 bins: 17.2 us a launch against 13.3)
     for (int v = threadIdx.x; v < (b.nbins + 3) / 4; v += kScanThreads) {
         const uint32_t w0 = v > 0 ? lb[2 * v - 1] >> 16 : 0u, w1 = lb[2 * v], w2 = lb[2 * v + 1];
-        const int4 st = make_int4((int)w0, (int)(w1 & 0xffffu), (int)(w1 >> 16), (int)(w2 & 0xffffu));
+        const Int4 st = {(int)w0, (int)(w1 & 0xffffu), (int)(w1 >> 16), (int)(w2 & 0xffffu)};
         if (4 * v + 4 <= b.nbins) {
-            reinterpret_cast<int4*>(b.bin_start)[v] = st;
+            *(FPS_GLOBAL Int4*)&b.bin_start[4 * v] = st;
         } else {
-            const int s4[4] = {st.x, st.y, st.z, st.w};
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (4 * v + e < b.nbins) b.bin_start[4 * v + e] = s4[e];
+                if (4 * v + e < b.nbins) b.bin_start[4 * v + e] = st[e];
         }
     }
     // stable order: an agent's slot counts the smaller ids of its bin
@@ -376,7 +381,7 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
         for (int s = s0; s < s1; ++s) below += lp[s] < a;
         const int f = s0 + below;
         b.slot[a] = f;
-        b.xy[f] = make_float2(ax[q], ay[q]);
+        *(FPS_GLOBAL Float2*)&b.xy[f] = Float2{ax[q], ay[q]};
     }
 }
 

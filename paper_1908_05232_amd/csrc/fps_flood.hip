@@ -337,7 +337,7 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
     // stores of the march (which the compiler cannot tell apart from them)
     const FvParams p = scn_at<kOne>(B, sc).fv;
     if (tile >= p.ntiles) return;
-    DevState* st = p.st;
+    const FPS_GLOBAL DevState* st = gmem(p.st);
     if (!st->active || flood_skipped(st)) return;
     // the state words are read through a generic pointer: make them wave-uniform
     // so that the buffer selects below are scalar
@@ -620,7 +620,7 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
     }
     const FvParams p = scn_at<kOne>(B, sc).fv;
     if (tile >= p.ntiles) return;
-    DevState* st = p.st;
+    const FPS_GLOBAL DevState* st = gmem(p.st);
     if (!st->active || flood_skipped(st)) return;
     const int cur = __builtin_amdgcn_readfirstlane(st->cur);
     const Src s0{gmem<const float>(cur ? p.h[1] : p.h[0]), gmem<const float>(cur ? p.qx[1] : p.qx[0]),
@@ -1012,9 +1012,9 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     // the parameters used, in registers: loaded in the first round, not
     // reloaded after the stores below
     const FvParams& p = S.fv;
-    DevState* gst = p.st;
-    const double* partials = p.partials;
-    int32_t* wet = p.wet;
+    FPS_GLOBAL DevState* gst = gmem(p.st);
+    const FPS_GLOBAL double* partials = gmem(p.partials);
+    FPS_GLOBAL int32_t* wet = gmem(p.wet);
     // partials of a large grid were added by chunks into every kRedTiles-th one
     const int every = p.ntiles > kRedMin ? kRedTiles : 1;
     const int ntiles = (p.ntiles + every - 1) / every, n_inflow = p.n_inflow, inflow_side = p.inflow_side;
@@ -1045,14 +1045,14 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     // load under a condition makes the compiler wait for it before the
     // lanes that skip it may touch its register.
     const int cw = threadIdx.x < kHyd0 ? (int)threadIdx.x : (int)threadIdx.x - kHyd0 + kHyd1;
-    const uint32_t word = reinterpret_cast<const uint32_t*>(gst)[threadIdx.x < kCopy ? cw : 0];
+    const uint32_t word = ((const FPS_GLOBAL uint32_t*)gst)[threadIdx.x < kCopy ? cw : 0];
     const double hk_t = gst->hyd_t[lane], hk_q = gst->hyd_q[lane];
     // the flood partials summed in tile order
     double m = 0.0, vo = 0.0, vc = 0.0, sm = 0.0;
     {
         constexpr int kPU = 8;
-        const double2* P2 = reinterpret_cast<const double2*>(partials);
-        double2 a[kPU], c[kPU];
+        const FPS_GLOBAL Double2* P2 = (const FPS_GLOBAL Double2*)partials;
+        Double2 a[kPU], c[kPU];
 #pragma unroll
         for (int u = 0; u < kPU; ++u) {
             const int b = threadIdx.x + u * kScanThreads, bc = (b < ntiles ? b : 0) * every;
@@ -1070,7 +1070,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
             }
         }
         for (int b = threadIdx.x + kPU * kScanThreads; b < ntiles; b += kScanThreads) {
-            const double* q = partials + 4 * (size_t)b * every;
+            const FPS_GLOBAL double* q = partials + 4 * (size_t)b * every;
             m += q[0];
             vo += q[1];
             vc += q[2];
@@ -1187,7 +1187,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     }
     __syncthreads();
     if (threadIdx.x < kCopy)
-        reinterpret_cast<uint32_t*>(gst)[cw] = reinterpret_cast<const uint32_t*>(&sst)[cw];
+        ((FPS_GLOBAL uint32_t*)gst)[cw] = reinterpret_cast<const uint32_t*>(&sst)[cw];
     if (mode == 0 && na > 0 && !lds_bins) {
         const BinParams bp = S.bins;
         if (bp.nchunk > 0) {

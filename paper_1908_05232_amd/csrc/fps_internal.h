@@ -100,31 +100,52 @@ struct FvParams {
     int jb, jbx, jby;
 };
 
+// A pointer of a parameter record.  Read from memory, as the records of an
+// ensemble are, a plain pointer is a generic one to the compiler, and a flat
+// load also counts as an LDS access: the first use of any waits for all of them.
+// Its elements lie in global memory.
+#define FPS_GLOBAL __attribute__((address_space(1)))
+template <class T>
+struct GlobalPtr {
+    T* p;
+    GlobalPtr& operator=(T* q)
+    {
+        p = q;
+        return *this;
+    }
+    __host__ __device__ operator T*() const { return p; }
+    template <class I>
+    __device__ __forceinline__ FPS_GLOBAL T& operator[](I i) const
+    {
+        return ((FPS_GLOBAL T*)p)[i];
+    }
+};
+
 struct PedParams {
-    float* x;
-    float* y;
-    float* vx;
-    float* vy;
-    const float* vbase;
-    const uint8_t* role;
-    uint8_t* state;
-    uint8_t* cls;
-    int32_t* dest;
-    float* timer;
+    GlobalPtr<float> x;
+    GlobalPtr<float> y;
+    GlobalPtr<float> vx;
+    GlobalPtr<float> vy;
+    GlobalPtr<const float> vbase;
+    GlobalPtr<const uint8_t> role;
+    GlobalPtr<uint8_t> state;
+    GlobalPtr<uint8_t> cls;
+    GlobalPtr<int32_t> dest;
+    GlobalPtr<float> timer;
     int na;
-    int32_t* np;
-    const float* dist;
-    const uint8_t* walk;
+    GlobalPtr<int32_t> np;
+    GlobalPtr<const float> dist;
+    GlobalPtr<const uint8_t> walk;
     int n_dest, n_exit;
-    const int32_t* bin_start;   // bins of the positions at the start of the step
-    const float2* xy;           // positions in bin order
-    const int32_t* slot;        // each agent's place in that order
-    const uint4* wmask;         // per cell: obstacle cells within r_cut (bit per offset)
-    const uint8_t* codes;       // [n_dest][ny][nx]: heading (bits 0-3) and arrival (bit 4) per destination and cell
+    GlobalPtr<const int32_t> bin_start;   // bins of the positions at the start of the step
+    GlobalPtr<const float2> xy;           // positions in bin order
+    GlobalPtr<const int32_t> slot;        // each agent's place in that order
+    GlobalPtr<const uint4> wmask;         // per cell: obstacle cells within r_cut (bit per offset)
+    GlobalPtr<const uint8_t> codes;       // [n_dest][ny][nx]: heading (bits 0-3) and arrival (bit 4) per destination and cell
     int use_codes;              // codes valid (n_dest <= kCodeDest); else the step reads the distances
-    int32_t* bin_count;         // histogram of the new positions
-    int32_t* rank;
-    int32_t* key;
+    GlobalPtr<int32_t> bin_count;         // histogram of the new positions
+    GlobalPtr<int32_t> rank;
+    GlobalPtr<int32_t> key;
     int nx, ny, bsx, bsy, nbx, nby, Rx, Ry;
     int use_wmask;              // masks valid: (2Rx+1)(2Ry+1) <= 128
     float dx, dy, eps, tau, a_over_m, inv_b, two_r, radius, r_cut, r_arrive;
@@ -132,12 +153,12 @@ struct PedParams {
     int storage_dest, barrier_dest;
     int need_rank;              // histogram + each agent's rank in its bin (the global binning needs them)
     // pre-flood door flow: door cells [0, kMaxDoor) then their destinations [kMaxDoor, 2 kMaxDoor)
-    const int32_t* doors;
+    GlobalPtr<const int32_t> doors;
     int n_door, door_rate;
     uint64_t door_seed;
     // stability rule: bodies (NULL: body_h0 / body_m0 for everyone) and constants
-    const float* body_h;
-    const float* body_m;
+    GlobalPtr<const float> body_h;
+    GlobalPtr<const float> body_m;
     int stab;
     float stab_kd, stab_mu, stab_rw, stab_rb, stab_g, body_h0, body_m0;   // kd = rho_w c_drag / 2
     // wading rule: the speed cap sqrt(wade_k W' / (kd b h))
@@ -154,19 +175,19 @@ struct BarrierParams {
 };
 
 struct BinParams {
-    const float* x;
-    const float* y;
-    const uint8_t* state;
-    const uint8_t* role;
-    int32_t* bin_count;
-    int32_t* bin_start;
-    int32_t* rank;
-    int32_t* key;
-    int32_t* perm_u;
-    float2* xy;
-    int32_t* slot;
-    int32_t* np;
-    int32_t* csum;     // multi-block scan: per chunk of kChunkBins bins its count, then its offset; [nchunk]: active flag
+    GlobalPtr<const float> x;
+    GlobalPtr<const float> y;
+    GlobalPtr<const uint8_t> state;
+    GlobalPtr<const uint8_t> role;
+    GlobalPtr<int32_t> bin_count;
+    GlobalPtr<int32_t> bin_start;
+    GlobalPtr<int32_t> rank;
+    GlobalPtr<int32_t> key;
+    GlobalPtr<int32_t> perm_u;
+    GlobalPtr<float2> xy;
+    GlobalPtr<int32_t> slot;
+    GlobalPtr<int32_t> np;
+    GlobalPtr<int32_t> csum;     // multi-block scan: per chunk of kChunkBins bins its count, then its offset; [nchunk]: active flag
     int na, nbins, nx, ny, bsx, bsy, nbx;
     int nchunk;        // chunks of the multi-block scan (0: the bins are scanned by one block)
     float dx, dy;

@@ -196,8 +196,8 @@ __device__ __forceinline__ AgentRec load_agent(const PedParams& p, int a)
 // cell); the cells of the move.  Cell and bin indices use IEEE
 // division so they match the FP32 decisions of the oracle exactly.
 template <int L>
-__device__ void agent_step(const PedParams& p, const AgentRec& rec, const float* __restrict__ fh,
-                           const float* __restrict__ fqx, const float* __restrict__ fqy, int a, int q,
+__device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GLOBAL float* __restrict__ fh,
+                           const FPS_GLOBAL float* __restrict__ fqx, const FPS_GLOBAL float* __restrict__ fqy, int a, int q,
                            float dt, int any_wet, int done, int& drop, int& left)
 {
     const bool lead = q == 0;
@@ -261,8 +261,8 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const float*
     // A 32 x 32 -> 64-bit product: the 64 x 64 one leaves its upper addend
     // undefined, and the register chosen for it can be a load still in flight
     const uint64_t doff = (uint64_t)(uint32_t)(moving ? dest : 0) * (uint64_t)(uint32_t)nc;
-    const float* D = p.dist + doff;
-    const uint8_t* K = p.codes + doff;
+    const FPS_GLOBAL float* D = &p.dist[doff];
+    const FPS_GLOBAL uint8_t* K = &p.codes[doff];
     const float h = fh[c];
     float qxc = 0.0f, qyc = 0.0f;     // the cell's discharge: this round with several lanes per agent
     if constexpr (L > 1) {
@@ -270,16 +270,16 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const float*
         qyc = fqy[c];
     }
     const int kc = moving && p.use_codes ? (int)K[c] : 0;       // the cell's code of the destination
-    uint4 m4 = make_uint4(0, 0, 0, 0);
+    UInt4 m4 = {0, 0, 0, 0};
     if (p.use_wmask) {
         // with one lane per agent (many agents: the step is bound by memory
         // traffic) the obstacle mask is read only where the code says an
         // obstacle is near, a round later; with several lanes (few agents:
         // bound by latency) it goes out with this round
         if constexpr (L == 1) {
-            if (!(kc & kCodeClear)) m4 = p.wmask[c];
+            if (!(kc & kCodeClear)) m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
         } else {
-            m4 = p.wmask[c];
+            m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
         }
     }
     const int bi = ci / p.bsx, bj = cj / p.bsy;
@@ -391,14 +391,14 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const float*
         const int ntot = n01 + seg1[2] - seg0[2];
         for (int k0 = 0; k0 < ntot; k0 += U * kSlots) {
             int sl[U][J];
-            float2 o[U][J];
+            Float2 o[U][J];
 #pragma unroll
             for (int u = 0; u < U; ++u)
 #pragma unroll
                 for (int j = 0; j < J; ++j) {
                     const int kk = k0 + u * kSlots + q + j * L;
                     sl[u][j] = kk < n0 ? seg0[0] + kk : kk < n01 ? seg0[1] + (kk - n0) : seg0[2] + (kk - n01);
-                    o[u][j] = kk < ntot ? p.xy[sl[u][j]] : make_float2(x, y);
+                    o[u][j] = kk < ntot ? *(FPS_GLOBAL const Float2*)&p.xy[sl[u][j]] : Float2{x, y};
                 }
 #pragma unroll
             for (int u = 0; u < U; ++u)
@@ -568,15 +568,15 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const float*
     const size_t cn = (size_t)nj * p.nx + ni;
     const bool was = role == FPS_ROLE_EVACUEE && st0 == FPS_ST_EVAC;
     const bool now = role == FPS_ROLE_EVACUEE && st == FPS_ST_EVAC;
-    if (was && !(now && cn == c)) atomicSub(&p.np[c], 1);
-    if (now && !(was && cn == c)) atomicAdd(&p.np[cn], 1);
+    if (was && !(now && cn == c)) atomicSub((int32_t*)&p.np[c], 1);
+    if (now && !(was && cn == c)) atomicAdd((int32_t*)&p.np[cn], 1);
     // bin key of the new position; the global binning also needs the
     // histogram and each agent's rank in its bin (the LDS binning counts the
     // keys itself)
     if (st != FPS_ST_EXITED && st != FPS_ST_OUTSIDE) {
         int b = (nj / p.bsy) * p.nbx + ni / p.bsx;
         p.key[a] = b;
-        if (p.need_rank) p.rank[a] = atomicAdd(&p.bin_count[b], 1);
+        if (p.need_rank) p.rank[a] = atomicAdd((int32_t*)&p.bin_count[b], 1);
     } else {
         p.key[a] = -1;
     }
@@ -598,7 +598,7 @@ __global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
     // the agent's record in the same round of loads as the scenario's state words
     AgentRec rec{};
     if (a < S.na) rec = load_agent(P, a);
-    const DevState* st = S.fv.st;
+    const FPS_GLOBAL DevState* st = gmem(S.fv.st);
     if (!st->active) return;
     const bool skipped = flood_skipped(st);
     // the flood state this step's pedestrians see: the new one, or the
@@ -609,11 +609,11 @@ __global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
     // evacuation trigger: some cell is wet after this step's flood update
     // one wetness flag per lane (the flood update sets them per group of blocks)
     // (a skipped update left the state, and its wetness, as they were)
-    const int wet = skipped ? st->any_wet : (__ballot(S.fv.wet[kWetStride * threadIdx.x] != 0) != 0ull);
+    const int wet = skipped ? st->any_wet : (__ballot(gmem(S.fv.wet)[kWetStride * threadIdx.x] != 0) != 0ull);
     int drop = 0, left = 0;
     if (a < S.na)
-        agent_step<L>(P, rec, fb ? S.fv.h[1] : S.fv.h[0], fb ? S.fv.qx[1] : S.fv.qx[0], fb ? S.fv.qy[1] : S.fv.qy[0],
-                   a, q, dt, wet, done, drop, left);
+        agent_step<L>(P, rec, gmem(fb ? S.fv.h[1] : S.fv.h[0]), gmem(fb ? S.fv.qx[1] : S.fv.qx[0]),
+                      gmem(fb ? S.fv.qy[1] : S.fv.qy[0]), a, q, dt, wet, done, drop, left);
     // one wave per block: the sandbag drops of the wave (lane 0 of each
     // group), one atomic; the agent-steps of the step are the agents that
     // start it outside the exits, which the bins hold: one add per scenario,
@@ -621,13 +621,13 @@ __global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
     const unsigned long long drops = __popcll(__ballot(drop && q == 0));
     const unsigned long long leaves = __popcll(__ballot(left && q == 0));
     if (threadIdx.x == 0) {
-        DevState* stw = S.fv.st;
-        if (drops) atomicAdd(&stw->drops, (int)drops);
+        FPS_GLOBAL DevState* stw = gmem(S.fv.st);
+        if (drops) atomicAdd((int32_t*)&stw->drops, (int)drops);
         if (leaves) {
-            atomicAdd(&stw->n_outside, (int)leaves);
-            atomicAdd(reinterpret_cast<unsigned long long*>(&stw->door_out), leaves);
+            atomicAdd((int32_t*)&stw->n_outside, (int)leaves);
+            atomicAdd((unsigned long long*)&stw->door_out, leaves);
         }
-        if (a == 0) atomicAdd(&stw->ped_steps, (unsigned long long)P.bin_start[P.nbx * P.nby]);
+        if (a == 0) atomicAdd((unsigned long long*)&stw->ped_steps, (unsigned long long)P.bin_start[P.nbx * P.nby]);
     }
 }
 
@@ -725,7 +725,7 @@ __global__ __launch_bounds__(kScanThreads) void door_kernel(Batch B)
                 P.dest[a] = P.doors[kMaxDoor + leave];
                 const int b = (cj / P.bsy) * P.nbx + ci / P.bsx;
                 P.key[a] = b;
-                if (P.need_rank) P.rank[a] = atomicAdd(&P.bin_count[b], 1);
+                if (P.need_rank) P.rank[a] = atomicAdd((int32_t*)&P.bin_count[b], 1);
             }
         }
         __syncthreads();
@@ -765,7 +765,7 @@ __global__ void bin_keys_kernel(BinParams b)
     int cj = clampi(cell_of(b.y[a], b.dy, b.ny), 0, b.ny - 1);
     int k = (cj / b.bsy) * b.nbx + ci / b.bsx;
     b.key[a] = k;
-    b.rank[a] = atomicAdd(&b.bin_count[k], 1);
+    b.rank[a] = atomicAdd((int32_t*)&b.bin_count[k], 1);
 }
 
 __global__ __launch_bounds__(kScanThreads) void bin_scan_kernel(BinParams b) { block_scan_bins(b); }
@@ -827,7 +827,7 @@ __device__ __forceinline__ void chunk_counts(const BinParams& b, int k0, int (&v
     if (k0 + 16 <= b.nbins) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            const int4 w = *reinterpret_cast<const int4*>(b.bin_count + k0 + 4 * q);
+            const Int4 w = *(FPS_GLOBAL const Int4*)&b.bin_count[k0 + 4 * q];
             v[4 * q] = w.x; v[4 * q + 1] = w.y; v[4 * q + 2] = w.z; v[4 * q + 3] = w.w;
         }
     } else {
@@ -878,7 +878,7 @@ __global__ __launch_bounds__(kChunkThreads) void bin_chunk_scan_kernel(Batch B)
     const bool full = k0 + 16 <= b.nbins;
     if (full) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) *reinterpret_cast<int4*>(b.bin_count + k0 + 4 * q) = make_int4(0, 0, 0, 0);
+        for (int q = 0; q < 4; ++q) *(FPS_GLOBAL Int4*)&b.bin_count[k0 + 4 * q] = Int4{0, 0, 0, 0};
     } else {
         for (int e = 0; e < 16; ++e)
             if (k0 + e < b.nbins) b.bin_count[k0 + e] = 0;
@@ -894,12 +894,12 @@ __global__ __launch_bounds__(kChunkThreads) void bin_chunk_scan_kernel(Batch B)
     if (full) {
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-            int4 w;
+            Int4 w;
             w.x = run; run += v[4 * q];
             w.y = run; run += v[4 * q + 1];
             w.z = run; run += v[4 * q + 2];
             w.w = run; run += v[4 * q + 3];
-            *reinterpret_cast<int4*>(b.bin_start + k0 + 4 * q) = w;
+            *(FPS_GLOBAL Int4*)&b.bin_start[k0 + 4 * q] = w;
         }
     } else {
         for (int e = 0; e < 16; ++e) {
@@ -924,7 +924,7 @@ __global__ void count_kernel(BinParams b)
     if (b.role[a] != FPS_ROLE_EVACUEE || b.state[a] != FPS_ST_EVAC) return;
     int ci = clampi(cell_of(b.x[a], b.dx, b.nx), 0, b.nx - 1);
     int cj = clampi(cell_of(b.y[a], b.dy, b.ny), 0, b.ny - 1);
-    atomicAdd(&b.np[(size_t)cj * b.nx + ci], 1);
+    atomicAdd((int32_t*)&b.np[(size_t)cj * b.nx + ci], 1);
 }
 
 __global__ void fill_i32_kernel(int32_t* p, int32_t v, int64_t n)
