@@ -532,10 +532,12 @@ __global__ __launch_bounds__(kC64Threads) void conv64_kernel(const bf16* __restr
 // up its bias gradient, and between two barriers they store it to LDS.  Every
 // load of a tile goes out before the first wait, dz first (the order x, dz
 // measured 4 us a launch more).
-// Bound by HBM for large inputs (134 MB at 64-64 channels, 8 x 256^2, 45 to
-// 48 us) and by the chain load, transpose, store where a block has few tiles.
-// Measured 64-64 / 64-16 / 16-64 channels: 8 x 256^2 45-48 / 34 / 32 us, as with a
-// slot per image; 3 x 176 x 224 19.9 / 16.6 / 15.3 us (26.8 / 23 / 19.5).
+// What bounds it: HBM while tiles stream (134 MB at 64-64 channels and 8 x 256^2
+// are 27 us; a second set of registers, two tiles in flight, gained nothing),
+// and some 10 us a launch for the first tile and the partials (37.7 MB).
+// Measured 64-64 / 64-16 / 16-64 channels: 8 x 256^2 44.7 / 33.3 / 28.9 us (47 / 35
+// / 33 with plain tile order and a partial for every wave), 3 x 176 x 224 19.5 /
+// 16.2 / 12.9 us (26.8 / 23 / 19.5 with a slot per image besides).
 // ----------------------------------------------------------------------------
 constexpr int WTH = 4, WTW = 8, WNG = 8;      // weight-gradient tile: rows, columns, slots
 // bands of each run: the tiles of the pass are wg_run bands x W / WTW columns
@@ -547,6 +549,23 @@ __host__ __device__ constexpr int wg_ksplit(int cin, int cout) { return kWgWaves
 __host__ __device__ constexpr size_t wg_lds(int cin, int cout)
 {
     return (size_t)16 * (WTH * WTW * (cout + wg_pad(cout)) + (WTH + 2) * (WTW + 2) * (cin + wg_pad(cin)));
+}
+
+// The tiles of a weight-gradient block: first, step, end.  Tiles side by side
+// share two of ten input columns, bands one above the other two of six rows, and
+// blocks go to the 8 XCDs round-robin, each with its own L2: an XCD takes a run of
+// consecutive tiles, its blocks side by side, which leaves one reading of the
+// inputs from HBM.  A grid that is no multiple of 8 takes them in plain order.
+struct WgTiles {
+    int t, step, end;
+};
+__device__ __forceinline__ WgTiles wg_tiles(int ntiles)
+{
+    constexpr int XCDS = 8;
+    const int b = blockIdx.x, blocks = gridDim.x;
+    if (blocks % XCDS) return WgTiles{b, blocks, ntiles};
+    const int chunk = (ntiles + XCDS - 1) / XCDS, x0 = b % XCDS * chunk;
+    return WgTiles{x0 + b / XCDS, blocks / XCDS, min(x0 + chunk, ntiles)};
 }
 
 __device__ __forceinline__ int wg_swz(int c) { return c ^ ((c >> 3) & 7); }
@@ -575,7 +594,8 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
 
     const int wave = threadIdx.x >> 6;
     const int tiles_x = W / WTW, bands_y = H / WTH, nbands = N * bands_y;
-    const int run = (int)wg_run(N, H), ntiles = run * tiles_x;
+    const int run = (int)wg_run(N, H);
+    const WgTiles T = wg_tiles(run * tiles_x);
     float bsum[8] = {};
 
     if (wave >= kWgWaves) {
@@ -669,19 +689,22 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
         };
         // the next tile's loads are issued at barrier A and land during the
         // compute of this one
-        fetch(s0, blockIdx.x);
-        transpose(s0);
-        store(s0);
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        if (T.t < T.end) {
+            fetch(s0, T.t);
+            transpose(s0);
+            store(s0);
+        }
+        for (int t = T.t; t < T.end; t += T.step) {
             __syncthreads();                  // A: tile t is in LDS
-            const int t1 = t + gridDim.x;
-            if (t1 < ntiles) {
+            const int t1 = t + T.step;
+            if (t1 < T.end) {
                 fetch(s0, t1);
                 transpose(s0);
             }
             __syncthreads();                  // B: the compute waves are done with tile t
-            if (t1 < ntiles) store(s0);
+            if (t1 < T.end) store(s0);
         }
+        if constexpr (KS > 1) __syncthreads();      // C
     } else {
         // ---- compute waves
         const int lane = threadIdx.x & 63;
@@ -698,7 +721,7 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
 #pragma unroll
         for (int j = 0; j < CO_PER; ++j) co_sw[j] = wg_swz(16 * (cp * CO_PER + j) + row16);
         const int c0 = ks * CPW;
-        for (int t = blockIdx.x; t < ntiles; t += gridDim.x) {
+        for (int t = T.t; t < T.end; t += T.step) {
             __syncthreads();                  // A
             // window of input columns: win[dy][k % 3] holds halo column c0 + k, rows kgrp + dy
             bf16x8 win[3][3];
@@ -725,16 +748,35 @@ __global__ __launch_bounds__(kWgThreads) void wgrad_kernel(const bf16* __restric
             }
             __syncthreads();                  // B
         }
-        // partial [block * KS + ks][co][tap][ci]; D tile lane holds rows (co) 4*kgrp + r, column (ci) row16
-        float* pb = part + ((size_t)blockIdx.x * KS + ks) * COUT * 9 * CIN;
+        // Waves that split the columns add their sums in LDS, wave w those of
+        // output tile w, in the order of the columns: a partial for each wave was
+        // four times the bytes to write and to read again.
+        if constexpr (KS > 1) {
+            static_assert(KS == CO_PER && G == 1, "an output tile a wave");
+            f32x4* sums = reinterpret_cast<f32x4*>(smem) + lane;
+#pragma unroll
+            for (int j = 0; j < CO_PER; ++j)
+#pragma unroll
+                for (int tap = 0; tap < 9; ++tap) sums[((ks * CO_PER + j) * 9 + tap) * 64] = acc[j][tap];
+            __syncthreads();                  // C
+#pragma unroll
+            for (int tap = 0; tap < 9; ++tap) {
+                f32x4 v = sums[(ks * 9 + tap) * 64];
+#pragma unroll
+                for (int k = 1; k < KS; ++k) v += sums[((k * CO_PER + ks) * 9 + tap) * 64];
+                acc[0][tap] = v;
+            }
+        }
+        // partial [block][co][tap][ci]; D tile lane holds rows (co) 4*kgrp + r, column (ci) row16
+        float* pb = part + (size_t)blockIdx.x * COUT * 9 * CIN;
         const int ci = 16 * ct + row16;
 #pragma unroll
-        for (int j = 0; j < CO_PER; ++j)
+        for (int j = 0; j < (KS > 1 ? 1 : CO_PER); ++j)
 #pragma unroll
             for (int tap = 0; tap < 9; ++tap)
 #pragma unroll
                 for (int r = 0; r < 4; ++r) {
-                    const int co = 16 * (cp * CO_PER + j) + 4 * kgrp + r;
+                    const int co = 16 * (KS > 1 ? ks : cp * CO_PER + j) + 4 * kgrp + r;
                     pb[((size_t)co * 9 + tap) * CIN + ci] = acc[j][tap][r];
                 }
     }
@@ -1190,25 +1232,36 @@ int conv(fps_sur* s, int n, const bf16* x, const bf16* w, const float* b, void* 
     return FPS_OK;
 }
 
+// Blocks of a weight-gradient pass: persistent, one per compute unit, or fewer
+// when capped or when fewer take as many turns (every block writes a partial of
+// up to 147 KB that the sums read again; 240 of 256 for 3 x 176 x 224); a
+// multiple of 8 for the order of wg_tiles.
+int wg_blocks(const fps_sur* s, int tiles)
+{
+    const int cap = std::min(s->cus, kWgradBlocks);
+    if (s->wgrad_cap > 0 || cap % 8) return std::min(tiles, s->wgrad_cap > 0 ? std::min(s->wgrad_cap, cap) : cap);
+    const int chunk = (tiles + 7) / 8, turns = (chunk + cap / 8 - 1) / (cap / 8);
+    return (chunk + turns - 1) / turns * 8;
+}
+
 // weight and bias gradients of one layer: per-block partials, then the fixed-order sums
 template <int CIN, int COUT>
 int wgrad(fps_sur* s, int n, const bf16* x, const bf16* dz, int layer)
 {
-    const size_t lds = wg_lds(CIN, COUT);
+    // the tiles, or the sums of the waves
+    const size_t lds = std::max(wg_lds(CIN, COUT),
+                                wg_ksplit(CIN, COUT) > 1 ? (size_t)4 * wg_ksplit(CIN, COUT) * COUT * 9 * CIN : 0);
     auto k = wgrad_kernel<CIN, COUT>;
     SCHK(s, hipFuncSetAttribute((const void*)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
     const int tiles = (int)wg_run(n, s->H) * (s->W / WTW);
-    // persistent: one block per compute unit (or fewer, when capped)
-    const int cap = std::min(s->cus, kWgradBlocks);
-    const int blocks = std::min(tiles, s->wgrad_cap > 0 ? std::min(s->wgrad_cap, cap) : cap);
-    const int nparts = blocks * wg_ksplit(CIN, COUT);
+    const int blocks = wg_blocks(s, tiles);
     hipLaunchKernelGGL(k, dim3(blocks), dim3(kWgThreads), lds, s->stream, x, dz, s->wpart, s->bpart, n, s->H,
                        s->W);
     SCHK(s, hipGetLastError());
     const int count = COUT * 9 * CIN;
     float* dw = s->grads + param_offset(layer);
     hipLaunchKernelGGL(reduce_kernel, dim3((count + 63) / 64 + (COUT + 63) / 64), dim3(1024), 0, s->stream,
-                       s->wpart, nparts, count, dw, s->bpart, blocks, COUT, dw + w_count(layer));
+                       s->wpart, blocks, count, dw, s->bpart, blocks, COUT, dw + w_count(layer));
     SCHK(s, hipGetLastError());
     return FPS_OK;
 }

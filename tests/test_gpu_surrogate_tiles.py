@@ -64,3 +64,21 @@ def test_weight_gradient_of_ragged_batches_matches_oracle(n, H, W):
         say(f"{n} x {H} x {W}, layer {li + 1}: dW max|d| / max|ref| {ew:.2e}, db {eb:.2e}")
         assert ew <= ELEM_TOL and eb <= ELEM_TOL
         assert cosine(dw, dwb) >= 0.9999 and rel_l2(dw, dwb) <= 1e-2
+
+
+# 9 bands of 12 tiles: 14 tiles an XCD (the last 10), and grids capped to both orders
+def test_weight_gradient_blocks_only_group_the_sums():
+    params, x, target = make_case(71, 3, 96, 96)
+    p, xt, tt = to_dev(params, x, target)
+    out = []
+    for cap in (0, 8, 16, 7, 100):
+        sur = fps.Surrogate(3, 96, 96)
+        sur.set_params(p)
+        sur.set_blocks(0, cap)
+        out.append(sur.gradients(xt, tt)[1].cpu().numpy().astype(np.float64))
+        sur.close()
+    assert np.abs(out[0]).max() > 0
+    for g in out[1:]:
+        d = float(np.abs(g - out[0]).max() / np.abs(out[0]).max())
+        say(f"max|dg| / max|g| = {d:.2e}")
+        assert d <= 1e-5
