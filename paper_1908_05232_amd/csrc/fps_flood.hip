@@ -1199,17 +1199,35 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
 }
 
 // After the last step of a call: scenarios whose state sits in the scratch
-// buffer copy it back to the caller's buffers (grid: blocks x scenarios).
+// buffer copy it back to the caller's buffers (grid: blocks x scenarios), and
+// the state is in the caller's buffer again.  kCount: the last block of a
+// scenario to be done says so (every block has read `cur` before it counts
+// itself in, and the count ends at 0), which saves a call of one step a launch
+// of 2 us; its grid is small, since the blocks count on one word.  Otherwise a
+// launch of its own follows.
+template <bool kCount>
 __global__ void sync_back_kernel(Batch B)
 {
     const FvParams& p = B.scn[blockIdx.y].fv;
-    if (p.st->cur == 0) return;
+    FPS_GLOBAL DevState* st = gmem(p.st);
+    if (st->cur == 0) return;
     const int64_t nc = (int64_t)p.nx * p.ny;
+    const FPS_GLOBAL float *h = gmem(p.h[1]), *qx = gmem(p.qx[1]), *qy = gmem(p.qy[1]);
+    FPS_GLOBAL float *ho = gmem(p.h[0]), *qxo = gmem(p.qx[0]), *qyo = gmem(p.qy[0]);
     for (int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; k < nc;
          k += (int64_t)gridDim.x * blockDim.x) {
-        p.h[0][k] = p.h[1][k];
-        p.qx[0][k] = p.qx[1][k];
-        p.qy[0][k] = p.qy[1][k];
+        const float a = h[k], b = qx[k], c = qy[k];
+        ho[k] = a;
+        qxo[k] = b;
+        qyo[k] = c;
+    }
+    if constexpr (kCount) {
+        __syncthreads();
+        int32_t* count = p.wet + 1;       // between two wetness flags
+        if (threadIdx.x == 0 && atomicAdd(count, 1) == (int)gridDim.x - 1) {
+            *count = 0;
+            st->cur = 0;
+        }
     }
 }
 __global__ void reset_cur_kernel(Batch B)
@@ -1371,9 +1389,13 @@ hipError_t launch_finalize(const Batch& b, int mode, int s_first, int count, hip
 
 hipError_t launch_sync_back(const Batch& b, int64_t max_cells, hipStream_t s)
 {
-    int gx = (int)std::min<int64_t>((max_cells + 255) / 256, 2048);
-    hipLaunchKernelGGL(sync_back_kernel, dim3(std::max(gx, 1), b.S), dim3(256), 0, s, b);
-    hipLaunchKernelGGL(reset_cur_kernel, dim3(1), dim3(256), 0, s, b);
+    const int64_t need = std::max<int64_t>((max_cells + 255) / 256, 1);
+    if (need <= kSyncCount) {
+        hipLaunchKernelGGL(sync_back_kernel<true>, dim3((unsigned)need, b.S), dim3(256), 0, s, b);
+    } else {
+        hipLaunchKernelGGL(sync_back_kernel<false>, dim3((unsigned)std::min<int64_t>(need, 2048), b.S), dim3(256), 0, s, b);
+        hipLaunchKernelGGL(reset_cur_kernel, dim3(1), dim3(256), 0, s, b);
+    }
     return hipGetLastError();
 }
 

@@ -38,6 +38,7 @@ constexpr int kCodeDest = 16;          // destinations whose direction codes are
 constexpr int kChunkBins = 4096;       // bins per block of the multi-block bin scan (256 threads x 16)
 constexpr int kRedMin = 8192;          // flood partials the end-of-step block reads in one round (8 a thread)
 constexpr int kRedTiles = 2048;        // partials of a larger grid added by one block first
+constexpr int kSyncCount = 64;         // blocks a scenario that count themselves in the copy back
 constexpr int kDiagAgents = 16384;     // a poll counts up to this many agents by one block
 constexpr int kMbScanBins = 32768;     // scenarios with more bins scan them with many blocks
 

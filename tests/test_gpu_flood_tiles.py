@@ -68,3 +68,25 @@ def test_no_counts_equals_zero_counts():
     sim.set_occupancy(None)
     sim.step(4)
     assert all(np.array_equal(a, b) for a, b in zip(plain, sim.fields()))
+
+
+# 64 blocks of 256 cells count themselves in the copy back, 65 leave it to a launch
+@pytest.mark.parametrize("nx,ny", [(16, 16), (128, 128), (129, 128), (300, 200)])
+def test_odd_calls_return_the_state_to_the_callers_buffers(nx, ny):
+    """Calls of one and three steps (the state ends in the scratch buffers)
+    against one call, alone and beside a member that stopped on an odd step."""
+    scs = [random_wet_dry(nx, ny, 0.5, seed=nx + k, bc=BC, inflow=(2, 3, nx // 2)) for k in (0, 1)]
+    whole = _run(scs[0], 1, 12)[1]
+    ens = fps.Ensemble(scs)
+    ens.step(1)
+    ens[1].set_end_time(ens[1].diag()["t"] * 1.5)      # stops in the next step
+    for n in (1, 3, 1, 5, 1):
+        ens.step(n)
+        if n == 3:
+            stopped = ens[1].fields()
+    say(f"{nx} x {ny}: member 1 stopped at step {ens[1].diag()['step']}")
+    assert ens[1].diag()["active"] == 0 and ens[0].diag()["step"] == 12
+    for a, b in zip(ens[0].fields(), whole):
+        assert np.array_equal(a, b)
+    for a, b in zip(ens[1].fields(), stopped):
+        assert np.array_equal(a, b)
