@@ -45,7 +45,7 @@ struct fps_sim {
     int32_t* line;
     int32_t* stats;
     int32_t* doors;            // door cells, then their destinations (kMaxDoor each)
-    int32_t* csum;             // chunk counts / offsets of the multi-block bin scan
+    int32_t* csum;             // chunk counts of the multi-block bin scan
     int32_t line_cap;
     int H;
     int nbins, bsx, bsy, nbx, nby, Rx, Ry;
@@ -380,9 +380,7 @@ void fill_scn(const fps_sim* s, Scn& c)
 
     c.na = s->na;
     c.lds_bins = s->na > 0 && s->na <= kLdsAgents && s->nbins <= kLdsBins;
-    // many bins: scanned by many blocks
-    const bool mb = s->na > 0 && !c.lds_bins && s->nbins > kMbScanBins;
-    b.nchunk = mb ? (s->nbins + kChunkBins - 1) / kChunkBins : 0;
+    b.nchunk = s->na > 0 && !c.lds_bins ? (s->nbins + kChunkBins - 1) / kChunkBins : 0;
     c.ped.need_rank = !c.lds_bins;       // the LDS binning counts the keys itself
 }
 
@@ -525,7 +523,6 @@ int step_launches(Engine* e, hipStream_t st, KernelEvents* K)
     }
     rec(2, 0);
     HIPCHK_E(e, launch_fv_reduce(b, 0, e->S, st));
-    if (e->total_chunks > 0) HIPCHK_E(e, launch_bin_chunk_sum(b, st));
     HIPCHK_E(e, launch_finalize(b, 0, 0, e->S, st));
     if (e->total_chunks > 0) HIPCHK_E(e, launch_bin_chunk_scan(b, st));
     rec(2, 1);

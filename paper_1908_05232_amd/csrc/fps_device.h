@@ -183,33 +183,28 @@ __device__ inline void block_scan_bins(const BinParams& b)
     __syncthreads();
 }
 
-// The middle step of the multi-block bin scan, by the scenario's end-of-step
-// block: the chunk counts (written by the chunk-count launch) become their
-// exclusive offsets in place, one value per thread per round, and the total
-// closes the bin starts.
-__device__ inline void block_scan_chunks(const BinParams& b)
+// The first half of the multi-block bin scan: the count of chunk c, by a block
+// of kScanThreads (four bins a thread).
+__device__ inline void block_chunk_sum(const BinParams b, int c)
 {
-    __shared__ int wtot[kScanThreads / kWave];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
-    int carry = 0;
-    for (int base = 0; base < b.nchunk; base += kScanThreads) {
-        const int i = base + (int)threadIdx.x;
-        const int v = i < b.nchunk ? b.csum[i] : 0;
-        const int incl = wave_inclusive_scan(v);
-        if (lane == kWave - 1) wtot[wid] = incl;
-        __syncthreads();
-        int wbase = 0, total = 0;
-        for (int w = 0; w < kScanThreads / kWave; ++w) {
-            const int x = wtot[w];
-            wbase += w < wid ? x : 0;
-            total += x;
-        }
-        if (i < b.nchunk) b.csum[i] = carry + wbase + incl - v;
-        carry += total;
-        __syncthreads();      // wtot is rewritten by the next round
+    static_assert(kChunkBins == 4 * kScanThreads, "four bins a thread");
+    __shared__ int wt[kScanThreads / kWave];
+    const int k0 = c * kChunkBins + 4 * (int)threadIdx.x;
+    int t = 0;
+    if (k0 + 4 <= b.nbins) {
+        const Int4 w = *(FPS_GLOBAL const Int4*)&b.bin_count[k0];
+        t = w.x + w.y + w.z + w.w;
+    } else {
+        for (int k = k0; k < b.nbins; ++k) t += b.bin_count[k];
     }
-    if (threadIdx.x == 0) b.bin_start[b.nbins] = carry;
+    const int incl = wave_inclusive_scan(t);
+    if ((threadIdx.x & (kWave - 1)) == kWave - 1) wt[threadIdx.x >> 6] = incl;
     __syncthreads();
+    if (threadIdx.x == 0) {
+        int sum = 0;
+        for (int w = 0; w < kScanThreads / kWave; ++w) sum += wt[w];
+        b.csum[c] = sum;
+    }
 }
 
 // Placement of the agents into their bins by rank, then the stable order: an

@@ -992,21 +992,30 @@ __device__ double wave_hydro_integral(int nh, double tk, double qk, double a, do
     return total + readlane_f64(after, nh - 1);
 }
 
-// End of a step: blocks (scenario, 0) update the state, blocks (scenario, 1)
-// rebuild the neighbour bins of scenarios binned in LDS; the two run side by
-// side (they share no data).  The state update reduces the flood partials in
-// a fixed order, advances time, sets the next CFL time step (sec. 3) and
-// inflow depth, applies the sandbag drops of the step to the barrier line
-// (sec. 2.4) and, for scenarios binned in global memory, scans the histogram
-// of the new agent bins, or, for scenarios with many bins, the chunk counts of the
-// multi-block scan.  Mode 1 only recomputes the time step and mass of the current state.
+// End of a step: a row of blocks, one per scenario, updates the states; beside
+// them, a second row rebuilds the neighbour bins of scenarios binned in LDS, and
+// further rows count the chunks of the others (they share no data).  The state update
+// reduces the flood partials in a fixed order, advances time, sets the next CFL
+// time step (sec. 3) and inflow depth, and applies the sandbag drops of the step
+// to the barrier line (sec. 2.4).  Mode 1 only recomputes the time step and mass
+// of the current state, of the scenarios from s_first.
 template <bool kOne>
 __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mode, int s_first)
 {
+    if (blockIdx.y > 1) {
+        const int64_t row = (int64_t)blockIdx.z * ((int)gridDim.y - 2) + (int)blockIdx.y - 2;
+        const int64_t at = row * (int)gridDim.x + (int)blockIdx.x;
+        if (at >= B.total_chunks) return;
+        const int g = (int)at;
+        const int sc = kOne ? 0 : find_scenario(B.chunk_off, B.S, g);
+        block_chunk_sum(scn_at<kOne>(B, sc).bins, g - (kOne ? 0 : B.chunk_off[sc]));
+        return;
+    }
+    if (blockIdx.z > 0) return;
     const int sc = s_first + blockIdx.x;
     const Scn& S = scn_at<kOne>(B, sc);
     if (blockIdx.y == 1) {
-        if (S.lds_bins && S.na > 0) lds_bins_build(S.bins);
+        if (S.lds_bins) lds_bins_build(S.bins);
         return;
     }
     // the parameters used, in registers: loaded in the first round, not
@@ -1021,7 +1030,8 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     const double dxdy = p.dxdy;
     const float cfl = p.cfl, dt_max = p.dt_max, dn = inflow_side <= 1 ? p.dx : p.dy;
     const bool jmask = p.jmask != nullptr;
-    const int na = S.na, lds_bins = S.lds_bins, nline = S.bar.nline;
+    const int na = S.na, nline = S.bar.nline, nchunk = S.bins.nchunk;
+    FPS_GLOBAL int32_t* stepped = gmem(S.bins.csum.p);
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
     // The scenario's state words go through LDS: one cooperative load, the
     // serial end-of-step logic on the copy, one cooperative store.  Nothing
@@ -1079,6 +1089,8 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     }
     __syncthreads();
     DevState* st = &sst;
+    // the chunk scan that follows asks whether this step was one of the scenario
+    if (mode == 0 && nchunk > 0 && threadIdx.x == 0) stepped[nchunk] = st->active;
     if (mode == 0 && !st->active) return;     // the whole block: one LDS word
     const bool skipped = mode == 0 && flood_skipped(st);
     if (skipped) {
@@ -1188,14 +1200,6 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     __syncthreads();
     if (threadIdx.x < kCopy)
         ((FPS_GLOBAL uint32_t*)gst)[cw] = reinterpret_cast<const uint32_t*>(&sst)[cw];
-    if (mode == 0 && na > 0 && !lds_bins) {
-        const BinParams bp = S.bins;
-        if (bp.nchunk > 0) {
-            block_scan_chunks(bp);      // the chunk scans follow in a launch of their own
-        } else {
-            block_scan_bins(bp);
-        }
-    }
 }
 
 // After the last step of a call: scenarios whose state sits in the scratch
@@ -1378,9 +1382,13 @@ hipError_t prepare_finalize(int lds_bytes)
 
 hipError_t launch_finalize(const Batch& b, int mode, int s_first, int count, hipStream_t s)
 {
-    // the binning blocks only where some scenario is binned in LDS
-    const bool bins = mode == 0 && b.fin_lds_bytes > 0;
-    const dim3 grid(count, bins ? 2 : 1);
+    // rows of blocks: the states; after a step, where there are such, the LDS
+    // binnings and then the chunks (the kind by the row: a bound from the
+    // arguments, read first, cost the state update 0.3 us)
+    const int chunks = mode == 0 ? (b.total_chunks + count - 1) / count : 0;
+    const bool bins = mode == 0 && (b.fin_lds_bytes > 0 || chunks > 0);
+    constexpr int kRows = 32768;      // rows of chunks a layer (a grid has at most 65,535)
+    const dim3 grid(count, 1 + (int)bins + std::min(chunks, kRows), std::max((chunks + kRows - 1) / kRows, 1));
     const int lds = bins ? b.fin_lds_bytes : 0;
     if (b.S == 1) hipLaunchKernelGGL(finalize_kernel<true>, grid, dim3(kScanThreads), lds, s, b, mode, s_first);
     else hipLaunchKernelGGL(finalize_kernel<false>, grid, dim3(kScanThreads), lds, s, b, mode, s_first);

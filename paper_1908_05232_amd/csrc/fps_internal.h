@@ -40,7 +40,6 @@ constexpr int kRedMin = 8192;          // flood partials the end-of-step block r
 constexpr int kRedTiles = 2048;        // partials of a larger grid added by one block first
 constexpr int kSyncCount = 64;         // blocks a scenario that count themselves in the copy back
 constexpr int kDiagAgents = 16384;     // a poll counts up to this many agents by one block
-constexpr int kMbScanBins = 32768;     // scenarios with more bins scan them with many blocks
 
 // Scalars that live in device memory so that n steps run without the host.
 struct DevState {
@@ -188,9 +187,9 @@ struct BinParams {
     GlobalPtr<float2> xy;
     GlobalPtr<int32_t> slot;
     GlobalPtr<int32_t> np;
-    GlobalPtr<int32_t> csum;     // multi-block scan: per chunk of kChunkBins bins its count, then its offset; [nchunk]: active flag
+    GlobalPtr<int32_t> csum;     // multi-block scan: per chunk of kChunkBins bins its count; [nchunk]: whether the scenario stepped
     int na, nbins, nx, ny, bsx, bsy, nbx;
-    int nchunk;        // chunks of the multi-block scan (0: the bins are scanned by one block)
+    int nchunk;        // chunks of the multi-block scan (0: no agents, or binned in LDS)
     float dx, dy;
 };
 
@@ -243,7 +242,6 @@ hipError_t launch_doors(const Batch& b, hipStream_t s);    // entries of the pre
 hipError_t launch_count_state(const uint8_t* state, int na, int value, int32_t* out, hipStream_t s);
 hipError_t launch_bin_place_all(const Batch& b, hipStream_t s);
 hipError_t launch_perm_from_slots(const int32_t* key, const int32_t* slot, int na, int32_t* perm, hipStream_t s);
-hipError_t launch_bin_chunk_sum(const Batch& b, hipStream_t s);    // multi-block scan: chunk counts
 hipError_t launch_bin_chunk_scan(const Batch& b, hipStream_t s);   // multi-block scan: bin starts
 hipError_t launch_bin_sort_all(const Batch& b, hipStream_t s);
 hipError_t launch_bin_keys(const BinParams& b, hipStream_t s);   // keys + ranks from positions

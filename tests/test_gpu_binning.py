@@ -45,3 +45,22 @@ def test_crowded_bins_keep_the_stable_order(oracle):
     say(f"most in a bin: {int(np.diff(bs).max())}")
     assert np.diff(bs).max() > 100
     assert np.array_equal(bs, bs_ref) and np.array_equal(perm, perm_ref)
+
+
+def test_stopped_member_with_many_bins_keeps_them(oracle):
+    """A member beyond the LDS binning (66,049 bins in 17 chunks) stops while one
+    with as many, and one binned in LDS, step on."""
+    scs = [I.shopping_centre(n=n, dx=0.25, seed=n + k, n_evac=m, q_peak=20.0)
+           for k, (n, m) in enumerate(((1028, 500), (64, 50), (1028, 9000)))]
+    ens = fps.Ensemble(scs)
+    ens[0].set_end_time(1.0)
+    ens.step(60)
+    assert ens[0].diag()["active"] == 0 and ens.active() == 2
+    for step in (0, 7):
+        ens.step(step)
+        for k, sc in enumerate(scs):
+            P, A = oracle.make_params(sc.desc, sc.ped), ens[k].agents()
+            bs, perm = ens[k].bins()
+            bs_ref, perm_ref = oracle.build_bins(P, A["x"], A["y"], A["state"])
+            assert np.array_equal(bs, bs_ref) and np.array_equal(perm, perm_ref)
+    say(f"stopped at t = {ens[0].diag()['t']:.3f}")
