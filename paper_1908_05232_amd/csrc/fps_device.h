@@ -66,10 +66,63 @@ __device__ __forceinline__ int wave_inclusive_scan(int v)
 // (fps_set_flood_frozen: the pedestrians walk on a flood state set from
 // outside).  Every kernel of the step evaluates this on the same device state
 // before the finalize changes it.
+__device__ __forceinline__ bool flood_skipped(int frozen, int settled, int any_wet, float inc)
+{
+    return frozen || (settled && !any_wet && inc == 0.0f);
+}
 template <class St>      // DevState, in global memory or LDS
 __device__ __forceinline__ bool flood_skipped(const St* st)
 {
-    return st->frozen || (st->settled && !st->any_wet && st->inc == 0.0f);
+    return flood_skipped(st->frozen, st->settled, st->any_wet, st->inc);
+}
+
+// What the kernels of a step ask the state first (wave-uniform).  All words are
+// here before any is looked at: left to itself the compiler loads each where a
+// branch needs it, a load and a wait at a time, and a kernel of a small grid
+// is little else than its chain of waits (the march, the pedestrian step and the
+// order of its loads: 512^2 with 2,000 people 23.2 -> 22.5 us a step).
+struct StepState {
+    int active, cur, any_wet, settled, frozen, done;
+    float dt, inc;
+    __device__ __forceinline__ bool skipped() const { return flood_skipped(frozen, settled, any_wet, inc); }
+};
+__device__ __forceinline__ StepState step_state(const FPS_GLOBAL DevState* st)
+{
+    StepState s{st->active, st->cur, st->any_wet, st->settled, st->frozen, st->done, st->dt, st->inc};
+    int dt = __builtin_bit_cast(int, s.dt), inc = __builtin_bit_cast(int, s.inc);
+    s.active = __builtin_amdgcn_readfirstlane(s.active);
+    s.cur = __builtin_amdgcn_readfirstlane(s.cur);
+    s.any_wet = __builtin_amdgcn_readfirstlane(s.any_wet);
+    s.settled = __builtin_amdgcn_readfirstlane(s.settled);
+    s.frozen = __builtin_amdgcn_readfirstlane(s.frozen);
+    s.done = __builtin_amdgcn_readfirstlane(s.done);
+    dt = __builtin_amdgcn_readfirstlane(dt);
+    inc = __builtin_amdgcn_readfirstlane(inc);
+    asm("" : "+s"(s.active), "+s"(s.cur), "+s"(s.any_wet), "+s"(s.settled), "+s"(s.frozen), "+s"(s.done),
+                 "+s"(dt), "+s"(inc));
+    s.dt = __builtin_bit_cast(float, dt);
+    s.inc = __builtin_bit_cast(float, inc);
+    return s;
+}
+
+// A parameter record by value, all of its words loaded before any is used (the
+// same for the record itself: at most six vectors of 16 words).
+template <class T>
+__device__ __forceinline__ T all_at_once(const T& record)
+{
+    typedef uint32_t Words __attribute__((ext_vector_type(16)));
+    constexpr int N = (sizeof(T) + 63) / 64;
+    static_assert(N >= 1 && N <= 5 && sizeof(T) % 4 == 0, "what fits the scalar registers");
+    Words w[5] = {};
+    __builtin_memcpy(w, &record, sizeof(T));
+    if constexpr (N == 1) asm("" : "+s"(w[0]));
+    if constexpr (N == 2) asm("" : "+s"(w[0]), "+s"(w[1]));
+    if constexpr (N == 3) asm("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]));
+    if constexpr (N == 4) asm("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]));
+    if constexpr (N == 5) asm("" : "+s"(w[0]), "+s"(w[1]), "+s"(w[2]), "+s"(w[3]), "+s"(w[4]));
+    T out;
+    __builtin_memcpy(&out, w, sizeof(T));
+    return out;
 }
 
 __device__ __forceinline__ double hydro_q(const DevState* st, double t)

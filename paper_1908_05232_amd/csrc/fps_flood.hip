@@ -335,13 +335,11 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
     }
     // parameters by value: wave-uniform registers, not reloaded after the
     // stores of the march (which the compiler cannot tell apart from them)
-    const FvParams p = scn_at<kOne>(B, sc).fv;
+    const FvParams p = all_at_once(scn_at<kOne>(B, sc).fv);
     if (tile >= p.ntiles) return;
-    const FPS_GLOBAL DevState* st = gmem(p.st);
-    if (!st->active || flood_skipped(st)) return;
-    // the state words are read through a generic pointer: make them wave-uniform
-    // so that the buffer selects below are scalar
-    const int cur = __builtin_amdgcn_readfirstlane(st->cur);
+    const StepState st = step_state(gmem(p.st));
+    if (!st.active || st.skipped()) return;
+    const int cur = st.cur;
     // selects, not indexing, so that the parameter copy stays in registers
     const Src src{gmem<const float>(cur ? p.h[1] : p.h[0]), gmem<const float>(cur ? p.qx[1] : p.qx[0]),
                   gmem<const float>(cur ? p.qy[1] : p.qy[0]), gmem(p.z)};
@@ -352,8 +350,7 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
     // mass, boundary fluxes through the x and y sides, clipped depth
     double m_acc = 0.0, vx_acc = 0.0, vy_acc = 0.0, vclip_acc = 0.0;
     float smax = 0.0f;
-    const float dt = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->dt)));
-    const float inc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->inc)));
+    const float dt = st.dt, inc = st.inc;
     const float lx = dt * p.inv_dx, ly = dt * p.inv_dy;
 
     {
@@ -618,11 +615,11 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
         sc = find_scenario(B.tile_off, B.S, g);
         tile = g - B.tile_off[sc];
     }
-    const FvParams p = scn_at<kOne>(B, sc).fv;
+    const FvParams p = all_at_once(scn_at<kOne>(B, sc).fv);
     if (tile >= p.ntiles) return;
-    const FPS_GLOBAL DevState* st = gmem(p.st);
-    if (!st->active || flood_skipped(st)) return;
-    const int cur = __builtin_amdgcn_readfirstlane(st->cur);
+    const StepState st = step_state(gmem(p.st));
+    if (!st.active || st.skipped()) return;
+    const int cur = st.cur;
     const Src s0{gmem<const float>(cur ? p.h[1] : p.h[0]), gmem<const float>(cur ? p.qx[1] : p.qx[0]),
                  gmem<const float>(cur ? p.qy[1] : p.qy[0]), gmem(p.z)};
     const Src s1{gmem<const float>(p.h1), gmem<const float>(p.qx1), gmem<const float>(p.qy1), gmem(p.z)};
@@ -631,8 +628,7 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
     FPS_GLOBAL float* __restrict__ qxo = gmem(kStage == 1 ? p.qx1 : cur ? p.qx[0] : p.qx[1]);
     FPS_GLOBAL float* __restrict__ qyo = gmem(kStage == 1 ? p.qy1 : cur ? p.qy[0] : p.qy[1]);
     const FPS_GLOBAL int32_t* __restrict__ npp = gmem(p.np);
-    const float dt = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->dt)));
-    const float inc = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, st->inc)));
+    const float dt = st.dt, inc = st.inc;
     const float lx = dt * p.inv_dx, ly = dt * p.inv_dy;
     const int sx = tile % p.nsx, sy = tile / p.nsx;
     const int i = sx * kStrip2 - 2 + lane;

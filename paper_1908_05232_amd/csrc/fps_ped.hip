@@ -588,28 +588,29 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
 template <bool kOne, int L>
 __global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
 {
-    const int g0 = blockIdx.x * (kWave / L);
-    if (g0 >= B.total_agents) return;
+    const int g0 = blockIdx.x * (kWave / L);      // < total_agents: the grid covers them exactly
     const int sc = kOne ? 0 : find_scenario(B.agent_off, B.S, g0);
     const Scn& S = scn_at<kOne>(B, sc);
     const int q = (int)threadIdx.x & (L - 1);
     const int a = g0 - (kOne ? 0 : B.agent_off[sc]) + (int)threadIdx.x / L;
+    // the agent's record and the wetness flags (one a lane; the flood update sets
+    // them per group of blocks) in the same round of loads as the state words,
+    // and the other parameters after them: read first, they are four rounds
+    const int flag = gmem(S.fv.wet)[kWetStride * threadIdx.x];
+    const AgentRec rec = load_agent(S.ped, min(a, S.na - 1));     // a scenario with blocks has agents
+    const StepState at = step_state(gmem(S.fv.st));
+    __builtin_amdgcn_sched_barrier(0);
+    if (!at.active) return;
     const PedParams P = S.ped;     // by value: not reloaded after the agent's stores
-    // the agent's record in the same round of loads as the scenario's state words
-    AgentRec rec{};
-    if (a < S.na) rec = load_agent(P, a);
-    const FPS_GLOBAL DevState* st = gmem(S.fv.st);
-    if (!st->active) return;
-    const bool skipped = flood_skipped(st);
+    const bool skipped = at.skipped();
+    const float dt = at.dt;             // the step length of this step
+    const int done = at.done;
     // the flood state this step's pedestrians see: the new one, or the
     // unchanged one when the dry step skipped the flood update
-    const int fb = skipped ? st->cur : (st->cur ^ 1);
-    const float dt = st->dt;            // the step length of this step
-    const int done = st->done;
+    const int fb = skipped ? at.cur : (at.cur ^ 1);
     // evacuation trigger: some cell is wet after this step's flood update
-    // one wetness flag per lane (the flood update sets them per group of blocks)
     // (a skipped update left the state, and its wetness, as they were)
-    const int wet = skipped ? st->any_wet : (__ballot(gmem(S.fv.wet)[kWetStride * threadIdx.x] != 0) != 0ull);
+    const int wet = skipped ? at.any_wet : (__ballot(flag != 0) != 0ull);
     int drop = 0, left = 0;
     if (a < S.na)
         agent_step<L>(P, rec, gmem(fb ? S.fv.h[1] : S.fv.h[0]), gmem(fb ? S.fv.qx[1] : S.fv.qx[0]),
