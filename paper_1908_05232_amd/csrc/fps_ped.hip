@@ -158,6 +158,117 @@ __device__ __forceinline__ int window_row(int b, int wdth, int wcells, uint32_t 
     return wcells <= (1 << 20) / wdth ? (int)(((uint64_t)(uint32_t)b * wmagic) >> 20) : b / wdth;
 }
 
+// The obstacle cell of bit b of an agent's mask: the nearest point of the cell
+// repels it.
+__device__ __forceinline__ void repel_cell(const PedParams& p, float x, float y, int ci, int cj, int b, int wdth,
+                                           uint32_t wmagic, float& fx, float& fy)
+{
+    const int row = (int)(((uint32_t)b * wmagic) >> 20), col = b - row * wdth;      // b < 128: exact
+    const int wi = ci + col - p.Rx, wj = cj + row - p.Ry;
+    const float px = fminf(fmaxf(x, (float)wi * p.dx), (float)(wi + 1) * p.dx);
+    const float py = fminf(fmaxf(y, (float)wj * p.dy), (float)(wj + 1) * p.dy);
+    repel(p, x - px, y - py, p.radius, fx, fy);
+}
+
+// The cells of slot s of a mask (bits s, s + 16, ... in order), added to the slot's sums.
+__device__ __forceinline__ void slot_cells(const PedParams& p, float x, float y, int ci, int cj, const UInt4& m, int s,
+                                           int wdth, uint32_t wmagic, float& fx, float& fy)
+{
+    uint32_t left = 0;
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        left |= (m[w] >> s & 1u) << (2 * w);
+        left |= (m[w] >> (s + 16) & 1u) << (2 * w + 1);
+    }
+    for (; left; left &= left - 1)
+        repel_cell(p, x, y, ci, cj, s + kSlots * __builtin_ctz(left), wdth, wmagic, fx, fy);
+}
+
+// Forces from the obstacle cells of the masks m4 (zero for agents without any)
+// onto the slots, and the total of neighbours and obstacles.  Called by the
+// whole wave.  With 16 lanes an agent each lane takes its slot.  With fewer, the
+// agents that have obstacle cells near (a third of a crowd in a shopping centre,
+// 18 of 81 cells each) are taken four at a time by 16 lanes each, through LDS:
+// by its own lanes, every cell of the window was work for the whole wave as
+// soon as one agent had it.  A slot's additions and their order are the same,
+// and so are the bits.  Measured, us a launch before and with it: 1 lane an agent
+// (6 centres of 50,000) 82 and 64 (of it 5 by the fifth wave a SIMD that loading
+// four neighbours at a time allows), 4 lanes (41,000) 19.8 and 13.2, 16 lanes
+// (2,000) 7.3 and 6.1.
+template <int L>
+__device__ __forceinline__ void wall_forces(const PedParams& p, float x, float y, int ci, int cj, const UInt4& m4, int q,
+                                            float (&fx)[kSlots / L], float (&fy)[kSlots / L], float& fsx, float& fsy)
+{
+    constexpr int J = kSlots / L, G = kWave / kSlots;
+    const int wdth = 2 * p.Rx + 1;
+    const uint32_t wmagic = ((1u << 20) + (uint32_t)wdth - 1u) / (uint32_t)wdth;
+    if (wdth * (2 * p.Ry + 1) <= kSlots) {      // a cell a slot at most: each lane takes its own (0.4 us a launch less)
+#pragma unroll
+        for (int j = 0; j < J; ++j)
+            if (m4[0] >> (q + j * L) & 1u) repel_cell(p, x, y, ci, cj, q + j * L, wdth, wmagic, fx[j], fy[j]);
+        fsx = slot_sum<L>(fx);
+        fsy = slot_sum<L>(fy);
+        return;
+    }
+    const bool some = (m4[0] | m4[1] | m4[2] | m4[3]) != 0;
+    if constexpr (L == kSlots) {
+        if (some) slot_cells(p, x, y, ci, cj, m4, q, wdth, wmagic, fx[0], fy[0]);
+        fsx = slot_sum<L>(fx);
+        fsy = slot_sum<L>(fy);
+    } else {
+        struct Agent {
+            float x, y;
+            int ci, cj;
+            UInt4 m;
+            float fx[kSlots], fy[kSlots];
+        };
+        __shared__ Agent taken[G];
+        __shared__ float total[G][2];
+        const int lane = threadIdx.x, g = lane / kSlots, s = lane & (kSlots - 1);
+        const uint64_t todo = __ballot(some && q == 0);
+        const int n = __popcll(todo), rank = __popcll(todo & ((1ull << (lane & ~(L - 1))) - 1ull));
+        float tx = 0.0f, ty = 0.0f;
+        for (int k = 0; k < n; k += G) {
+            const bool mine = some && rank / G == k / G;
+            Agent& A = taken[rank % G];
+            if (mine) {
+                if (q == 0) {
+                    A.x = x;
+                    A.y = y;
+                    A.ci = ci;
+                    A.cj = cj;
+                    A.m = m4;
+                }
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    A.fx[q + j * L] = fx[j];
+                    A.fy[q + j * L] = fy[j];
+                }
+            }
+            __syncthreads();
+            float f[1] = {0.0f}, h[1] = {0.0f};
+            if (k + g < n) {
+                const Agent& T = taken[g];
+                f[0] = T.fx[s];
+                h[0] = T.fy[s];
+                slot_cells(p, T.x, T.y, T.ci, T.cj, T.m, s, wdth, wmagic, f[0], h[0]);
+            }
+            const float sx = slot_sum<kSlots>(f), sy = slot_sum<kSlots>(h);
+            if (s == 0) {
+                total[g][0] = sx;
+                total[g][1] = sy;
+            }
+            __syncthreads();
+            if (mine) {
+                tx = total[rank % G][0];
+                ty = total[rank % G][1];
+            }
+        }
+        fsx = some ? tx : slot_sum<L>(fx);
+        fsy = some ? ty : slot_sum<L>(fy);
+    }
+}
+
 // The agent's record, read before anything else of the step.
 struct AgentRec {
     float x, y, vx, vy, vbase, timer, body_h, body_m;
@@ -198,7 +309,7 @@ __device__ __forceinline__ AgentRec load_agent(const PedParams& p, int a)
 template <int L>
 __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GLOBAL float* __restrict__ fh,
                            const FPS_GLOBAL float* __restrict__ fqx, const FPS_GLOBAL float* __restrict__ fqy, int a, int q,
-                           float dt, int any_wet, int done, int& drop, int& left)
+                           bool valid, float dt, int any_wet, int done, int& drop, int& left)
 {
     const bool lead = q == 0;
     const int st0 = rec.state;
@@ -208,168 +319,179 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
     int dest = rec.dest;
     const float vbase = rec.vbase;
     const int self = rec.slot;
-    if (st0 == FPS_ST_EXITED || st0 == FPS_ST_OUTSIDE) {
-        if (lead) p.key[a] = -1;
-        return;
-    }
+    // valid: the lanes past the last agent take part in the wave's shared work only
+    const bool alive = valid && st0 != FPS_ST_EXITED && st0 != FPS_ST_OUTSIDE;
+    if (valid && !alive && lead) p.key[a] = -1;
+    if constexpr (L == kSlots)
+        if (!alive) return;      // nothing is shared across agents
     const int ci = clampi(cell_of(x, p.dx, p.nx), 0, p.nx - 1);
     const int cj = clampi(cell_of(y, p.dy, p.ny), 0, p.ny - 1);
     const size_t c = (size_t)cj * p.nx + ci;
     const size_t nc = (size_t)p.nx * p.ny;
-    // the agent's state and destination, from its record alone (the new
-    // destination of an agent without one reads the exits' distances), so
-    // that the record is complete before the next round of loads goes out
-    int st = st0;
-    if (dest < 0) {
-        if (role == FPS_ROLE_EVACUEE) {
-            dest = nearest_exit(p, ci, cj);
-            st = FPS_ST_EVAC;
-        } else {
-            dest = p.storage_dest;
-            st = FPS_ST_TO_STORAGE;
-        }
-    }
-    if (role == FPS_ROLE_RESPONDER && done && st != FPS_ST_EVAC) {
-        st = FPS_ST_EVAC;
-        dest = nearest_exit(p, ci, cj);
-    }
-    // the flood has reached the site: walkers of the pre-flood flow become
-    // evacuees heading for the nearest exit
-    if (st == FPS_ST_SHOPPING && any_wet) {
-        st = FPS_ST_EVAC;
-        dest = nearest_exit(p, ci, cj);
-    }
-    bool moving = true;
-    if (st == FPS_ST_PICKING || st == FPS_ST_DROPPING) {
-        float tm = rec.timer - dt;
-        if (lead) p.timer[a] = tm;
-        if (tm > 0.0f) {
-            moving = false;
-        } else if (st == FPS_ST_PICKING) {
-            st = FPS_ST_TO_BARRIER;
-            dest = p.barrier_dest;
-        } else {
-            drop = 1;
-            st = FPS_ST_TO_STORAGE;
-            dest = p.storage_dest;
-        }
-    }
-    if (moving && role == FPS_ROLE_EVACUEE && st == FPS_ST_EVAC && !any_wet) moving = false;
-    // an agent without a valid destination (e.g. a responder with no barrier set) stands
-    if (dest < 0 || dest >= p.n_dest) moving = false;
-    // second load round: everything addressed by the cell.
-    // A 32 x 32 -> 64-bit product: the 64 x 64 one leaves its upper addend
-    // undefined, and the register chosen for it can be a load still in flight
-    const uint64_t doff = (uint64_t)(uint32_t)(moving ? dest : 0) * (uint64_t)(uint32_t)nc;
-    const FPS_GLOBAL float* D = &p.dist[doff];
-    const FPS_GLOBAL uint8_t* K = &p.codes[doff];
-    const float h = fh[c];
-    float qxc = 0.0f, qyc = 0.0f;     // the cell's discharge: this round with several lanes per agent
-    if constexpr (L > 1) {
-        qxc = fqx[c];
-        qyc = fqy[c];
-    }
-    const int kc = moving && p.use_codes ? (int)K[c] : 0;       // the cell's code of the destination
+    int st = st0, kc = 0;
+    bool moving = false;
+    uint64_t doff = 0;
+    float h = 0.0f, qxc = 0.0f, qyc = 0.0f;     // the cell's discharge: in the cell's round with several lanes per agent
+    float ex = 0.0f, ey = 0.0f;                 // desired direction
     UInt4 m4 = {0, 0, 0, 0};
-    if (p.use_wmask) {
-        // with one lane per agent (many agents: the step is bound by memory
-        // traffic) the obstacle mask is read only where the code says an
-        // obstacle is near, a round later; with several lanes (few agents:
-        // bound by latency) it goes out with this round
-        if constexpr (L == 1) {
-            if (!(kc & kCodeClear)) m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
-        } else {
-            m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
-        }
-    }
-    const int bi = ci / p.bsx, bj = cj / p.bsy;
-    const int qi0 = max(bi - 1, 0), qi1 = min(bi + 1, p.nbx - 1);
-    // both bounds of every bin row are loaded (a row outside the grid reads
-    // the agent's own row and is then made empty), so that the six loads go
-    // out together: a load under a condition would make the empty-row copy
-    // wait for the one before it
-    int seg0[3], seg1[3];
-#pragma unroll
-    for (int r = 0; r < 3; ++r) {
-        const int qj = bj - 1 + r;
-        const bool ok = qj >= 0 && qj < p.nby;
-        const int row = ok ? qj : bj;
-        const int s0 = p.bin_start[row * p.nbx + qi0], s1 = p.bin_start[row * p.nbx + qi1 + 1];
-        seg0[r] = s0;
-        seg1[r] = ok ? s1 : s0;
-    }
-    // the direction: from the cell's heading code of the destination (one
-    // byte), or, for destinations beyond the coded ones, from the nine
-    // distances of its field; the loads go out before the wait for the cell's
-    // flood state (the hazard class below), so that they travel in the same
-    // round as the cell's.
-    float ex = 0.0f, ey = 0.0f;    // desired direction
-    if (moving) {
-        bool has_target;
-        int ti, tj;
-        if (p.use_codes) {
-            const int code = kc & 15;
-            has_target = code <= kCodeHere;
-            const bool here_c = code == kCodeHere;
-            ti = here_c ? ci : ci + off_of(kOffXPacked, code & 7);
-            tj = here_c ? cj : cj + off_of(kOffYPacked, code & 7);
-        } else {
-            float dk[8];
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                const int qi = ci + kOffX[k], qj = cj + kOffY[k];
-                const bool in = qi >= 0 && qj >= 0 && qi < p.nx && qj < p.ny;
-                const float val = D[(size_t)clampi(qj, 0, p.ny - 1) * p.nx + clampi(qi, 0, p.nx - 1)];
-                dk[k] = in ? val : __builtin_inff();
-            }
-            const float here = D[c];
-            // steepest descent: the first of the smallest neighbour distances
-            // below the agent's own; on the destination (distance 0) the target
-            // is the agent's cell.  Selected without a branch on the agent's own
-            // distance (which would hold the other eight loads back until it
-            // arrives) and with the offsets as constants (no offset table read).
-            float best = here;
-            int box = 0, boy = 0;
-            bool found = false;
-#pragma unroll
-            for (int k = 0; k < 8; ++k) {
-                if (dk[k] < best) {
-                    best = dk[k];
-                    box = kOffX[k];
-                    boy = kOffY[k];
-                    found = true;
-                }
-            }
-            const bool at_goal = here == 0.0f;
-            has_target = at_goal || found;
-            ti = at_goal ? ci : ci + box;
-            tj = at_goal ? cj : cj + boy;
-        }
-        if (has_target) {
-            float tx = ((float)ti + 0.5f) * p.dx - x, ty = ((float)tj + 0.5f) * p.dy - y;
-            float len2 = tx * tx + ty * ty;
-            if (len2 > 0.0f) {
-                float il = __builtin_amdgcn_rsqf(len2);
-                ex = tx * il;
-                ey = ty * il;
+    int seg0[3] = {}, seg1[3] = {};
+    if (alive) {
+        // the agent's state and destination, from its record alone (the new
+        // destination of an agent without one reads the exits' distances), so
+        // that the record is complete before the next round of loads goes out
+        if (dest < 0) {
+            if (role == FPS_ROLE_EVACUEE) {
+                dest = nearest_exit(p, ci, cj);
+                st = FPS_ST_EVAC;
+            } else {
+                dest = p.storage_dest;
+                st = FPS_ST_TO_STORAGE;
             }
         }
-    }
-    // the direction is needed here: this keeps the compiler from moving its
-    // loads below the neighbour loop, where they would form a round of their own
-    asm volatile("" : "+v"(ex), "+v"(ey));
-    // with one lane per agent (many agents: the step is bound by memory
-    // traffic) the cell's discharge is read only where the cell is wet, in
-    // the round of the neighbours' positions
-    if constexpr (L == 1) {
-        if (h > p.eps) {
+        if (role == FPS_ROLE_RESPONDER && done && st != FPS_ST_EVAC) {
+            st = FPS_ST_EVAC;
+            dest = nearest_exit(p, ci, cj);
+        }
+        // the flood has reached the site: walkers of the pre-flood flow become
+        // evacuees heading for the nearest exit
+        if (st == FPS_ST_SHOPPING && any_wet) {
+            st = FPS_ST_EVAC;
+            dest = nearest_exit(p, ci, cj);
+        }
+        moving = true;
+        if (st == FPS_ST_PICKING || st == FPS_ST_DROPPING) {
+            float tm = rec.timer - dt;
+            if (lead) p.timer[a] = tm;
+            if (tm > 0.0f) {
+                moving = false;
+            } else if (st == FPS_ST_PICKING) {
+                st = FPS_ST_TO_BARRIER;
+                dest = p.barrier_dest;
+            } else {
+                drop = 1;
+                st = FPS_ST_TO_STORAGE;
+                dest = p.storage_dest;
+            }
+        }
+        if (moving && role == FPS_ROLE_EVACUEE && st == FPS_ST_EVAC && !any_wet) moving = false;
+        // an agent without a valid destination (e.g. a responder with no barrier set) stands
+        if (dest < 0 || dest >= p.n_dest) moving = false;
+        // second load round: everything addressed by the cell.
+        // A 32 x 32 -> 64-bit product: the 64 x 64 one leaves its upper addend
+        // undefined, and the register chosen for it can be a load still in flight
+        doff = (uint64_t)(uint32_t)(moving ? dest : 0) * (uint64_t)(uint32_t)nc;
+        const FPS_GLOBAL float* D = &p.dist[doff];
+        const FPS_GLOBAL uint8_t* K = &p.codes[doff];
+        h = fh[c];
+        if constexpr (L > 1) {
             qxc = fqx[c];
             qyc = fqy[c];
+        }
+        kc = moving && p.use_codes ? (int)K[c] : 0;       // the cell's code of the destination
+        if (p.use_wmask) {
+            // with one lane per agent (many agents: the step is bound by memory
+            // traffic) the obstacle mask is read only where the code says an
+            // obstacle is near, a round later; with several lanes (few agents:
+            // bound by latency) it goes out with this round
+            if constexpr (L == 1) {
+                if (!(kc & kCodeClear)) m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
+            } else {
+                m4 = *(FPS_GLOBAL const UInt4*)&p.wmask[c];
+            }
+        }
+        const int bi = ci / p.bsx, bj = cj / p.bsy;
+        const int qi0 = max(bi - 1, 0), qi1 = min(bi + 1, p.nbx - 1);
+        // both bounds of every bin row are loaded (a row outside the grid reads
+        // the agent's own row and is then made empty), so that the six loads go
+        // out together: a load under a condition would make the empty-row copy
+        // wait for the one before it
+#pragma unroll
+        for (int r = 0; r < 3; ++r) {
+            const int qj = bj - 1 + r;
+            const bool ok = qj >= 0 && qj < p.nby;
+            const int row = ok ? qj : bj;
+            const int s0 = p.bin_start[row * p.nbx + qi0], s1 = p.bin_start[row * p.nbx + qi1 + 1];
+            seg0[r] = s0;
+            seg1[r] = ok ? s1 : s0;
+        }
+        // the direction: from the cell's heading code of the destination (one
+        // byte), or, for destinations beyond the coded ones, from the nine
+        // distances of its field; the loads go out before the wait for the cell's
+        // flood state (the hazard class below), so that they travel in the same
+        // round as the cell's.
+        if (moving) {
+            bool has_target;
+            int ti, tj;
+            if (p.use_codes) {
+                const int code = kc & 15;
+                has_target = code <= kCodeHere;
+                const bool here_c = code == kCodeHere;
+                ti = here_c ? ci : ci + off_of(kOffXPacked, code & 7);
+                tj = here_c ? cj : cj + off_of(kOffYPacked, code & 7);
+            } else {
+                float dk[8];
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    const int qi = ci + kOffX[k], qj = cj + kOffY[k];
+                    const bool in = qi >= 0 && qj >= 0 && qi < p.nx && qj < p.ny;
+                    const float val = D[(size_t)clampi(qj, 0, p.ny - 1) * p.nx + clampi(qi, 0, p.nx - 1)];
+                    dk[k] = in ? val : __builtin_inff();
+                }
+                const float here = D[c];
+                // steepest descent: the first of the smallest neighbour distances
+                // below the agent's own; on the destination (distance 0) the target
+                // is the agent's cell.  Selected without a branch on the agent's own
+                // distance (which would hold the other eight loads back until it
+                // arrives) and with the offsets as constants (no offset table read).
+                float best = here;
+                int box = 0, boy = 0;
+                bool found = false;
+#pragma unroll
+                for (int k = 0; k < 8; ++k) {
+                    if (dk[k] < best) {
+                        best = dk[k];
+                        box = kOffX[k];
+                        boy = kOffY[k];
+                        found = true;
+                    }
+                }
+                const bool at_goal = here == 0.0f;
+                has_target = at_goal || found;
+                ti = at_goal ? ci : ci + box;
+                tj = at_goal ? cj : cj + boy;
+            }
+            if (has_target) {
+                float tx = ((float)ti + 0.5f) * p.dx - x, ty = ((float)tj + 0.5f) * p.dy - y;
+                float len2 = tx * tx + ty * ty;
+                if (len2 > 0.0f) {
+                    float il = __builtin_amdgcn_rsqf(len2);
+                    ex = tx * il;
+                    ey = ty * il;
+                }
+            }
+        }
+        // the direction is needed here: this keeps the compiler from moving its
+        // loads below the neighbour loop, where they would form a round of their own
+        asm volatile("" : "+v"(ex), "+v"(ey));
+        // with one lane per agent (many agents: the step is bound by memory
+        // traffic) the cell's discharge is read only where the cell is wet, in
+        // the round of the neighbours' positions
+        if constexpr (L == 1) {
+            if (h > p.eps) {
+                qxc = fqx[c];
+                qyc = fqy[c];
+            }
         }
     }
     // the forces first (they do not depend on the hazard class), so that
     // the discharge loads travel with the neighbour loads
-    float fsx = 0.0f, fsy = 0.0f;
+    constexpr int J = kSlots / L;
+    float fx[J], fy[J];
+#pragma unroll
+    for (int j = 0; j < J; ++j) {
+        fx[j] = 0.0f;
+        fy[j] = 0.0f;
+    }
     if (moving) {
         // repulsion from the neighbours in the 3x3 bins (the three bins of one
         // bin row are one contiguous run of the sorted positions; the runs of
@@ -379,33 +501,35 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
         // k of each list goes into slot k mod kSlots, in list order; the slots
         // are then added by a fixed tree.  Lane q holds slots q, q + L, ...,
         // so the sum has the same bits whatever the number L of lanes.
-        constexpr int J = kSlots / L;
         constexpr int U = J >= 8 ? 1 : 2;      // slot batches per round of loads
-        float fx[J], fy[J];
-#pragma unroll
-        for (int j = 0; j < J; ++j) {
-            fx[j] = 0.0f;
-            fy[j] = 0.0f;
-        }
+        constexpr int B = J < 4 ? J : 4;       // loads of a batch before their uses
         const int n0 = seg1[0] - seg0[0], n01 = n0 + seg1[1] - seg0[1];
         const int ntot = n01 + seg1[2] - seg0[2];
         for (int k0 = 0; k0 < ntot; k0 += U * kSlots) {
-            int sl[U][J];
-            Float2 o[U][J];
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+            for (int j0 = 0; j0 < J; j0 += B) {
+                int sl[U][B];
+                Float2 o[U][B];
 #pragma unroll
-                for (int j = 0; j < J; ++j) {
-                    const int kk = k0 + u * kSlots + q + j * L;
-                    sl[u][j] = kk < n0 ? seg0[0] + kk : kk < n01 ? seg0[1] + (kk - n0) : seg0[2] + (kk - n01);
-                    o[u][j] = kk < ntot ? *(FPS_GLOBAL const Float2*)&p.xy[sl[u][j]] : Float2{x, y};
-                }
+                for (int u = 0; u < U; ++u)
 #pragma unroll
-            for (int u = 0; u < U; ++u)
+                    for (int j = 0; j < B; ++j) {
+                        const int kk = k0 + u * kSlots + q + (j0 + j) * L;
+                        sl[u][j] = kk < n0 ? seg0[0] + kk : kk < n01 ? seg0[1] + (kk - n0) : seg0[2] + (kk - n01);
+                        o[u][j] = kk < ntot ? *(FPS_GLOBAL const Float2*)&p.xy[sl[u][j]] : Float2{x, y};
+                    }
 #pragma unroll
-                for (int j = 0; j < J; ++j)
-                    if (sl[u][j] != self) repel(p, x - o[u][j].x, y - o[u][j].y, p.two_r, fx[j], fy[j]);
+                for (int u = 0; u < U; ++u)
+#pragma unroll
+                    for (int j = 0; j < B; ++j)
+                        if (sl[u][j] != self) repel(p, x - o[u][j].x, y - o[u][j].y, p.two_r, fx[j0 + j], fy[j0 + j]);
+            }
         }
+    }
+    float fsx = 0.0f, fsy = 0.0f;
+    if (p.use_wmask) {
+        wall_forces<L>(p, x, y, ci, cj, moving ? m4 : UInt4{0, 0, 0, 0}, q, fx, fy, fsx, fsy);
+    } else if (moving) {
         const int wdth = 2 * p.Rx + 1, wcells = (kc & kCodeClear) ? 0 : wdth * (2 * p.Ry + 1);
         const uint32_t wmagic = ((1u << 20) + (uint32_t)wdth - 1u) / (uint32_t)wdth;
         for (int b0 = 0; b0 < wcells; b0 += kSlots) {
@@ -415,23 +539,16 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
                 if (b >= wcells) continue;
                 const int row = window_row(b, wdth, wcells, wmagic), col = b - row * wdth;
                 const int wi = ci + col - p.Rx, wj = cj + row - p.Ry;
-                bool obst;
-                if (p.use_wmask) {
-                    const uint32_t word = b < 32 ? m4.x : b < 64 ? m4.y : b < 96 ? m4.z : m4.w;
-                    obst = (word >> (b & 31)) & 1u;
-                } else {
-                    obst = wi >= 0 && wj >= 0 && wi < p.nx && wj < p.ny && !p.walk[(size_t)wj * p.nx + wi];
-                }
-                if (obst) {
-                    const float px = fminf(fmaxf(x, (float)wi * p.dx), (float)(wi + 1) * p.dx);
-                    const float py = fminf(fmaxf(y, (float)wj * p.dy), (float)(wj + 1) * p.dy);
-                    repel(p, x - px, y - py, p.radius, fx[j], fy[j]);
-                }
+                if (wi < 0 || wj < 0 || wi >= p.nx || wj >= p.ny || p.walk[(size_t)wj * p.nx + wi]) continue;
+                const float px = fminf(fmaxf(x, (float)wi * p.dx), (float)(wi + 1) * p.dx);
+                const float py = fminf(fmaxf(y, (float)wj * p.dy), (float)(wj + 1) * p.dy);
+                repel(p, x - px, y - py, p.radius, fx[j], fy[j]);
             }
         }
         fsx = slot_sum<L>(fx);
         fsy = slot_sum<L>(fy);
     }
+    if (!alive) return;
     // hazard of the containing cell (Table 1)
     int cls;
     float v0;
@@ -498,6 +615,8 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
         // move, rejecting an axis that lands in an obstacle or outside.  The
         // cells the outcome can depend on are read together (one round of
         // loads instead of three dependent ones), then selected.
+        const FPS_GLOBAL float* D = &p.dist[doff];
+        const FPS_GLOBAL uint8_t* K = &p.codes[doff];
         xn = x + dt * vx;
         const int ni_try = cell_of(xn, p.dx, p.nx);
         const int ny_try = cell_of(y + dt * vy, p.dy, p.ny);
@@ -586,7 +705,7 @@ __device__ void agent_step(const PedParams& p, const AgentRec& rec, const FPS_GL
 // ranges of the scenarios are padded to whole multiples of kWave agents in the
 // flattened index, so no block straddles two scenarios.
 template <bool kOne, int L>
-__global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
+__global__ __launch_bounds__(kWave, L == 1 ? 5 : 1) void ped_step_kernel(Batch B)
 {
     const int g0 = blockIdx.x * (kWave / L);      // < total_agents: the grid covers them exactly
     const int sc = kOne ? 0 : find_scenario(B.agent_off, B.S, g0);
@@ -612,9 +731,8 @@ __global__ __launch_bounds__(kWave) void ped_step_kernel(Batch B)
     // (a skipped update left the state, and its wetness, as they were)
     const int wet = skipped ? at.any_wet : (__ballot(flag != 0) != 0ull);
     int drop = 0, left = 0;
-    if (a < S.na)
-        agent_step<L>(P, rec, gmem(fb ? S.fv.h[1] : S.fv.h[0]), gmem(fb ? S.fv.qx[1] : S.fv.qx[0]),
-                      gmem(fb ? S.fv.qy[1] : S.fv.qy[0]), a, q, dt, wet, done, drop, left);
+    agent_step<L>(P, rec, gmem(fb ? S.fv.h[1] : S.fv.h[0]), gmem(fb ? S.fv.qx[1] : S.fv.qx[0]),
+                      gmem(fb ? S.fv.qy[1] : S.fv.qy[0]), a, q, a < S.na, dt, wet, done, drop, left);
     // one wave per block: the sandbag drops of the wave (lane 0 of each
     // group), one atomic; the agent-steps of the step are the agents that
     // start it outside the exits, which the bins hold: one add per scenario,
