@@ -35,7 +35,7 @@ constexpr int kWetSlots = 64;          // wetness flags of a flood update, one p
 constexpr int kWetStride = 32;         // ints between flags (one 128-byte line each)
 constexpr int kMaxDoor = 16;           // entrance doors of the pre-flood flow
 constexpr int kCodeDest = 16;          // destinations whose direction codes are kept (more: read the distances)
-constexpr int kChunkBins = 4096;       // bins per block of the multi-block bin scan (256 threads x 16)
+constexpr int kChunkBins = 4096;       // bins per block of the multi-block bin scan (4 a thread)
 constexpr int kRedMin = 8192;          // flood partials the end-of-step block reads in one round (8 a thread)
 constexpr int kRedTiles = 2048;        // partials of a larger grid added by one block first
 constexpr int kSyncCount = 64;         // blocks a scenario that count themselves in the copy back

@@ -940,76 +940,66 @@ __global__ __launch_bounds__(kPedBlock) void bin_sort_all_kernel(Batch B)
 // time) keeps its bins: the end-of-step block records whether it stepped,
 // before it may mark it inactive.  Measured: the counts in a launch of their
 // own and their scan in the end-of-step block took 6 us more a step.
-constexpr int kChunkThreads = kChunkBins / 16;
-
-__device__ __forceinline__ void chunk_counts(const BinParams& b, int k0, int (&v)[16])
+// Four bins a thread, so that a wave's loads and stores are whole lines (with
+// sixteen a thread each lane's 16 bytes were a request of their own), and every
+// load goes out before the first wait: six grids of 2048^2 cells (1.6 M bins)
+// 9.6 -> 7.3 us.
+__global__ __launch_bounds__(kScanThreads) void bin_chunk_scan_kernel(Batch B)
 {
-    if (k0 + 16 <= b.nbins) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const Int4 w = *(FPS_GLOBAL const Int4*)&b.bin_count[k0 + 4 * q];
-            v[4 * q] = w.x; v[4 * q + 1] = w.y; v[4 * q + 2] = w.z; v[4 * q + 3] = w.w;
-        }
-    } else {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) v[e] = k0 + e < b.nbins ? b.bin_count[k0 + e] : 0;
-    }
-}
-
-__global__ __launch_bounds__(kChunkThreads) void bin_chunk_scan_kernel(Batch B)
-{
-    __shared__ int wt[kChunkThreads / kWave], before[kChunkThreads / kWave];
+    __shared__ int wt[kScanThreads / kWave], before[kScanThreads / kWave];
     const int g = blockIdx.x;
     const int sc = find_scenario(B.chunk_off, B.S, g);
-    const Scn& S = B.scn[sc];
-    const BinParams b = S.bins;
+    const BinParams b = B.scn[sc].bins;
     const int c = g - B.chunk_off[sc];
-    if (!b.csum[b.nchunk]) return;
+    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
+    const int k0 = c * kChunkBins + 4 * (int)threadIdx.x;
+    const bool full = k0 + 4 <= b.nbins;
+    const int stepped = b.csum[b.nchunk];
+    Int4 v = {0, 0, 0, 0};
+    if (full) {
+        v = *(FPS_GLOBAL const Int4*)&b.bin_count[k0];
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (k0 + e < b.nbins) v[e] = b.bin_count[k0 + e];
+    }
     // the agents in the chunks before this one
     int pre = 0;
-    for (int i = threadIdx.x; i < c; i += kChunkThreads) pre += b.csum[i];
-    const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
-    const int k0 = c * kChunkBins + 16 * (int)threadIdx.x;
-    int v[16];
-    chunk_counts(b, k0, v);
-    const bool full = k0 + 16 <= b.nbins;
+    for (int i = threadIdx.x; i < c; i += kScanThreads) pre += b.csum[i];
+    if (!stepped) return;
     if (full) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) *(FPS_GLOBAL Int4*)&b.bin_count[k0 + 4 * q] = Int4{0, 0, 0, 0};
+        *(FPS_GLOBAL Int4*)&b.bin_count[k0] = Int4{0, 0, 0, 0};
     } else {
-        for (int e = 0; e < 16; ++e)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
             if (k0 + e < b.nbins) b.bin_count[k0 + e] = 0;
     }
-    int t = 0;
-#pragma unroll
-    for (int e = 0; e < 16; ++e) t += v[e];
-    const int incl = wave_inclusive_scan(t);
-    const int pincl = wave_inclusive_scan(pre);
+    const int own = v[0] + v[1] + v[2] + v[3];
+    const int incl = wave_inclusive_scan(own), pincl = wave_inclusive_scan(pre);
     if (lane == kWave - 1) {
         wt[wid] = incl;
         before[wid] = pincl;
     }
     __syncthreads();
-    int run = incl - t;
-    for (int w = 0; w < wid; ++w) run += wt[w];
-    for (int w = 0; w < kChunkThreads / kWave; ++w) run += before[w];
-    if (full) {
+    // the waves' totals, one a lane, scanned within the row of sixteen lanes
+    const int tot = wave_inclusive_scan(wt[lane & (kScanThreads / kWave - 1)]);
+    const int ptot = wave_inclusive_scan(before[lane & (kScanThreads / kWave - 1)]);
+    int run = incl - own + (wid > 0 ? __builtin_amdgcn_readlane(tot, max(wid - 1, 0)) : 0) +
+              __builtin_amdgcn_readlane(ptot, kScanThreads / kWave - 1);
+    Int4 start;
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            Int4 w;
-            w.x = run; run += v[4 * q];
-            w.y = run; run += v[4 * q + 1];
-            w.z = run; run += v[4 * q + 2];
-            w.w = run; run += v[4 * q + 3];
-            *(FPS_GLOBAL Int4*)&b.bin_start[k0 + 4 * q] = w;
-        }
-    } else {
-        for (int e = 0; e < 16; ++e) {
-            if (k0 + e < b.nbins) b.bin_start[k0 + e] = run;
-            run += v[e];
-        }
+    for (int e = 0; e < 4; ++e) {
+        start[e] = run;
+        run += v[e];
     }
-    if (c == b.nchunk - 1 && threadIdx.x == kChunkThreads - 1) b.bin_start[b.nbins] = run;     // all agents
+    if (full) {
+        *(FPS_GLOBAL Int4*)&b.bin_start[k0] = start;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (k0 + e < b.nbins) b.bin_start[k0 + e] = start[e];
+    }
+    if (c == b.nchunk - 1 && threadIdx.x == kScanThreads - 1) b.bin_start[b.nbins] = run;     // all agents
 }
 
 // the agents in bin order from each binned agent's slot (the step keeps only
@@ -1198,12 +1188,11 @@ void launch_ped_lanes(const Batch& b, hipStream_t s)
 }  // namespace
 
 // Lanes per agent, by measurement: 16 for small crowds (latency bound: the
-// lanes share an agent's neighbour and obstacle loops; a whole step with 4 and
-// with 16 lanes: 10,000 agents on 512^2 cells 44.8 and 40.4 us, 20,000 on
-// 1024^2 59.2 and 55.8, 45,000 there 64.4 and 64.1, but the 36 sites of 128^2
-// with 36,000 lose 1.8), 4 up to 2^18 agents (the 64-scenario sweep with 170 k
-// agents: 58 us per step against 66 with 1 lane and 88 with 16), then 1, where
-// the agents' own work fills the chip.
+// lanes share an agent's neighbours; a whole step with 4 and with 16 lanes: 8,000
+// agents on 512^2 cells 27.6 and 25.8 us, 20,000 on 1024^2 49.2 and 48.8, 45,000
+// there 53.3 and 55.9; the launch for 36 sites of 128^2 with 36,000 12.2 and 15.2),
+// 4 up to 2^18 agents, then 1, where the agents' own work fills the chip (the
+// launch for 300,000 with 1, 4 and 16 lanes: 64.5, 71.5 and 117 us).
 int ped_lanes(int64_t total_agents)
 {
     return total_agents <= 20480 ? 16 : total_agents <= 262144 ? 4 : 1;
@@ -1255,7 +1244,7 @@ hipError_t launch_bin_place_all(const Batch& b, hipStream_t s)
 hipError_t launch_bin_chunk_scan(const Batch& b, hipStream_t s)
 {
     if (b.total_chunks > 0)
-        hipLaunchKernelGGL(bin_chunk_scan_kernel, dim3(b.total_chunks), dim3(kChunkThreads), 0, s, b);
+        hipLaunchKernelGGL(bin_chunk_scan_kernel, dim3(b.total_chunks), dim3(kScanThreads), 0, s, b);
     return hipGetLastError();
 }
 hipError_t launch_bin_sort_all(const Batch& b, hipStream_t s)
