@@ -1000,11 +1000,11 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
 {
     if (blockIdx.y > 1) {
         const int64_t row = (int64_t)blockIdx.z * ((int)gridDim.y - 2) + (int)blockIdx.y - 2;
-        const int64_t at = row * (int)gridDim.x + (int)blockIdx.x;
+        const int64_t at = (row * (int)gridDim.x + (int)blockIdx.x) * kChunkWaves + (int)(threadIdx.x >> 6);
         if (at >= B.total_chunks) return;
-        const int g = (int)at;
+        const int g = __builtin_amdgcn_readfirstlane((int)at);
         const int sc = kOne ? 0 : find_scenario(B.chunk_off, B.S, g);
-        block_chunk_sum(scn_at<kOne>(B, sc).bins, g - (kOne ? 0 : B.chunk_off[sc]));
+        wave_chunk_sum(scn_at<kOne>(B, sc).bins, g - (kOne ? 0 : B.chunk_off[sc]));
         return;
     }
     if (blockIdx.z > 0) return;
@@ -1342,23 +1342,28 @@ hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t 
     return hipGetLastError();
 }
 
-// Rows per wave before any tuning: the longest march (fewest halo rows) that
-// still gives the chip kMinWaves waves, at most 16 rows.  Measured flood
-// launches (us) at 1, 2, 4, 8, 16, 32 rows:
-//   128^2 x 2     3.9   4.5   5.6   7.7  12.2   21
-//   512^2         6.1   6.1   6.9   8.2  12.6   22
-//   1531 x 977   19.1  16.0  15.4  17.7  19.0   24
-//   2048^2         43    33    30    31    33   39
-//   6 x 2048^2    365   273   223   200   193  201
-//   8192^2        663   509   480   423   417  442
-// (before: 16 rows at 2048^2, 64 at 8192^2, never fewer than 4).
+// Rows per wave before any tuning: the longest march (fewest halo rows and
+// partials) that still leaves enough waves to fill the chip and hide its loads;
+// the fewer rows, the more a halving costs, so the fewer waves will do.
+// Measured, a whole step (us) at 1, 2, 4, 8, 16 rows:
+//   400^2        13.8  14.6  14.8  17.4  22.4      1 (1,400 waves at 2)
+//   512^2        15.1  14.8  16.1  17.4  22.3      2 (2,304)
+//   700 x 500    16.5  15.1  16.2  17.5  22.6      2 (3,000)
+//   1811 x 364   23.0  18.3  17.7  19.7  22.7      4 (2,730)
+//   1024^2       26.9  24.7  21.5  23.0  26.8      4 (4,352)
+//   1531 x 977   31.5  27.9  24.4  26.8  27.7      4 (6,125; 3,075 at 8)
+//   1500^2       39.4  33.9  33.5  30.6  33.4      8 (4,700)
+//   2048^2       56.4  46.7  44.3  45.4  44.6      8 (8,704; 4,352 at 16; second order 86.7, 82.3, 83.6)
+//   3000^2      102.6  80.4  75.2  72.2  70.3     16 (9,212)
+// and the flood launch of 6 x 2048^2: 365, 273, 223, 200, 193 (201 at 32).  Beyond
+// 8,192 waves of one grid the partials take a launch more (fv_reduce_kernel).
 int fv_rows_per_wave(const fps_grid_desc* d, int S)
 {
-    constexpr int64_t kMinWaves = 6000;     // about the waves that fit the chip at 7 per SIMD
     for (int H = 16; H > 1; H >>= 1) {
+        const int64_t enough = H >= 16 ? 6000 : H >= 8 ? 4096 : H >= 4 ? 2560 : 2300;
         int64_t tiles = 0;
         for (int k = 0; k < S; ++k) tiles += fv_tiles(d[k].nx, d[k].ny, H);
-        if (tiles >= kMinWaves) return H;
+        if (tiles >= enough) return H;
     }
     return 1;
 }
@@ -1381,7 +1386,8 @@ hipError_t launch_finalize(const Batch& b, int mode, int s_first, int count, hip
     // rows of blocks: the states; after a step, where there are such, the LDS
     // binnings and then the chunks (the kind by the row: a bound from the
     // arguments, read first, cost the state update 0.3 us)
-    const int chunks = mode == 0 ? (b.total_chunks + count - 1) / count : 0;
+    const int blocks = mode == 0 ? (b.total_chunks + kChunkWaves - 1) / kChunkWaves : 0;
+    const int chunks = (blocks + count - 1) / count;
     const bool bins = mode == 0 && (b.fin_lds_bytes > 0 || chunks > 0);
     constexpr int kRows = 32768;      // rows of chunks a layer (a grid has at most 65,535)
     const dim3 grid(count, 1 + (int)bins + std::min(chunks, kRows), std::max((chunks + kRows - 1) / kRows, 1));
