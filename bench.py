@@ -475,14 +475,16 @@ def probe_section(args, stream):
     bsim.set_order(2)
     bms_o2 = bsim.time_flood(args.probe_steps)
     bcells = args.probe_n * args.probe_n
-    bach = FV_BYTES_PER_CELL * bcells / (bms * 1e-3) / 1e9
+    bpc = FV_BYTES_PER_CELL - 4      # nobody on this grid: the evacuee counts are not read
+    bach = bpc * bcells / (bms * 1e-3) / 1e9
     probe = {"workload": f"wet_probe_{args.probe_n} (fully wet dam break, {bcells} cells)",
              "rows_per_wave": brows,
              "ms_per_launch": bms, "cell_updates_per_s": bcells / (bms * 1e-3),
              "achieved_GBs": bach, "frac": bach / HBM_PEAK_GBS,
              "hll_flux_ms_per_launch": bms_hll,
              "second_order_ms_per_step": bms_o2,
-             "working_set_MB": (FV_BYTES_PER_CELL + 12) * bcells / 1e6}
+             "bytes_per_cell": bpc,
+             "working_set_MB": (bpc + 12) * bcells / 1e6}
     bsim.close()
     del bsim
     torch.cuda.empty_cache()

@@ -20,10 +20,13 @@
 // Before the flood, walkers of the door flow (sec. 3.2) walk at their own
 // speed to the door they leave by; the door kernel below lets free slots in.
 //
-// Binning is a stable counting sort by (bin, agent id): integer histogram with
-// atomic ranks, one-block exclusive scan, placement by rank, then each agent
-// finds its final slot by counting the smaller ids of its own bin, so the
-// result is deterministic and equal to a stable sort.
+// Binning is a stable counting sort by (bin, agent id): integer histogram,
+// exclusive scan, placement, then each agent finds its final slot by counting
+// the smaller ids of its own bin, so the result is deterministic and equal to a
+// stable sort.  Up to 8192 agents and 65,536 bins one block of the end of step
+// does it in LDS, from the agents' keys; beyond, the kernels below do, with
+// ranks from the histogram's atomics and the scan by many blocks (by one block
+// where the bins are rebuilt after the agents were set).
 #include "fps_device.h"
 
 // No contraction of a * b + c into fused multiply-adds in this file: the
