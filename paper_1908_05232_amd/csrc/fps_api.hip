@@ -93,7 +93,7 @@ struct Engine {
     std::vector<int> tile_off_h, agent_off_h, chunk_off_h;
     int total_tiles = 0, total_agents = 0, total_chunks = 0, red_chunks = 0, fv_blocks = 0;
     int64_t max_cells = 0;
-    int fin_lds_bytes = 0;
+    int fin_lds_bytes = 0, fin_tiles = 0;
     bool any_big = false;
     bool any_doors = false;          // some scenario runs the pre-flood door flow
     bool dirty = true;
@@ -405,6 +405,7 @@ int upload(Engine* e)
     e->people = false;
     e->red_chunks = 0;
     e->fin_lds_bytes = 0;
+    e->fin_tiles = 0;
     for (int k = 0; k < e->S; ++k) {
         fps_sim* s = e->m[k];
         fill_scn(s, e->scn_h[k]);
@@ -417,8 +418,10 @@ int upload(Engine* e)
         e->chunk_off_h[k + 1] = e->chunk_off_h[k] + e->scn_h[k].bins.nchunk;
         e->any_big = e->any_big || (s->na > 0 && !e->scn_h[k].lds_bins);
         e->any_doors = e->any_doors || e->scn_h[k].ped.n_door > 0;
-        if (e->scn_h[k].lds_bins)
-            e->fin_lds_bytes = std::max(e->fin_lds_bytes, lds_bin_bytes(s->nbins, s->na));
+        if (e->scn_h[k].lds_bins) {
+            e->fin_lds_bytes = std::max(e->fin_lds_bytes, lds_bin_bytes(std::min(s->nbins, kLdsTile), s->na));
+            e->fin_tiles = std::max(e->fin_tiles, (s->nbins + kLdsTile - 1) / kLdsTile);
+        }
     }
     HIPCHK_E(e, prepare_finalize(e->fin_lds_bytes));
     e->total_tiles = e->tile_off_h[e->S];
@@ -451,6 +454,7 @@ Batch batch_of(const Engine* e, int s_only = -1)
     b.total_agents = e->total_agents;
     b.fv_blocks = e->fv_blocks;
     b.fin_lds_bytes = e->fin_lds_bytes;
+    b.fin_tiles = e->fin_tiles;
     b.s_only = s_only;
     b.hll = e->hll;
     b.order2 = e->order2;

@@ -298,36 +298,36 @@ __device__ inline void sort_agent(const BinParams& b, int a)
     *(FPS_GLOBAL Float2*)&b.xy[f] = Float2{b.x[a], b.y[a]};
 }
 
-// One-block binning in LDS (at most kLdsBins bins and kLdsAgents agents), run
-// by a block of its own beside the end-of-step state update.  It starts from
-// the agents' bin keys alone: a histogram by LDS atomics, the exclusive scan,
-// the placement by LDS atomics and the stable order by id; only the results are
-// stored.  Being a function of the keys, it gives the same bins however often
-// it runs on them (a scenario that did not step keeps its bins).  Same results
-// as the global binning.
+// Binning in LDS (at most kLdsAgents agents and kLdsBins bins), run by blocks of
+// their own beside the end-of-step state update, one for every kLdsTile bins.
+// A block starts from the agents' bin keys alone: the agents in the bins before
+// its own (counted from the keys: no block waits for another), a histogram by
+// LDS atomics, the exclusive scan, the placement by LDS atomics and the stable
+// order by id; only the results are stored.  Being a function of the keys, it
+// gives the same bins however often it runs on them (a scenario that did not
+// step keeps its bins).  Same results as the global binning.
 // A count, a start and an agent's number here are at most kLdsAgents, so bins
-// are held two to a word and agents in 16 bits: 65,536 bins (a 1024^2 grid of
-// 0.25 m cells) and 8192 agents take 144 KB.  The scan goes by tiles of sixteen
-// bins a thread (8 words), all tiles between the same two barriers.  Bound by
-// the chain keys - histogram - scan - placement - order, in one launch that the
+// are held two to a word and agents in 16 bits: at most 48 KB.  Bound by the
+// chain keys - histogram - scan - placement - order, in one launch that the
 // state update needs anyway.  Measured, a step of one centre of 576^2 / 724^2 /
-// 1024^2 cells with 2,000 to 3,000 people: 23.7 / 30.6 / 38.6 us; with the global
+// 1024^2 / 1400^2 cells with 2,000 to 3,000 people: 21.5 / 23.5 / 28.0 / 33.4 us; with one
+// block for all bins 21.6 / 24.5 / 31.8 (and four launches, 45.2, beyond 65,536 bins); with the global
 // histogram scanned and placed by one block, or beyond 32,768 bins by four
 // launches, 36.7 / 43.6 / 48.5 (about 2 of the difference are the flood march's).
-constexpr int kLdsTile = 16 * kScanThreads;
-
-template <int TILES>
-__device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
+__device__ __forceinline__ void lds_bins_build(const BinParams b, int tile)      // by value: not reloaded after the stores
 {
-    constexpr int APT = kLdsAgents / kScanThreads;
+    constexpr int APT = kLdsAgents / kScanThreads, W = kScanThreads / kWave;
+    static_assert(kLdsTile == 16 * kScanThreads && W == 16, "sixteen bins a thread, a wave total a lane of a row");
     extern __shared__ uint4 fin_lds4[];
-    uint32_t* lb = reinterpret_cast<uint32_t*>(fin_lds4);      // halves [nbins]: counts, then starts, then ends
-    const int nw = lds_bin_words(b.nbins);
-    uint16_t* lp = reinterpret_cast<uint16_t*>(lb + nw);       // [na]: agents by bin, unordered
-    __shared__ int wtot[TILES][kScanThreads / kWave];
+    const int base = tile * kLdsTile, nb = min(b.nbins - base, kLdsTile);      // the block's bins
+    uint32_t* lb = reinterpret_cast<uint32_t*>(fin_lds4);      // halves [nb]: counts, then starts, then ends
+    const int nw = lds_bin_words(nb);
+    uint16_t* lp = reinterpret_cast<uint16_t*>(lb + nw);       // the block's agents by bin, unordered
+    __shared__ int wtot[W], wbelow[W];
     const int lane = threadIdx.x & (kWave - 1), wid = threadIdx.x >> 6;
-    int key[APT];
+    int key[APT];      // within the block's bins, or -1
     float ax[APT], ay[APT];
+    int below = 0;     // agents of the wave in bins before the block's
 #pragma unroll
     for (int q = 0; q < APT; ++q) {
         const int a = threadIdx.x + q * kScanThreads;
@@ -339,64 +339,52 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
         }
     }
     for (int v = threadIdx.x; v < nw / 4; v += kScanThreads) fin_lds4[v] = make_uint4(0, 0, 0, 0);
+#pragma unroll
+    for (int q = 0; q < APT; ++q) {
+        below += __popcll(__ballot(key[q] >= 0 && key[q] < base));
+        key[q] = key[q] >= base && key[q] - base < nb ? key[q] - base : -1;
+    }
     __syncthreads();
 #pragma unroll
     for (int q = 0; q < APT; ++q)
         if (key[q] >= 0) atomicAdd(&lb[key[q] >> 1], 1u << (key[q] & 1) * 16);
     __syncthreads();
-    // sixteen bins of each tile a thread; vectors past the last bin count
-    // nothing.  The counts are read again when the starts are formed: held over
-    // the barrier they spilled.
-    auto counts = [&](int t, uint32_t (&h)[8]) {
-        const int v0 = (t * kLdsTile + 16 * (int)threadIdx.x) / 8;
+    // sixteen bins a thread; vectors past the last bin count nothing
+    const int k0 = 16 * (int)threadIdx.x, v0 = k0 / 8;
+    uint32_t hist[8];
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const uint4 w = v0 + q < nw / 4 ? fin_lds4[v0 + q] : make_uint4(0, 0, 0, 0);
-            h[4 * q] = w.x; h[4 * q + 1] = w.y; h[4 * q + 2] = w.z; h[4 * q + 3] = w.w;
-        }
-    };
-    int incl[TILES], own[TILES];
+    for (int q = 0; q < 2; ++q) {
+        const uint4 w = v0 + q < nw / 4 ? fin_lds4[v0 + q] : make_uint4(0, 0, 0, 0);
+        hist[4 * q] = w.x; hist[4 * q + 1] = w.y; hist[4 * q + 2] = w.z; hist[4 * q + 3] = w.w;
+    }
+    int own = 0;
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) {
-        uint32_t hist[8];
-        counts(t, hist);
-        own[t] = 0;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) own[t] += (int)(hist[e] & 0xffffu) + (int)(hist[e] >> 16);
-        incl[t] = wave_inclusive_scan(own[t]);
-        if (lane == kWave - 1) wtot[t][wid] = incl[t];
+    for (int e = 0; e < 8; ++e) own += (int)(hist[e] & 0xffffu) + (int)(hist[e] >> 16);
+    const int incl = wave_inclusive_scan(own);
+    if (lane == kWave - 1) {
+        wtot[wid] = incl;
+        wbelow[wid] = below;
     }
     __syncthreads();
-    int carry = 0;      // agents before the tile
+    // the waves' totals: one a lane, scanned within the row of sixteen lanes
+    const int tot = wave_inclusive_scan(wtot[lane & (W - 1)]);
+    const int carry = __builtin_amdgcn_readlane(wave_inclusive_scan(wbelow[lane & (W - 1)]), W - 1);
+    const int total = __builtin_amdgcn_readlane(tot, W - 1);
+    int run = incl - own + (wid > 0 ? __builtin_amdgcn_readlane(tot, max(wid - 1, 0)) : 0);
 #pragma unroll
-    for (int t = 0; t < TILES; ++t) {
-        const int k0 = t * kLdsTile + 16 * (int)threadIdx.x;
-        // the waves' totals: one a lane, scanned within the row of sixteen lanes
-        const int tot = wave_inclusive_scan(wtot[t][lane & (kScanThreads / kWave - 1)]);
-        int run = carry + incl[t] - own[t] + (wid > 0 ? __builtin_amdgcn_readlane(tot, max(wid - 1, 0)) : 0);
-        carry += __builtin_amdgcn_readlane(tot, kScanThreads / kWave - 1);
-        if (k0 >= b.nbins) continue;
-        uint32_t hist[8];
-        counts(t, hist);
-        int start[16];
+    for (int q = 0; q < 2; ++q) {
+        uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            start[2 * e] = run;
-            run += (int)(hist[e] & 0xffffu);
-            start[2 * e + 1] = run;
-            run += (int)(hist[e] >> 16);
+        for (int e = 0; e < 4; ++e) {
+            const uint32_t h = hist[4 * q + e];
+            w[e] = (uint32_t)run;
+            run += (int)(h & 0xffffu);
+            w[e] |= (uint32_t)run << 16;
+            run += (int)(h >> 16);
         }
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            uint4 w;
-            w.x = (uint32_t)start[8 * q] | (uint32_t)start[8 * q + 1] << 16;
-            w.y = (uint32_t)start[8 * q + 2] | (uint32_t)start[8 * q + 3] << 16;
-            w.z = (uint32_t)start[8 * q + 4] | (uint32_t)start[8 * q + 5] << 16;
-            w.w = (uint32_t)start[8 * q + 6] | (uint32_t)start[8 * q + 7] << 16;
-            if (k0 / 8 + q < nw / 4) fin_lds4[k0 / 8 + q] = w;
-        }
+        if (v0 + q < nw / 4) fin_lds4[v0 + q] = make_uint4(w[0], w[1], w[2], w[3]);
     }
-    if (threadIdx.x == 0) b.bin_start[b.nbins] = carry;
+    if (threadIdx.x == 0 && base + nb == b.nbins) b.bin_start[b.nbins] = carry + total;
     __syncthreads();
     // unordered placement: each agent takes the next free slot of its bin;
     // afterwards half k is the end of bin k (= start of bin k + 1)
@@ -410,16 +398,16 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
     __syncthreads();
     // the starts, four bins a lane and whole lines a wave: stored by the thread
     // that scanned them, every lane's sixteen bytes are a request of their own
-    // (65,536 bins: 17.2 us a launch against 13.3)
-    for (int v = threadIdx.x; v < (b.nbins + 3) / 4; v += kScanThreads) {
+    // (65,536 bins by one block: 17.2 us a launch against 13.3)
+    for (int v = threadIdx.x; v < (nb + 3) / 4; v += kScanThreads) {
         const uint32_t w0 = v > 0 ? lb[2 * v - 1] >> 16 : 0u, w1 = lb[2 * v], w2 = lb[2 * v + 1];
-        const Int4 st = {(int)w0, (int)(w1 & 0xffffu), (int)(w1 >> 16), (int)(w2 & 0xffffu)};
-        if (4 * v + 4 <= b.nbins) {
-            *(FPS_GLOBAL Int4*)&b.bin_start[4 * v] = st;
+        const Int4 st = {carry + (int)w0, carry + (int)(w1 & 0xffffu), carry + (int)(w1 >> 16), carry + (int)(w2 & 0xffffu)};
+        if (4 * v + 4 <= nb) {
+            *(FPS_GLOBAL Int4*)&b.bin_start[base + 4 * v] = st;
         } else {
 #pragma unroll
             for (int e = 0; e < 4; ++e)
-                if (4 * v + e < b.nbins) b.bin_start[4 * v + e] = st[e];
+                if (4 * v + e < nb) b.bin_start[base + 4 * v + e] = st[e];
         }
     }
     // stable order: an agent's slot counts the smaller ids of its bin
@@ -430,20 +418,12 @@ __device__ __forceinline__ void lds_bins_tiles(const BinParams& b)
         if (k < 0) continue;
         const int a = threadIdx.x + q * kScanThreads;
         const int s0 = k > 0 ? end(k - 1) : 0, s1 = end(k);
-        int below = 0;
-        for (int s = s0; s < s1; ++s) below += lp[s] < a;
-        const int f = s0 + below;
+        int smaller = 0;
+        for (int s = s0; s < s1; ++s) smaller += lp[s] < a;
+        const int f = carry + s0 + smaller;
         b.slot[a] = f;
         *(FPS_GLOBAL Float2*)&b.xy[f] = Float2{ax[q], ay[q]};
     }
-}
-
-__device__ inline void lds_bins_build(const BinParams b)      // by value: not reloaded after the stores
-{
-    static_assert(kLdsBins == 4 * kLdsTile, "at most four tiles");
-    if (b.nbins <= kLdsTile) lds_bins_tiles<1>(b);
-    else if (b.nbins <= 2 * kLdsTile) lds_bins_tiles<2>(b);
-    else lds_bins_tiles<4>(b);
 }
 
 }  // namespace fps

@@ -989,7 +989,7 @@ __device__ double wave_hydro_integral(int nh, double tk, double qk, double a, do
 }
 
 // End of a step: a row of blocks, one per scenario, updates the states; beside
-// them, a second row rebuilds the neighbour bins of scenarios binned in LDS, and
+// them, the next rows rebuild the neighbour bins of scenarios binned in LDS, and
 // further rows count the chunks of the others (they share no data).  The state update
 // reduces the flood partials in a fixed order, advances time, sets the next CFL
 // time step (sec. 3) and inflow depth, and applies the sandbag drops of the step
@@ -998,8 +998,15 @@ __device__ double wave_hydro_integral(int nh, double tk, double qk, double a, do
 template <bool kOne>
 __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mode, int s_first)
 {
-    if (blockIdx.y > 1) {
-        const int64_t row = (int64_t)blockIdx.z * ((int)gridDim.y - 2) + (int)blockIdx.y - 2;
+    if (blockIdx.y > 0) {
+        const int r = (int)blockIdx.y - 1, tiles = B.fin_tiles;
+        if (r < tiles) {
+            if (blockIdx.z > 0) return;
+            const Scn& S = scn_at<kOne>(B, s_first + blockIdx.x);
+            if (S.lds_bins && r * kLdsTile < S.bins.nbins) lds_bins_build(S.bins, r);
+            return;
+        }
+        const int64_t row = (int64_t)blockIdx.z * ((int)gridDim.y - 1 - tiles) + r - tiles;
         const int64_t at = (row * (int)gridDim.x + (int)blockIdx.x) * kChunkWaves + (int)(threadIdx.x >> 6);
         if (at >= B.total_chunks) return;
         const int g = __builtin_amdgcn_readfirstlane((int)at);
@@ -1010,10 +1017,6 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     if (blockIdx.z > 0) return;
     const int sc = s_first + blockIdx.x;
     const Scn& S = scn_at<kOne>(B, sc);
-    if (blockIdx.y == 1) {
-        if (S.lds_bins) lds_bins_build(S.bins);
-        return;
-    }
     // the parameters used, in registers: loaded in the first round, not
     // reloaded after the stores below
     const FvParams& p = S.fv;
@@ -1388,10 +1391,10 @@ hipError_t launch_finalize(const Batch& b, int mode, int s_first, int count, hip
     // arguments, read first, cost the state update 0.3 us)
     const int blocks = mode == 0 ? (b.total_chunks + kChunkWaves - 1) / kChunkWaves : 0;
     const int chunks = (blocks + count - 1) / count;
-    const bool bins = mode == 0 && (b.fin_lds_bytes > 0 || chunks > 0);
+    const int tiles = mode == 0 ? b.fin_tiles : 0;
     constexpr int kRows = 32768;      // rows of chunks a layer (a grid has at most 65,535)
-    const dim3 grid(count, 1 + (int)bins + std::min(chunks, kRows), std::max((chunks + kRows - 1) / kRows, 1));
-    const int lds = bins ? b.fin_lds_bytes : 0;
+    const dim3 grid(count, 1 + tiles + std::min(chunks, kRows), std::max((chunks + kRows - 1) / kRows, 1));
+    const int lds = mode == 0 ? b.fin_lds_bytes : 0;
     if (b.S == 1) hipLaunchKernelGGL(finalize_kernel<true>, grid, dim3(kScanThreads), lds, s, b, mode, s_first);
     else hipLaunchKernelGGL(finalize_kernel<false>, grid, dim3(kScanThreads), lds, s, b, mode, s_first);
     return hipGetLastError();

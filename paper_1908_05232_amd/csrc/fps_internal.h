@@ -26,8 +26,9 @@ constexpr int kSlots = 16;             // partial sums of an agent's forces (the
 constexpr int kScanThreads = 1024;
 constexpr int kMaxHydro = 64;
 constexpr int kMaskBits = 128;         // obstacle bitmask per cell (uint4)
-constexpr int kLdsAgents = 8192;       // agents and bins binned in LDS by a block of the end of step
-constexpr int kLdsBins = 65536;
+constexpr int kLdsAgents = 8192;       // agents and bins binned in LDS by blocks of the end of step
+constexpr int kLdsTile = 16 * kScanThreads;   // bins a block
+constexpr int kLdsBins = 16 * kLdsTile;       // (a launch has as many rows of blocks as its largest member needs)
 // dynamic LDS of that binning: halves per bin in whole 16-byte vectors, halves per agent
 __host__ __device__ constexpr int lds_bin_words(int nbins) { return (nbins + 7) / 8 * 4; }
 __host__ __device__ constexpr int lds_bin_bytes(int nbins, int na) { return 4 * lds_bin_words(nbins) + (2 * na + 3) / 4 * 4; }
@@ -214,6 +215,7 @@ struct Batch {
     int red_chunks;        // chunks of partials of the largest scenario that reduces them in two levels (0: none)
     int fv_blocks;         // launched flood blocks: a multiple of 8 covering total_tiles
     int fin_lds_bytes;     // dynamic LDS of the finalize launch (LDS binning)
+    int fin_tiles;         // LDS binning blocks of the largest scenario binned so (0: none)
     int s_only;            // >= 0: restrict the flood launch to one scenario (tuning)
     Scn one;               // S == 1: the scenario itself, read from the kernel arguments
     int hll;               // face flux: HLL (1) or HLLC (0), the same for every scenario

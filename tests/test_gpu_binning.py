@@ -1,5 +1,5 @@
 """The neighbour bins after a step against the oracle's stable counting sort, at
-the edges of the paths: one, two and four tiles of the LDS binning, its largest
+the edges of the paths: one to sixteen tiles of the LDS binning, its largest
 numbers of bins and agents, and the grids just past them, which are scanned by
 many blocks."""
 import numpy as np
@@ -14,7 +14,7 @@ pytestmark = pytest.mark.gpu
 # cells a side, bins (4 x 4 cells each), agents
 @pytest.mark.parametrize("n,nbins,agents", [
     (512, 128 ** 2, 2000), (516, 129 ** 2, 2000), (724, 181 ** 2, 8192), (728, 182 ** 2, 1), (1024, 256 ** 2, 8192),
-    (724, 181 ** 2, 8193), (1028, 257 ** 2, 500)])
+    (724, 181 ** 2, 8193), (1028, 257 ** 2, 500), (2048, 512 ** 2, 3000), (2052, 513 ** 2, 300)])
 def test_bins_at_the_edges_of_the_paths(oracle, n, nbins, agents):
     sc = I.shopping_centre(n=n, dx=0.25, seed=n, n_evac=agents, q_peak=20.0)
     sim = fps.Sim(sc)
@@ -48,10 +48,10 @@ def test_crowded_bins_keep_the_stable_order(oracle):
 
 
 def test_stopped_member_with_many_bins_keeps_them(oracle):
-    """A member beyond the LDS binning (66,049 bins in 17 chunks) stops while one
-    with as many, and one binned in LDS, step on."""
+    """A member beyond the LDS binning (8,300 agents; 66,049 bins in 17 chunks) stops
+    while one with as many bins, and one binned in LDS, step on."""
     scs = [I.shopping_centre(n=n, dx=0.25, seed=n + k, n_evac=m, q_peak=20.0)
-           for k, (n, m) in enumerate(((1028, 500), (64, 50), (1028, 9000)))]
+           for k, (n, m) in enumerate(((1028, 8300), (64, 50), (1028, 9000)))]
     ens = fps.Ensemble(scs)
     ens[0].set_end_time(1.0)
     ens.step(60)
