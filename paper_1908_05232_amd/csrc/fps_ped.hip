@@ -23,8 +23,8 @@
 // Binning is a stable counting sort by (bin, agent id): integer histogram,
 // exclusive scan, placement, then each agent finds its final slot by counting
 // the smaller ids of its own bin, so the result is deterministic and equal to a
-// stable sort.  Up to 8192 agents and 65,536 bins one block of the end of step
-// does it in LDS, from the agents' keys; beyond, the kernels below do, with
+// stable sort.  Up to 8192 agents and 262,144 bins blocks of the end of step
+// do it in LDS, from the agents' keys; beyond, the kernels below do, with
 // ranks from the histogram's atomics and the scan by many blocks (by one block
 // where the bins are rebuilt after the agents were set).
 #include "fps_device.h"
