@@ -280,11 +280,11 @@ __device__ __forceinline__ double wave_sum(double v)
 }
 // Maximum of non-negative floats (the wave speeds): their bit patterns order
 // as the values do, so an unsigned maximum of the bits serves (one
-// instruction; a NaN, above every finite pattern, comes through to the time
-// step check).  The rows a broadcast skips receive 0 = +0.0.
-__device__ __forceinline__ float wave_max(float v)
+// instruction; a NaN, above every finite pattern, comes through, and every
+// later level keeps it in the same way: the end of the step sees it and latches
+// the fault).  The rows a broadcast skips receive 0 = +0.0.
+__device__ __forceinline__ float wave_max_bits(unsigned u)
 {
-    unsigned u = __builtin_bit_cast(unsigned, v);
     u = max(u, (unsigned)dpp_i32<kQuadSwap1, 0xF>((int)u));
     u = max(u, (unsigned)dpp_i32<kQuadSwap2, 0xF>((int)u));
     u = max(u, (unsigned)dpp_i32<kRowHalfMirror, 0xF>((int)u));
@@ -293,6 +293,9 @@ __device__ __forceinline__ float wave_max(float v)
     u = max(u, (unsigned)dpp_i32<kRowBcast31, 0xC>((int)u));
     return __builtin_bit_cast(float, __builtin_amdgcn_readlane((int)u, kWave - 1));
 }
+__device__ __forceinline__ float wave_max(float v) { return wave_max_bits(__builtin_bit_cast(unsigned, v)); }
+// the bits of a partial's wave speed (partials hold FP32 speeds as doubles)
+__device__ __forceinline__ unsigned speed_bits(double s) { return __builtin_bit_cast(unsigned, (float)s); }
 
 // Blocks are handed to the 8 XCDs round-robin by block id; this mapping gives
 // each XCD a contiguous run of tiles (a band of rows), so the halo columns and
@@ -525,7 +528,7 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
         // one flag per group of blocks; every wet wave of the group stores the
         // same 1 with a plain store (no read-modify-write, nothing to wait for:
         // the wave ends as soon as its stores are issued)
-        if (smax > 0.0f) st_at(gmem(p.wet), (uint32_t)(kWetStride * (blockIdx.x & (kWetSlots - 1))), 1);
+        if (!(smax <= 0.0f)) st_at(gmem(p.wet), (uint32_t)(kWetStride * (blockIdx.x & (kWetSlots - 1))), 1);
     }
 }
 
@@ -855,7 +858,7 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
         part[1] = vo1 + vout_acc;
         part[2] = vc1 + vclip_acc;
         part[3] = (double)smax;
-        if (smax > 0.0f) st_at(gmem(p.wet), (uint32_t)(kWetStride * (blockIdx.x & (kWetSlots - 1))), 1);
+        if (!(smax <= 0.0f)) st_at(gmem(p.wet), (uint32_t)(kWetStride * (blockIdx.x & (kWetSlots - 1))), 1);
     }
 }
 
@@ -923,27 +926,29 @@ __global__ __launch_bounds__(kFvBlock) void fv_reduce_kernel(Batch B, int s_firs
         a[u] = P2[2 * b];
         c[u] = P2[2 * b + 1];
     }
-    double m = 0.0, vo = 0.0, vc = 0.0, sm = 0.0;
+    double m = 0.0, vo = 0.0, vc = 0.0;
+    unsigned sm = 0;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         if (t0 + (int)threadIdx.x + u * kFvBlock < ntiles) {
             m += a[u].x;
             vo += a[u].y;
             vc += c[u].x;
-            sm = fmax(sm, c[u].y);
+            sm = max(sm, speed_bits(c[u].y));
         }
     }
-    __shared__ double red[kFvBlock / kWave][4];
+    __shared__ double red[kFvBlock / kWave][3];
+    __shared__ unsigned redsm[kFvBlock / kWave];
     m = wave_sum(m);
     vo = wave_sum(vo);
     vc = wave_sum(vc);
-    sm = (double)wave_max((float)sm);
+    sm = __builtin_bit_cast(unsigned, wave_max_bits(sm));
     if ((threadIdx.x & (kWave - 1)) == 0) {
         const int w = threadIdx.x >> 6;
         red[w][0] = m;
         red[w][1] = vo;
         red[w][2] = vc;
-        red[w][3] = sm;
+        redsm[w] = sm;
     }
     __syncthreads();      // every partial of the block has been read
     if (threadIdx.x == 0) {
@@ -951,10 +956,10 @@ __global__ __launch_bounds__(kFvBlock) void fv_reduce_kernel(Batch B, int s_firs
             m += red[w][0];
             vo += red[w][1];
             vc += red[w][2];
-            sm = fmax(sm, red[w][3]);
+            sm = max(sm, redsm[w]);
         }
         P2[2 * t0] = make_double2(m, vo);
-        P2[2 * t0 + 1] = make_double2(vc, sm);
+        P2[2 * t0 + 1] = make_double2(vc, (double)__builtin_bit_cast(float, sm));
     }
 }
 
@@ -1057,7 +1062,8 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
     const uint32_t word = ((const FPS_GLOBAL uint32_t*)gst)[threadIdx.x < kCopy ? cw : 0];
     const double hk_t = gst->hyd_t[lane], hk_q = gst->hyd_q[lane];
     // the flood partials summed in tile order
-    double m = 0.0, vo = 0.0, vc = 0.0, sm = 0.0;
+    double m = 0.0, vo = 0.0, vc = 0.0;
+    unsigned sm = 0;      // the largest wave speed, as bits
     {
         constexpr int kPU = 8;
         const FPS_GLOBAL Double2* P2 = (const FPS_GLOBAL Double2*)partials;
@@ -1075,7 +1081,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
                 m += a[u].x;
                 vo += a[u].y;
                 vc += c[u].x;
-                sm = fmax(sm, c[u].y);
+                sm = max(sm, speed_bits(c[u].y));
             }
         }
         for (int b = threadIdx.x + kPU * kScanThreads; b < ntiles; b += kScanThreads) {
@@ -1083,7 +1089,7 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
             m += q[0];
             vo += q[1];
             vc += q[2];
-            sm = fmax(sm, q[3]);
+            sm = max(sm, speed_bits(q[3]));
         }
     }
     __syncthreads();
@@ -1096,34 +1102,34 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
         m = 0.0;
         vo = 0.0;
         vc = 0.0;
-        sm = 0.0;
+        sm = 0;
     }
     // the pedestrians of this step have read the wetness flags: clear them
     if (threadIdx.x < kWetSlots) wet[kWetStride * threadIdx.x] = 0;
-    __shared__ double red[kScanThreads / kWave][4];
+    __shared__ double red[kScanThreads / kWave][3];
+    __shared__ unsigned redsm[kScanThreads / kWave];
     m = wave_sum(m);
     vo = wave_sum(vo);
     vc = wave_sum(vc);
-    sm = (double)wave_max((float)sm);     // the partials hold FP32 wave speeds
+    sm = __builtin_bit_cast(unsigned, wave_max_bits(sm));
     if (lane == 0) {
         red[wid][0] = m;
         red[wid][1] = vo;
         red[wid][2] = vc;
-        red[wid][3] = sm;
+        redsm[wid] = sm;
     }
     __syncthreads();
     if (wid == 0) {
         // the serial end of the step, on every lane of the first wave (same
         // values); lane 0 stores
-        // lanes 0-3 combine one quantity each over the waves, in wave order
+        // lanes 0-2 add one quantity each over the waves, in wave order
         double acc = 0.0;
-        if (lane < 4) {
+        if (lane < 3) {
             acc = red[0][lane];
-            for (int w = 1; w < kScanThreads / kWave; ++w)
-                acc = lane == 3 ? fmax(acc, red[w][lane]) : acc + red[w][lane];
+            for (int w = 1; w < kScanThreads / kWave; ++w) acc += red[w][lane];
         }
-        const double M = readlane_f64(acc, 0), VO = readlane_f64(acc, 1), VC = readlane_f64(acc, 2),
-                     SM = readlane_f64(acc, 3);
+        const double M = readlane_f64(acc, 0), VO = readlane_f64(acc, 1), VC = readlane_f64(acc, 2);
+        const float smax = wave_max_bits(redsm[lane & (kScanThreads / kWave - 1)]);
         double t = st->t, v_out = st->v_out, v_clip = st->v_clip, v_in = st->v_in, mass = st->mass;
         int64_t step = st->step;
         float dt = st->dt, dt_prev = st->dt_prev;
@@ -1143,15 +1149,14 @@ __global__ __launch_bounds__(kScanThreads) void finalize_kernel(Batch B, int mod
             }
         }
         if (!skipped) {
-            const float smax = (float)SM;
             mass = M * dxdy;
-            any_wet = smax > 0.0f;
+            any_wet = !(smax <= 0.0f);
             dt = any_wet && !jmask ? fminf(cfl / smax, dt_max) : dt_max;
         }
         float inc = 0.0f;
         if (inflow_side >= 0)
             inc = (float)(wave_hydro_integral(st->nh, hk_t, hk_q, t, t + (double)dt) / (double)dn);
-        if (!isfinite(mass) || !(dt > 0.0f) || !isfinite(dt) || !(SM == SM)) status = FPS_E_NUMERIC;
+        if (!isfinite(mass) || !(dt > 0.0f) || !isfinite(dt) || !(smax == smax)) status = FPS_E_NUMERIC;
         if (lane == 0) {
             st->t = t;
             st->step = step;
