@@ -214,7 +214,9 @@ __device__ __forceinline__ float counted_friction(const FvParams& p, int npc)
 
 // Manning friction of a wet cell (kn = g n^2), splitting point-implicit with a
 // no-reversal limiter, on the discharges; u, v become the new velocities.
-// Still water: the guard keeps every factor finite, and nothing is taken off.
+// Still water: the reciprocal of its speed counts as 0, so nothing is taken off
+// and no factor overflows, however thin the film (1 / speed bounded by a
+// constant overflowed in dt Cf r / speed).
 __device__ __forceinline__ void friction(const FvParams& p, float dt, float kn, float hn, float& qx, float& qy,
                                          float& u, float& v)
 {
@@ -223,10 +225,11 @@ __device__ __forceinline__ void friction(const FvParams& p, float dt, float kn, 
     u = qx * r;
     v = qy * r;
     const float uu = u * u, vv = v * v;
-    const float speed = sqrt_fast(fmaxf(fmaf(u, u, vv), 1e-36f));
+    const float V2 = fmaf(u, u, vv);
+    const float speed = sqrt_fast(V2), rspeed = V2 > 0.0f ? rcp(speed) : 0.0f;
     const float Cf = kn * __builtin_amdgcn_exp2f(__builtin_amdgcn_logf(hn) * (-1.0f / 3.0f));
     const float Sx = u * -Cf * speed, Sy = v * -Cf * speed;
-    const float a = dt * Cf * r * rcp(speed);
+    const float a = dt * Cf * r * rspeed;
     const float Dx = fmaf(fmaf(u, u + u, vv), a, 1.0f), Dy = fmaf(fmaf(v, v + v, uu), a, 1.0f);
     float dqx = dt * Sx * rcp(Dx), dqy = dt * Sy * rcp(Dy);
     if (fabsf(dqx) > fabsf(qx)) dqx = -qx;
