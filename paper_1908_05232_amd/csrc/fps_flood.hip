@@ -36,6 +36,15 @@ struct Cell {
 };
 
 __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
+// A bed elevation as the faces use it: an infinite one (a block no water passes)
+// becomes NaN.  The positive and negative parts of a bed step (one instruction
+// each) carry a NaN through, so both sides of such a face are dry: a wall, and
+// water that lies on the block stays there.  With fmaxf and fminf, which drop a
+// NaN, the step between two such cells was none, and the reconstruction of a dry
+// cell beside one left a level bed to flow over.
+__device__ __forceinline__ float bed(float z) { return fmaf(z, 0.0f, z); }
+__device__ __forceinline__ float step_up(float dz) { return __builtin_elementwise_maximum(dz, 0.0f); }
+__device__ __forceinline__ float step_down(float dz) { return __builtin_elementwise_minimum(dz, 0.0f); }
 // A value used on a path that few waves take: what is computed from it stays
 // on that path (the compiler would otherwise compute it always, and select).
 __device__ __forceinline__ float rare(float x)
@@ -125,8 +134,8 @@ __device__ __forceinline__ void face_march(const FvParams& p, float hL, float un
 {
 #pragma clang fp contract(off)
     const float dz = zR - zL;
-    float hl = hL - fmaxf(dz, 0.0f);
-    float hr = hR + fminf(dz, 0.0f);
+    float hl = hL - step_up(dz);
+    float hr = hR + step_down(dz);
     const bool wetL = hl > p.eps, wetR = hr > p.eps;
     hl = wetL ? hl : 0.0f;
     hr = wetR ? hr : 0.0f;
@@ -174,8 +183,8 @@ __device__ __forceinline__ void face_lean(const FvParams& p, float hL, float unL
 {
 #pragma clang fp contract(off)
     const float dz = zR - zL;
-    float hl = hL - fmaxf(dz, 0.0f);
-    float hr = hR + fminf(dz, 0.0f);
+    float hl = hL - step_up(dz);
+    float hr = hR + step_down(dz);
     const bool wetL = hl > p.eps, wetR = hr > p.eps;
     hl = wetL ? hl : 0.0f;
     hr = wetR ? hr : 0.0f;
@@ -403,6 +412,7 @@ __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
         // walls) and the reciprocal depth
         auto prim = [&](const Cell& raw, int j, float& r) {
             Cell c = raw;
+            c.z = bed(raw.z);
             r = c.h > p.eps ? rcp(c.h) : 0.0f;
             if (side_strip && mirror_x) c.qx = -c.qx;
             if ((j < 0 && p.bc[2] == FPS_BC_WALL) || (j >= p.ny && p.bc[3] == FPS_BC_WALL)) c.qy = -c.qy;
@@ -673,7 +683,7 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
         c.qx = raw.qx;
         c.qy = raw.qy;
         c.v.h = raw.h;
-        c.v.eta = raw.h + raw.z;
+        c.v.eta = raw.h + bed(raw.z);
         c.v.u = raw.qx * r;
         c.v.v = raw.qy * r;
         if (mirror_x) c.v.u = -c.v.u;

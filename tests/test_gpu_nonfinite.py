@@ -1,12 +1,12 @@
 """Values that are not finite, or whose factors are not: a step that leaves NaN
 discharges is a numeric fault at once, whatever shares the wave; a film of still
-water has no friction however thin it is."""
+water has no friction however thin it is; a bed of infinite height is a wall."""
 import numpy as np
 import pytest
 import torch
 
 from paper_1908_05232_amd import fps, inputs as I
-from tests.gpu_util import say
+from tests.gpu_util import random_wet_dry, say
 
 pytestmark = pytest.mark.gpu
 
@@ -49,3 +49,31 @@ def test_film_of_still_water_stays_still(h_dry, depth, dt_max, dx, people, order
     h, qx, qy, _ = sim.fields()
     say(f"film of {depth} m: max|q| {np.abs(qx).max()}, {np.abs(qy).max()}, t {sim.diag()['t']}")
     assert np.all(h == np.float32(depth)) and np.all(qx == 0) and np.all(qy == 0)
+
+
+@pytest.mark.parametrize("order,depth", [(1, 0.0), (2, 0.0), (1, 0.01)])
+def test_infinite_bed_is_a_wall(order, depth):
+    """Blocks of cells whose bed is +inf, alone, in pairs, in large blocks and along the
+    sides, against the same cells 1,000 km high: the same bits everywhere else, and the
+    water that lies on them stays."""
+    nx, ny = 130, 70
+    sc = random_wet_dry(nx, ny, 0.5, seed=8, bc=(0, 1, 0, 1))
+    sc.desc.order = order
+    block = I.rng_of(9).random((ny, nx)) < 0.05
+    for j, i in ((10, 20), (30, 55), (40, 0), (0, 80), (64, 118)):
+        block[j:j + 6, i:i + 12] = True
+    for f in (sc.h, sc.qx, sc.qy):
+        f[block] = 0.0
+    out = []
+    for height, held in ((1e6, 0.0), (np.inf, depth)):
+        sc.z[block] = height
+        sc.h[block] = held
+        sim = fps.Sim(sc)
+        sim.step(20)
+        out.append((sim.fields()[:3], sim.diag()["t"]))
+    (ref, t), (got, ti) = out
+    say(f"order {order}, {int(block.sum())} cells, t {t:.4f} and {ti:.4f}")
+    assert t == ti
+    for a, b in zip(ref, got):
+        assert np.array_equal(a[~block], b[~block])
+    assert np.all(got[0][block] == np.float32(depth)) and np.all(got[1][block] == 0) and np.all(got[2][block] == 0)
