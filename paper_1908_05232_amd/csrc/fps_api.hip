@@ -74,7 +74,7 @@ struct fps_sim {
     int32_t n_door, door_rate;
     uint64_t door_seed;
     bool numeric_fault;
-    bool counts;               // evacuee counts were set since creation or the last clearing: they may be non-zero
+    bool counts;               // evacuee counts were set since creation: they may be non-zero
 };
 
 struct Engine {
@@ -510,9 +510,11 @@ struct KernelEvents {
 };
 
 // the launches of one step of every scenario
-int step_launches(Engine* e, hipStream_t st, KernelEvents* K)
+int step_launches(Engine* e, hipStream_t st, KernelEvents* K, bool by_caller = false)
 {
     Batch b = batch_of(e);
+    // steps that the caller captures may be replayed after counts were set: they read them
+    if (by_caller) b.people = 1;
     auto rec = [&](int k, int w) {
         if (K) (void)hipEventRecord(K->ev[k][w], st);
     };
@@ -611,8 +613,10 @@ int run_steps(Engine* e, int32_t n, KernelEvents* K)
         HIPCHK_E(e, hipEventRecord(e->ev_out, e->cap));
         HIPCHK_E(e, hipStreamWaitEvent(e->stream, e->ev_out, 0));
     }
+    hipStreamCaptureStatus by_caller = hipStreamCaptureStatusNone;
+    if (done < n && !e->people) HIPCHK_E(e, hipStreamIsCapturing(e->stream, &by_caller));
     for (; done < n; ++done) {
-        rc = step_launches(e, e->stream, K);
+        rc = step_launches(e, e->stream, K, by_caller != hipStreamCaptureStatusNone);
         if (rc != FPS_OK) return rc;
     }
     if (n > 0) HIPCHK_E(e, launch_sync_back(batch_of(e), e->max_cells, e->stream));
@@ -1477,10 +1481,13 @@ int fps_set_occupancy(fps_sim* s, const int32_t* counts)
     const size_t nc = (size_t)s->G.nx * s->G.ny;
     if (counts) HIPCHK(s, hipMemcpyAsync(s->np, counts, sizeof(int32_t) * nc, hipMemcpyDeviceToDevice, st));
     else HIPCHK(s, launch_fill_i32(s->np, 0, (int64_t)nc, st));
-    // whether the flood update reads the counts at all follows from here
-    if (s->counts != (counts != nullptr)) {
-        s->counts = counts != nullptr;
-        mark_dirty(s);
+    // from its first counts on, the flood update of the engine reads them; the
+    // records stay as they are (an upload would wait, and not in a capture), and
+    // only our own captured launches name the other kernel
+    if (counts) s->counts = true;
+    if (counts && !s->eng->people) {
+        s->eng->people = true;
+        drop_graph(s->eng);
     }
     return FPS_OK;
 }

@@ -220,7 +220,7 @@ struct Batch {
     Scn one;               // S == 1: the scenario itself, read from the kernel arguments
     int hll;               // face flux: HLL (1) or HLLC (0), the same for every scenario
     int order2;            // the second-order (MUSCL, two-stage) variant for every scenario
-    int people;            // some scenario has (or had) evacuee counts; else they are all zero
+    int people;            // some scenario may have evacuee counts; else they are all zero and not read
 };
 
 // launchers (stream-ordered, no synchronisation)
