@@ -175,7 +175,8 @@ __device__ __forceinline__ void face_march(const FvParams& p, float hL, float un
 //    it (a, or b), and the wet formulas then give the dry-bed speeds (its
 //    depth, celerity and discharge are zero, so it enters nothing else).
 // About 50 instructions against 66; the rounding is another (the first-order
-// march keeps the form whose results its runs have always had).
+// march keeps the form whose results its runs have always had), no larger: the
+// difference of the discharges is rounded once, as there.
 template <bool kHll>
 __device__ __forceinline__ void face_lean(const FvParams& p, float hL, float unL, float utL, float zL, float hR,
                                           float unR, float utR, float zR, bool wall, float& F0, float& GL,
@@ -199,14 +200,15 @@ __device__ __forceinline__ void face_lean(const FvParams& p, float hL, float unL
     const float qL = hl * uL, qR = hr * uR;
     const float ML = fmaf(qL, uL, pL), MR = fmaf(qR, uR, pR);
     const float k = sL * rcp(fmaxf(sR - sL, 1e-30f));
-    const float H0 = fmaf(k, fmaf(sR, hr - hl, qL - qR), qL);
-    const float F1 = fmaf(k, fmaf(sR, qR - qL, ML - MR), ML);
+    const float dq = fmaf(-hr, uR, qL);
+    const float H0 = fmaf(k, fmaf(sR, hr - hl, dq), qL);
+    const float F1 = fmaf(k, fmaf(-sR, dq, ML - MR), ML);
     F0 = wall ? 0.0f : H0;
     GL = F1 - pL;
     GR = F1 - pR;
     if (kHll) {
-        const float tL = qL * utL, tR = qR * utR;
-        const float H2 = fmaf(k, fmaf(sR, hr * utR - hl * utL, tL - tR), tL);
+        const float tL = qL * utL;
+        const float H2 = fmaf(k, fmaf(sR, fmaf(hr, utR, -(hl * utL)), fmaf(-qR, utR, tL)), tL);
         F2 = wall ? 0.0f : H2;
     } else {
         F2 = F0 * (F0 >= 0.0f ? utL : utR);
@@ -584,14 +586,14 @@ __device__ __forceinline__ V4 operator-(const V4& a, const V4& b)
 // cell c reconstructed at its two faces in one direction from the differences
 // f (to the next cell) and g (from the cell before); half: 1/2, or 0 for a
 // ghost or next to a dry cell (no slope).  Returns the change of the surface
-// across the cell.  A face value lies between the cell's and its mean with a
+// across the cell, between the face values as rounded.  A face value lies between the cell's and its mean with a
 // neighbour, so a face is dry only where the cell is, and its velocity is then 0.
 __device__ __forceinline__ float recon(const V4& c, const V4& f, const V4& g, float half, V4& lo, V4& hi)
 {
     const V4 m{minmod(f.h, g.h), minmod(f.eta, g.eta), minmod(f.u, g.u), minmod(f.v, g.v)};
     lo = V4{fmaf(-half, m.h, c.h), fmaf(-half, m.eta, c.eta), fmaf(-half, m.u, c.u), fmaf(-half, m.v, c.v)};
     hi = V4{fmaf(half, m.h, c.h), fmaf(half, m.eta, c.eta), fmaf(half, m.u, c.u), fmaf(half, m.v, c.v)};
-    return (half + half) * m.eta;
+    return hi.eta - lo.eta;
 }
 
 // One Runge-Kutta stage of the second-order variant over one tile (kStage 1:
@@ -604,7 +606,11 @@ __device__ __forceinline__ float recon(const V4& c, const V4& f, const V4& g, fl
 // less 1/2 g h*^2), the centred term 1/2 g (h_w + h_e)(z_e - z_w); the squares
 // and that term are together 1/2 g (h_w + h_e)(eta_e - eta_w), and h_w + h_e is
 // twice the cell's depth, so a cell receives G_e - G_w + g h (eta_e - eta_w):
-// one multiply-add, and nothing where the surface is level.
+// one multiply-add, and nothing where the surface is level.  eta_e - eta_w is
+// taken from the face values as rounded, which the faces used too: the slope
+// itself, unrounded, leaves 3 % more rounding error in the discharges after
+// eight steps (rms on long waves 1.10e-8 m^2/s; 1.06e-8 so, and 1.07e-8 with the
+// terms as squares).
 //
 // What bounds it: VALU issue up to a few million cells, HBM (72 B a cell over
 // the two stages) beyond.  Before this form (general faces and limiter, window
