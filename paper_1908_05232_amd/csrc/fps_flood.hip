@@ -1384,13 +1384,21 @@ hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t 
 //   3000^2      102.6  80.4  75.2  72.2  70.3     16 (9,212)
 // and the flood launch of 6 x 2048^2: 365, 273, 223, 200, 193 (201 at 32).  Beyond
 // 8,192 waves of one grid the partials take a launch more (fv_reduce_kernel).
+// The waves of all members of a launch count, and all get one height: a mix of
+// heights gives the XCDs, each with a run of as many waves, unequal work (four
+// grids each of 1024, 512, 256 and 716 a side 64.6 us a step at 16 rows, 71.0 with
+// at least 1,024 waves a member).  But members stop, or are dry, and the others
+// then march alone: an average member must keep 512 waves, half a wave a SIMD,
+// beyond four rows.  That mix gets 8 rows (65.5 us), and its members left alone take
+// 60.0, 29.8, 21.0 and 41.4 us, where 16 rows took 59.2, 33.2, 22.2 and 47.8; 32 x
+// 256^2 gets 4: 31.8 us, alone 16.9 (32.1 and 19.1 at 8).
 int fv_rows_per_wave(const fps_grid_desc* d, int S)
 {
     for (int H = 16; H > 1; H >>= 1) {
         const int64_t enough = H >= 16 ? 6000 : H >= 8 ? 4096 : H >= 4 ? 2560 : 2300;
         int64_t tiles = 0;
         for (int k = 0; k < S; ++k) tiles += fv_tiles(d[k].nx, d[k].ny, H);
-        if (tiles >= enough) return H;
+        if (tiles >= enough && (H <= 4 || tiles >= (int64_t)512 * S)) return H;
     }
     return 1;
 }
