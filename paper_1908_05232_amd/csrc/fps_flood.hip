@@ -1372,15 +1372,22 @@ hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t 
 // Rows per wave before any tuning: the longest march (fewest halo rows and
 // partials) that still leaves enough waves to fill the chip and hide its loads;
 // the fewer rows, the more a halving costs, so the fewer waves will do.
-// Measured, a whole step (us) at 1, 2, 4, 8, 16 rows:
-//   400^2        13.8  14.6  14.8  17.4  22.4      1 (1,400 waves at 2)
-//   512^2        15.1  14.8  16.1  17.4  22.3      2 (2,304)
-//   700 x 500    16.5  15.1  16.2  17.5  22.6      2 (3,000)
-//   1811 x 364   23.0  18.3  17.7  19.7  22.7      4 (2,730)
-//   1024^2       26.9  24.7  21.5  23.0  26.8      4 (4,352)
-//   1531 x 977   31.5  27.9  24.4  26.8  27.7      4 (6,125; 3,075 at 8)
-//   1500^2       39.4  33.9  33.5  30.6  33.4      8 (4,700)
-//   2048^2       56.4  46.7  44.3  45.4  44.6      8 (8,704; 4,352 at 16; second order 86.7, 82.3, 83.6)
+// Measured, a whole step (us) at 1, 2, 4, 8, 16 rows, and the waves the rule asks
+// of a height, between the sizes on either side of the line:
+//   400^2        11.9  12.5  13.1  15.6  20.6      1 (1,400 waves at 2)
+//   440^2        13.0  12.7  13.1  15.7  20.6      2 (1,760)                   2 rows: 1,600
+//   480^2        13.1  12.7  13.0  15.7  20.7      2
+//   512^2        13.3  13.2  14.2  15.5  20.6      2
+//   620^2        15.1  14.2  14.3  15.6  20.8      2 (1,550 at 4)
+//   768^2        20.6  15.5  15.9  17.6  20.9      2 (2,496)
+//   1811 x 364   23.0  18.3  17.7  19.7  22.7      4 (2,730)                   4 rows: 2,560
+//   860^2        22.0  16.8  16.1  17.9  20.9      4 (3,010)
+//   1024^2       25.3  23.0  19.6  21.2  24.9      4 (2,176 at 8)
+//   1200^2       29.3  26.1  22.3  22.0  25.6      4 (3,000)
+//   1400^2       33.8  29.5  26.0  25.8  26.2      4 (4,025)                   8 rows: 4,096
+//   1600^2       39.2  33.9  33.5  31.6  31.7      8 (5,200; 2,600 at 16)
+//   2048^2       54.6  45.2  42.6  43.7  42.7      8 (4,352; second order 84.7, 80.6, 81.8)
+//   2400^2       68.4  55.2  51.6  52.2  48.7     16 (5,850)                  16 rows: 5,000
 //   3000^2      102.6  80.4  75.2  72.2  70.3     16 (9,212)
 // and the flood launch of 6 x 2048^2: 365, 273, 223, 200, 193 (201 at 32).  Beyond
 // 8,192 waves of one grid the partials take a launch more (fv_reduce_kernel).
@@ -1395,7 +1402,7 @@ hipError_t launch_fv_reduce(const Batch& b, int s_first, int count, hipStream_t 
 int fv_rows_per_wave(const fps_grid_desc* d, int S)
 {
     for (int H = 16; H > 1; H >>= 1) {
-        const int64_t enough = H >= 16 ? 6000 : H >= 8 ? 4096 : H >= 4 ? 2560 : 2300;
+        const int64_t enough = H >= 16 ? 5000 : H >= 8 ? 4096 : H >= 4 ? 2560 : 1600;
         int64_t tiles = 0;
         for (int k = 0; k < S; ++k) tiles += fv_tiles(d[k].nx, d[k].ny, H);
         if (tiles >= enough && (H <= 4 || tiles >= (int64_t)512 * S)) return H;
