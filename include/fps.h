@@ -18,8 +18,9 @@
  *  - Pointers documented "device" are HIP device pointers owned by the caller;
  *    they must stay valid until rebinding or fps_destroy.  The library never
  *    allocates or frees device memory: all scratch lives in the caller's
- *    workspace (fps_workspace_bytes).  "host" pointers are read during the
- *    call only.
+ *    workspace (fps_workspace_bytes).  A handle holds 1.4 KB of pinned host
+ *    memory per scenario, which polls are written to.  "host" pointers are
+ *    read during the call only.
  *  - Every call returns an fps_status.  An invalid argument returns
  *    FPS_E_INVALID and changes nothing.  No C++ exception crosses this ABI.
  *  - Stepping is asynchronous on the stream given to fps_create; numeric faults
@@ -287,7 +288,8 @@ int fps_set_flood_frozen(fps_sim* sim, int32_t frozen);
 
 /* Per-cell evacuee counts that raise the Manning coefficient (sec. 2.3) for
    a simulation with no agents bound: device int32 [ny][nx], copied
-   (asynchronously) and kept until the next call; NULL clears them.
+   (asynchronously) and kept until the next call; NULL clears them.  Steps
+   that the caller has captured use the counts of the replay.
    FPS_E_STATE when agents are bound (their counts are used). */
 int fps_set_occupancy(fps_sim* sim, const int32_t* counts);
 

@@ -335,7 +335,6 @@ void fill_scn(const fps_sim* s, Scn& c)
     p.jmask = s->jmask;
     p.jb = s->jb > 0 ? s->jb : 1;
     p.jbx = (s->G.nx + p.jb - 1) / p.jb;
-    p.jby = (s->G.ny + p.jb - 1) / p.jb;
 
     PedParams& q = c.ped;
     q.x = s->x; q.y = s->y; q.vx = s->vx; q.vy = s->vy; q.vbase = s->vbase;

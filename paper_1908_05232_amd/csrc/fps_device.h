@@ -106,7 +106,7 @@ __device__ __forceinline__ StepState step_state(const FPS_GLOBAL DevState* st)
 }
 
 // A parameter record by value, all of its words loaded before any is used (the
-// same for the record itself: at most six vectors of 16 words).
+// same for the record itself: at most five vectors of 16 words).
 template <class T>
 __device__ __forceinline__ T all_at_once(const T& record)
 {
@@ -123,36 +123,6 @@ __device__ __forceinline__ T all_at_once(const T& record)
     T out;
     __builtin_memcpy(&out, w, sizeof(T));
     return out;
-}
-
-__device__ __forceinline__ double hydro_q(const DevState* st, double t)
-{
-    int n = st->nh;
-    if (n <= 0) return 0.0;
-    if (t <= st->hyd_t[0]) return st->hyd_q[0];
-    if (t >= st->hyd_t[n - 1]) return st->hyd_q[n - 1];
-    for (int k = 0; k + 1 < n; ++k) {
-        if (t >= st->hyd_t[k] && t <= st->hyd_t[k + 1]) {
-            double w = (t - st->hyd_t[k]) / (st->hyd_t[k + 1] - st->hyd_t[k]);
-            return st->hyd_q[k] + w * (st->hyd_q[k + 1] - st->hyd_q[k]);
-        }
-    }
-    return st->hyd_q[n - 1];
-}
-
-// exact integral of the piecewise-linear hydrograph over [a, b] (sec. 3.1)
-__device__ inline double hydro_integral(const DevState* st, double a, double b)
-{
-    if (st->nh <= 0 || !(b > a)) return 0.0;
-    double total = 0.0, lo = a;
-    for (int k = 0; k < st->nh; ++k) {
-        double tk = st->hyd_t[k];
-        if (tk > lo && tk < b) {
-            total += 0.5 * (hydro_q(st, lo) + hydro_q(st, tk)) * (tk - lo);
-            lo = tk;
-        }
-    }
-    return total + 0.5 * (hydro_q(st, lo) + hydro_q(st, b)) * (b - lo);
 }
 
 // Exclusive scan of the bin histogram by one block of kScanThreads: tiles of

@@ -320,17 +320,19 @@ __device__ __forceinline__ int xcd_tile_block(int b, int nblocks)
     return (b & 7) * per + (b >> 3);
 }
 
-// What bounds it: VALU issue while it takes more than about 200 instructions a
-// row of 62 cells, HBM below that.  With 266 a row (22 of them copies of the
-// rows in flight and the carried face, 20 more for volumes that only edge
-// cells have) the counters showed the VALU busy for all of the launch: 8192^2
-// wet cells, 499 us at 16 rows a wave.  Written with four rows a turn (no
-// copies), rare work behind uniform branches and the leaner face, 212 a row:
-// 423 us, 28 B a cell at 4.45 TB/s (a 1 GiB copy on the card: 4.95 TB/s), with
-// the same bits.  1531 x 977: 17.7 -> 16.5 us; 6 x 2048^2 with people: 204 ->
-// 184 us.  Loads run four rows ahead, so a wave keeps 16 of them in flight.
-// kPeople: some scenario has evacuee counts (they raise the friction); without
-// any the counts are not read (4 of 32 B a cell).
+// What bounds it: VALU issue, with HBM close behind.  Counted on 8192^2 wet cells
+// at 16 rows a wave: 3,526 vector instructions a wave, 220 a row of 62 cells, one
+// every 4.1 cycles a SIMD (a wave's instruction takes four); 427 us, 28 B a cell
+// at 4.40 TB/s (a 1 GiB copy on the card: 4.95 TB/s).  The form before took 4,449
+// (copies of the rows in flight and of the carried face, volumes that only edge
+// cells have) and 499 us; this one takes four rows a turn (no copies), has rare
+// work behind uniform branches and the leaner face, with the same bits.  1531 x
+// 977: 17.7 -> 16.5 us; 6 x 2048^2 with people: 204 -> 191 us.  Loads run four
+// rows ahead, so a wave keeps 16 of them in flight.
+// kPeople: some scenario may have evacuee counts (they raise the friction), or
+// the caller captures the step and may set some later; else the counts are not
+// read (4 of 32 B a cell).  A branch on a word of device memory instead, around
+// two marches in one kernel, cost 0.5 to 1 % of a step.
 template <bool kOne, bool kHll, bool kPeople>
 __global__ __launch_bounds__(kFvBlock) void fv_step_kernel(Batch B)
 {
@@ -612,8 +614,9 @@ __device__ __forceinline__ float recon(const V4& c, const V4& f, const V4& g, fl
 // eight steps (rms on long waves 1.10e-8 m^2/s; 1.06e-8 so, and 1.07e-8 with the
 // terms as squares).
 //
-// What bounds it: VALU issue up to a few million cells, HBM (72 B a cell over
-// the two stages) beyond.  Before this form (general faces and limiter, window
+// What bounds it: VALU issue up to a few million cells (counted at 2048^2 and 8
+// rows a wave: 223 and 289 vector instructions a row, one every 4.3 cycles a SIMD
+// while waves run), HBM (72 B a cell over the two stages) beyond.  Before this form (general faces and limiter, window
 // and carried faces moved along every row, one row of U^n loaded where it is
 // used) both stages took 122 us at 2048^2 and 16 rows a wave; now 70 us at 8
 // rows, and 943 us at 8192^2 (5.1 TB/s).  It holds 96 VGPRs in stage 1 and 115
@@ -661,10 +664,8 @@ __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
     const bool mirror_x = (i < 0 && p.bc[0] == FPS_BC_WALL) || (i >= p.nx && p.bc[1] == FPS_BC_WALL);
     // the west face of this lane's column is a wall face
     const bool xwall = (i == 0 && p.bc[0] == FPS_BC_WALL) || (i == p.nx && p.bc[1] == FPS_BC_WALL);
-    // what only the strips on the west and east sides do (wave-uniform); the
-    // last strip may hold only the ghosts of the east side, so it is the one
-    // whose lanes reach it
-    const bool first_strip = sx == 0, last_strip = sx * kStrip2 + kStrip2 >= p.nx;
+    // what only the strips on the west and east sides do (wave-uniform)
+    const bool first_strip = sx == 0, last_strip = sx == p.nsx - 1;
     const bool out_w = first_strip && p.bc[0] == FPS_BC_TRANSMISSIVE, out_e = last_strip && p.bc[1] == FPS_BC_TRANSMISSIVE;
     const int out_s = p.bc[2] == FPS_BC_TRANSMISSIVE ? 0 : -1, out_n = p.bc[3] == FPS_BC_TRANSMISSIVE ? p.ny - 1 : -1;
     const bool inflow_x = (p.inflow_side == FPS_SIDE_W && first_strip) || (p.inflow_side == FPS_SIDE_E && last_strip);

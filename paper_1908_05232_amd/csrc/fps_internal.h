@@ -98,7 +98,7 @@ struct FvParams {
     // ([ceil(ny/jb)][jbx] blocks of jb x jb cells) update; the time step is
     // then dt_max, not the CFL step
     const uint8_t* jmask;
-    int jb, jbx, jby;
+    int jb, jbx;
 };
 
 // A pointer of a parameter record.  Read from memory, as the records of an

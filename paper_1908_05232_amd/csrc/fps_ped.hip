@@ -935,10 +935,10 @@ __global__ __launch_bounds__(kPedBlock) void bin_sort_all_kernel(Batch B)
 
 // --- multi-block bin scan (scenarios that are not binned in LDS) --------------
 // Instead of one block per scenario walking all its bins (2 us a step more at
-// 4,096 bins, 6 at 32,400): the count of every
-// chunk of kChunkBins bins (one block each, beside the end-of-step blocks), and
-// the scan of every chunk (one block each) from the sum of the counts before
-// it, which clears the histogram behind it.  Integer sums: the bin starts are
+// 4,096 bins, 6 at 32,400): the count of every chunk of kChunkBins bins (a wave
+// each, sixteen to a block beside the end-of-step blocks), and the scan of every
+// chunk (one block each) from the sum of the counts before it, which clears the
+// histogram behind it.  Integer sums: the bin starts are
 // those of the one-block scan.  A scenario that does not step (past its end
 // time) keeps its bins: the end-of-step block records whether it stepped,
 // before it may mark it inactive.  Measured: the counts in a launch of their
