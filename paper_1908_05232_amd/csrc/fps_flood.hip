@@ -616,12 +616,13 @@ __device__ __forceinline__ float recon(const V4& c, const V4& f, const V4& g, fl
 //
 // What bounds it: VALU issue up to a few million cells (counted at 2048^2 and 8
 // rows a wave: 223 and 289 vector instructions a row, one every 4.3 cycles a SIMD
-// while waves run), HBM (72 B a cell over the two stages) beyond.  Before this form (general faces and limiter, window
-// and carried faces moved along every row, one row of U^n loaded where it is
-// used) both stages took 122 us at 2048^2 and 16 rows a wave; now 70 us at 8
-// rows, and 943 us at 8192^2 (5.1 TB/s).  It holds 96 VGPRs in stage 1 and 115
-// in stage 2 (5 and 4 waves per SIMD); the scheduling barriers keep the two
-// faces of a row from being interleaved, which would take 123.
+// while waves run), HBM (72 B a cell over the two stages) beyond.  Before this
+// form (general faces and limiter, window and carried faces moved along every
+// row, one row of U^n loaded where it is used) both stages took 122 us at 2048^2
+// and 16 rows a wave; now 70 us at 8 rows, and 972 us at 8192^2 (4.97 TB/s).  It
+// holds 98 VGPRs in stage 1 and 116 in stage 2 (four waves a SIMD; stage 1 at 96
+// and five took as long); the scheduling barriers keep the two faces of a row
+// from being interleaved, which would take 123.
 template <bool kOne, bool kHll, bool kPeople, int kStage>
 __global__ __launch_bounds__(kFvBlock) void fv2_stage_kernel(Batch B)
 {
