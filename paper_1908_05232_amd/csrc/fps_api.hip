@@ -612,10 +612,15 @@ int run_steps(Engine* e, int32_t n, KernelEvents* K)
         HIPCHK_E(e, hipEventRecord(e->ev_out, e->cap));
         HIPCHK_E(e, hipStreamWaitEvent(e->stream, e->ev_out, 0));
     }
-    hipStreamCaptureStatus by_caller = hipStreamCaptureStatusNone;
-    if (done < n && !e->people) HIPCHK_E(e, hipStreamIsCapturing(e->stream, &by_caller));
+    // (a stream that cannot tell is left to its launches)
+    bool by_caller = false;
+    if (done < n && !e->people) {
+        hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(e->stream, &cs) != hipSuccess) (void)hipGetLastError();
+        by_caller = cs != hipStreamCaptureStatusNone;
+    }
     for (; done < n; ++done) {
-        rc = step_launches(e, e->stream, K, by_caller != hipStreamCaptureStatusNone);
+        rc = step_launches(e, e->stream, K, by_caller);
         if (rc != FPS_OK) return rc;
     }
     if (n > 0) HIPCHK_E(e, launch_sync_back(batch_of(e), e->max_cells, e->stream));
